@@ -114,7 +114,7 @@ typedef struct {
     int64_t near_nnz;     /* (target, node) coefficients of the stored near field, 0 if none */
     int64_t near_bytes;   /* device bytes of the stored near field */
     int32_t m2l_keys_per_item; /* schedule: M2L keys per workgroup item (tfmm_plan_autotune) */
-    int32_t p2p_wide;          /* schedule: 1 if one-field P2P blocks run four wavefronts */
+    int32_t p2p_wide;          /* schedule: 1 if per-tet P2P blocks of one or two fields run four wavefronts */
     /* one-field near field over shared mesh entities: (target, entity)
        evaluations per evaluation (nodes: a distance, edges: a logarithm,
        faces: a solid angle) */
@@ -396,8 +396,9 @@ int tfmm_demag_field_nodes(tfmm_plan plan, const double *u, double *H_node, void
 
 /*
  * Schedule tuning.  Times evaluations of one (synthetic) field on hip_stream
- * for a few choices of the M2L work item size (keys per workgroup) and of the
- * P2P workgroup shape, and keeps the fastest; the arithmetic, and so every
+ * for a few choices of the M2L work item size (keys per workgroup) and, where
+ * one field runs the per-tet near field, of its workgroup shape, and keeps
+ * the fastest; the arithmetic, and so every
  * result, is the same for all choices.  Synchronises the stream; allocates
  * and frees scratch device memory for one field.
  * Errors: TFMM_EINVAL (NULL or host-only plan), TFMM_EDEVICE.
@@ -406,8 +407,9 @@ int tfmm_plan_autotune(tfmm_plan plan, void *hip_stream);
 
 /*
  * Set the schedule knobs that tfmm_plan_autotune picks: M2L keys per
- * workgroup item of the tiled form (16..4096), the P2P workgroup shape for
- * one or two fields (p2p_wide 1: four wavefronts per block; 0: one), and
+ * workgroup item of the tiled form (16..4096), the per-tet P2P workgroup
+ * shape for one or two fields (p2p_wide 1: four wavefronts per block; 0:
+ * one; one field takes it only beside the surrogate's band), and
  * the M2L form for fewer than 16 fields with FP64 or FP32 translations
  * (m2l_packed 1: the translations of each key are packed 16 columns at a
  * time inside blocks of target cells, m2l_groups_per_item (16..4096) such

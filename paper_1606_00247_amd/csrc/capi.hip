@@ -112,6 +112,28 @@ T *dev_upload(const std::vector<T> &h, int64_t &bytes)
 
 namespace tfmm {
 
+// A device list needed only while the plan is uploaded.
+struct ScratchList {
+    int32_t *d;
+    explicit ScratchList(int32_t *p) : d(p) {}
+    ScratchList(const ScratchList &) = delete;
+    ScratchList &operator=(const ScratchList &) = delete;
+    ~ScratchList() { (void)hipFree(d); }
+};
+
+// Distance class of target cell a from source cell b: the squared gap between
+// the cubes in quarters of b's squared side, the last class all that is farther.
+constexpr int kRings = 64;
+static int cell_ring(const Cell &a, const Cell &b)
+{
+    const int l = std::max(a.level, b.level), sa = l - a.level, sb = l - b.level;
+    auto gap = [&](int64_t ia, int64_t ib) {
+        return (double)std::max<int64_t>({0, (ia << sa) - ((ib + 1) << sb), (ib << sb) - ((ia + 1) << sa)});
+    };
+    const double g0 = gap(a.ix, b.ix), g1 = gap(a.iy, b.iy), g2 = gap(a.iz, b.iz), s = (double)(1ll << sb);
+    return (int)std::min(kRings - 1.0, 4.0 * (g0 * g0 + g1 * g1 + g2 * g2) / (s * s));
+}
+
 void upload_plan(DevicePlan &dp)
 {
     const HostPlan &hp = dp.hp;
@@ -199,14 +221,25 @@ void upload_plan(DevicePlan &dp)
             std::vector<int32_t> fillp(cnt.begin(), cnt.end() - 1);
             for (size_t i = 0; i < hp.p2p_b.size(); ++i) tl[fillp[hp.p2p_b[i]]++] = hp.p2p_a[i];
         }
-        std::vector<int32_t> blk, idx;
+        std::vector<int32_t> blk, idx, by_ring;
+        std::vector<int8_t> ring;
         for (int64_t b = 0; b < C; ++b) {
             if (cnt[b + 1] == cnt[b]) continue;
             const int64_t ib = (int64_t)idx.size();
+            // target leaves by distance: the wavefronts of the nearest take the
+            // near field's closer forms, the others hardly ever do (point
+            // sources have one form and keep the octree's order)
+            int32_t at[kRings + 1] = {0};
+            ring.clear();
             for (int32_t j = cnt[b]; j < cnt[b + 1]; ++j) {
-                const Cell &A = hp.cells[tl[j]];
-                for (int32_t s = A.xbeg; s < A.xend; ++s) idx.push_back(s);
+                ring.push_back((int8_t)(hp.points ? 0 : cell_ring(hp.cells[tl[j]], hp.cells[b])));
+                ++at[ring.back() + 1];
             }
+            for (int r = 0; r < kRings; ++r) at[r + 1] += at[r];
+            by_ring.resize(ring.size());
+            for (size_t j = 0; j < ring.size(); ++j) by_ring[at[ring[j]]++] = tl[cnt[b] + j];
+            for (const int32_t a : by_ring)
+                for (int32_t s = hp.cells[a].xbeg; s < hp.cells[a].xend; ++s) idx.push_back(s);
             const int64_t ie = (int64_t)idx.size();
             if (ie > INT32_MAX) throw PlanError{TFMM_ENOTSUP, "near-field target list exceeds 2^31 entries"};
             const Cell &Bc = hp.cells[b];
@@ -248,27 +281,38 @@ void upload_plan(DevicePlan &dp)
             const int64_t nt = (int64_t)tp.blk[k + 3] - tp.blk[k + 2];
             for (int32_t ch = tp.blk[k]; ch < tp.blk[k + 1]; ++ch) {
                 dp.topo_evals[0] += nt * tp.ch_i[8 * (size_t)ch + 3];
-                dp.topo_evals[1] += nt * tp.ch_i[8 * (size_t)ch + 5];
-                dp.topo_evals[2] += nt * tp.ch_i[8 * (size_t)ch + 7];
+                dp.topo_evals[1] += nt * (tp.ch_i[8 * (size_t)ch + 5] - tp.pad[2 * (size_t)ch]);
+                dp.topo_evals[2] += nt * (tp.ch_i[8 * (size_t)ch + 7] - tp.pad[2 * (size_t)ch + 1]);
             }
         }
         dp.n_topo_ch = (int32_t)(tp.ch_i.size() / 8);
-        dp.n_topo_edges = (int64_t)tp.ed_il.size();
-        dp.n_topo_faces = (int64_t)(tp.fc_n.size() / 3);
-        dp.topo_blk = dev_upload(tp.blk, B);
+        // one-field work items: 64 targets of one block each
+        std::vector<int32_t> items;
+        for (size_t k = 0; k + 3 < tp.blk.size(); k += 4)
+            for (int32_t i = tp.blk[k + 2]; i < tp.blk[k + 3]; i += 64) {
+                const int32_t it[4] = {tp.blk[k], tp.blk[k + 1], i, std::min(tp.blk[k + 3], i + 64)};
+                items.insert(items.end(), it, it + 4);
+            }
+        dp.n_topo_items = (int32_t)(items.size() / 4);
+        dp.topo_item = dev_upload(items, B);
         dp.topo_ch_i = dev_upload(tp.ch_i, B);
         dp.topo_ch_c = dev_upload(tp.ch_c, B);
         dp.topo_w = dev_upload(tp.nd_w, B);
-        dp.topo_ab = dev_upload(tp.ed_ab, B);
-        dp.topo_il = dev_upload(tp.ed_il, B);
-        dp.topo_pqr = dev_upload(tp.fc_pqr, B);
-        dp.topo_n = dev_upload(tp.fc_n, B);
-        dp.topo_a2 = dev_upload(tp.fc_a2, B);
         dp.topo_inc = dev_upload(tp.inc, B);
-        std::vector<double> zA(4 * (size_t)std::max<int64_t>(dp.n_topo_faces, 1)),
-            zB(11 * (size_t)std::max<int64_t>(dp.n_topo_edges, 1));
-        dp.topo_A = dev_upload(zA, B);
-        dp.topo_B = dev_upload(zB, B);
+        if (dp.n_topo_ch > 0) {
+            const size_t ne = tp.ed_ab.size() / 2, nf = tp.fc_pqr.size() / 3;
+            auto room = [&](auto *&d, size_t n) {
+                hip_check(hipMalloc(&d, n * sizeof(*d)), "hipMalloc near-field entities");
+                B += (int64_t)(n * sizeof(*d));
+            };
+            room(dp.topo_edge, ne);
+            room(dp.topo_face, nf);
+            room(dp.topo_edge_w, ne);
+            room(dp.topo_face_w, nf);
+            int64_t tmp = 0;
+            ScratchList ab{dev_upload(tp.ed_ab, tmp)}, pqr{dev_upload(tp.fc_pqr, tmp)};
+            build_topo_records(dp, ab.d, pqr.d);
+        }
     }
     {
         dp.n_m2l_keys = (int32_t)(hp.m2l_keys.size() / 4);
@@ -310,9 +354,9 @@ void free_plan(DevicePlan &dp)
     dp.event_pool.clear();
     void *ptrs[] = {dp.tet_xyz, dp.tet_node, dp.tet_perm, dp.tgt_xyz, dp.tgt_perm, dp.tgt_leaf, dp.cell_c, dp.cell_i,
                     dp.p2m_cells, dp.m2m_cells, dp.l2l_cells, dp.p2p_blk, dp.p2p_idx, dp.quad, dp.far_rule, dp.node_lump, dp.tet_mom, dp.Q,
-                    dp.L, dp.Qt, dp.Qtf, dp.m2l_keys, dp.m2l_D, dp.m2l_Df, dp.sur_w, dp.sur_wb, dp.band_pairs, dp.band_rule, dp.topo_blk,
-                    dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_ab, dp.topo_il, dp.topo_pqr, dp.topo_n, dp.topo_a2,
-                    dp.topo_inc, dp.topo_A, dp.topo_B, dp.near_off, dp.near_nc, dp.near_cols, dp.near_val, dp.near_items};
+                    dp.L, dp.Qt, dp.Qtf, dp.m2l_keys, dp.m2l_D, dp.m2l_Df, dp.sur_w, dp.sur_wb, dp.band_pairs, dp.band_rule, dp.topo_item,
+                    dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_inc, dp.topo_edge, dp.topo_face, dp.topo_edge_w, dp.topo_face_w,
+                    dp.near_off, dp.near_nc, dp.near_cols, dp.near_val, dp.near_items};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto &t : dp.m2l_tiles) {

@@ -43,6 +43,28 @@ void hip_check(hipError_t e, const char *what);
 // Kernel timing slots
 enum { KT_P2M = 0, KT_M2M, KT_M2L, KT_L2L, KT_L2P, KT_P2P, KT_COUNT };
 
+// Shared mesh entities of the one-field near field: geometry once per plan
+// (k_topo_static), field weights once per evaluation (k_topo_coef) in arrays
+// of their own, so that an evaluation writes whole lines.  Corners are
+// chunk-local node indices.
+struct TopoEdge {
+    double L, il, l2;        // length, its inverse and square
+    uint32_t next, own;      // corners (a byte each) of the edge two on in the chunk (the last two name their own); its own
+};
+struct TopoFace {
+    double l2pq, l2pr, l2qr;  // squared edge lengths
+    double n[3], h0;          // unit normal, its height over the origin
+    double a4;                // four times the area
+    uint32_t next, own;       // corners (a byte each) of the face two on; its own
+};
+struct TopoEdgeW {
+    double B[11];  // 2/L times the quadratic in y (1, y0, y1, y2, y0y0, y0y1, y0y2, y1y1, y1y2, y2y2); Gamma/2
+    double pad;
+};
+struct TopoFaceW {
+    double A[4];  // -2 times the affine weight (1, y0, y1, y2)
+};
+
 struct DevicePlan {
     HostPlan hp;
     int device = -1;
@@ -125,15 +147,15 @@ struct DevicePlan {
     int32_t n_p2p_blk = 0;
     int32_t *p2p_idx = nullptr;  // sorted-target indices
     int64_t n_p2p_idx = 0;
-    // shared mesh entities of the P2P blocks (see NearTopo) and the
-    // per-evaluation coefficients of one field: faces A [nf][4] (affine in
-    // y = x - chunk centroid), edges B [ne][11] (quadratic in y: 1, y0, y1,
-    // y2, y0y0, y0y1, y0y2, y1y1, y1y2, y2y2; then the constant g weight)
-    int32_t *topo_blk = nullptr, *topo_ch_i = nullptr, *topo_ab = nullptr, *topo_pqr = nullptr, *topo_inc = nullptr;
-    double *topo_ch_c = nullptr, *topo_w = nullptr, *topo_il = nullptr, *topo_n = nullptr, *topo_a2 = nullptr;
-    double *topo_A = nullptr, *topo_B = nullptr;
-    int32_t n_topo_ch = 0;
-    int64_t n_topo_edges = 0, n_topo_faces = 0;
+    // shared mesh entities of the P2P blocks (see NearTopo) and the work items
+    // over them: [n][4] chunk begin, chunk end, target begin, target end (<= 64)
+    int32_t *topo_item = nullptr, *topo_ch_i = nullptr, *topo_inc = nullptr;
+    double *topo_ch_c = nullptr, *topo_w = nullptr;
+    TopoEdge *topo_edge = nullptr;
+    TopoFace *topo_face = nullptr;
+    TopoEdgeW *topo_edge_w = nullptr;
+    TopoFaceW *topo_face_w = nullptr;
+    int32_t n_topo_ch = 0, n_topo_items = 0;
     int64_t topo_evals[3] = {0, 0, 0};  // (target, node / edge / face) evaluations per one-field evaluation
     bool p2p_topo = true;  // single-field near field over shared entities
     // stored near-field operator (optional, built by store_near): per cell
@@ -212,6 +234,9 @@ void free_plan(DevicePlan &dp);
 void ensure_expansions(DevicePlan &dp, int32_t F);
 // Geometric moments of the tets (after the rule and cells are uploaded).
 void build_tet_moments(DevicePlan &dp);
+// Geometry of the entity records (after the chunks are uploaded): edges' and
+// faces' chunk-local corners ab [ne][2], pqr [nf][3] (device).
+void build_topo_records(DevicePlan &dp, const int32_t *ab, const int32_t *pqr);
 // Fill the M2L derivative tables (after the keys are uploaded).
 void build_m2l_table(DevicePlan &dp);
 // Tiles of tpt target cells (16, 8, 4, 2 or 1), built and uploaded once.

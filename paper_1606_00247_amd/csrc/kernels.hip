@@ -1717,20 +1717,72 @@ __global__ __launch_bounds__(kPtThreads) void k_p2p_points(const int32_t *__rest
 //   A_F(y)   = sum_{T, k: face k of T is F} alpha_{T,k}(y)                     (affine)
 //   B_e(y)   = sum_{T, k, e in face k} s_{k,e} alpha_{T,k}(y) n_k.(d_a x d_b)  (quadratic)
 //   Gamma_e  = sum_{T: e in T} gamma_{T,e}
-// (alpha affine in y, d = v - x).  k_topo_coef forms them once per evaluation;
-// k_p2p_topo then evaluates one square root per node, one log per edge and
-// one solid angle per face of the chunk for every target.
+// (alpha affine in y, d = v - x).  k_topo_static fills the geometry of every
+// entity record once per plan, k_topo_coef the field weights once per
+// evaluation; k_p2p_topo then evaluates one square root per node, one log per
+// edge and one solid angle per face of the chunk for every target.
 // ---------------------------------------------------------------------------
 // One wavefront takes kTopoChunksPerWave chunks, 16 lanes (one per tet) each.
 constexpr int kTopoChunksPerWave = 4;
 static_assert(kTopoTets <= 64 / kTopoChunksPerWave, "one lane per tet of a chunk");
+static_assert(kTopoEdges <= 64 && kTopoFaces <= 64, "one bit per entity, and its lines within one load a lane");
+static_assert(kTopoEdges % 2 == 0 && kTopoFaces % 2 == 0, "pairs");
+
+// Geometry of the entity records; one wavefront per chunk.
+__global__ __launch_bounds__(64) void k_topo_static(const int32_t *__restrict__ ch_i, int nch,
+                                                    const double *__restrict__ w, const int32_t *__restrict__ ab,
+                                                    const int32_t *__restrict__ pqr, TopoEdge *__restrict__ edge,
+                                                    TopoFace *__restrict__ face)
+{
+    const int ch = blockIdx.x;
+    if (ch >= nch) return;
+    const int noff = ch_i[8 * ch + 2], eoff = ch_i[8 * ch + 4], ne = ch_i[8 * ch + 5], foff = ch_i[8 * ch + 6],
+              nf = ch_i[8 * ch + 7];
+    const double *wn = w + 4 * (int64_t)noff;
+    auto dist2 = [&](int a, int b) {
+        const double d0 = wn[4 * b] - wn[4 * a], d1 = wn[4 * b + 1] - wn[4 * a + 1], d2 = wn[4 * b + 2] - wn[4 * a + 2];
+        return (d0 * d0 + d1 * d1) + d2 * d2;
+    };
+    for (int i = threadIdx.x; i < ne; i += 64) {
+        const int64_t e = (int64_t)eoff + i;
+        const int a = ab[2 * e], b = ab[2 * e + 1];
+        TopoEdge &E = edge[e];
+        const int64_t en = e + (i + 2 < ne ? 2 : 0);
+        E.l2 = dist2(a, b);
+        E.L = sqrt(E.l2);
+        E.il = 1.0 / E.L;
+        E.own = (uint32_t)(a | b << 8);
+        E.next = (uint32_t)(ab[2 * en] | ab[2 * en + 1] << 8);
+    }
+    for (int i = threadIdx.x; i < nf; i += 64) {
+        const int64_t f = (int64_t)foff + i;
+        const int p = pqr[3 * f], q = pqr[3 * f + 1], r = pqr[3 * f + 2];
+        double u[3], v[3];
+        for (int k = 0; k < 3; ++k) {
+            u[k] = wn[4 * q + k] - wn[4 * p + k];
+            v[k] = wn[4 * r + k] - wn[4 * p + k];
+        }
+        const double n[3] = {u[1] * v[2] - u[2] * v[1], u[2] * v[0] - u[0] * v[2], u[0] * v[1] - u[1] * v[0]};
+        const double a2 = sqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]), ia = 1.0 / a2;
+        TopoFace &F = face[f];
+        for (int k = 0; k < 3; ++k) F.n[k] = n[k] * ia;
+        F.h0 = F.n[0] * wn[4 * p] + F.n[1] * wn[4 * p + 1] + F.n[2] * wn[4 * p + 2];
+        F.a4 = 2.0 * a2;
+        F.l2pq = dist2(p, q);
+        F.l2pr = dist2(p, r);
+        F.l2qr = dist2(q, r);
+        F.own = (uint32_t)(p | q << 8 | r << 16);
+        const int64_t fnx = f + (i + 2 < nf ? 2 : 0);
+        F.next = (uint32_t)(pqr[3 * fnx] | pqr[3 * fnx + 1] << 8 | pqr[3 * fnx + 2] << 16);
+    }
+}
 
 __global__ __launch_bounds__(64) void k_topo_coef(const int32_t *__restrict__ ch_i, const double *__restrict__ ch_c,
                                                   int nch, const int32_t *__restrict__ inc,
                                                   const double *__restrict__ tet_xyz,
                                                   const int32_t *__restrict__ tet_node, int64_t T,
-                                                  const double *__restrict__ M, double *__restrict__ A,
-                                                  double *__restrict__ Bc)
+                                                  const double *__restrict__ M, const TopoEdge *__restrict__ edge,
+                                                  TopoEdgeW *__restrict__ edge_w, TopoFaceW *__restrict__ face_w)
 {
     constexpr int LPC = 64 / kTopoChunksPerWave;  // lanes per chunk
     __shared__ double s_Aw[kTopoChunksPerWave][kTopoFaces][4];
@@ -1800,111 +1852,336 @@ __global__ __launch_bounds__(64) void k_topo_coef(const int32_t *__restrict__ ch
     }
     __syncthreads();
     if (!live) return;
-    for (int i = tl; i < nf * 4; i += LPC) A[(int64_t)foff * 4 + i] = (&s_A[0][0])[i];
-    for (int i = tl; i < ne * 11; i += LPC) Bc[(int64_t)eoff * 11 + i] = (&s_B[0][0])[i];
+    // the records hold -2 A (the solid angle enters as its half), 2 il B and
+    // Gamma / 2 (f and g enter as f/2 and 2 g)
+    for (int i = tl; i < nf * 4; i += LPC) face_w[(int64_t)foff + (i >> 2)].A[i & 3] = -2.0 * (&s_A[0][0])[i];
+    for (int i = tl; i < ne * 12; i += LPC) {
+        const int e = i / 12, q = i - 12 * e;
+        const double w = q < 10 ? 2.0 * edge[(int64_t)eoff + e].il : 0.5;
+        (&edge_w[(int64_t)eoff + e].B[0])[q] = q < 11 ? s_B[e][q] * w : 0.0;
+    }
 }
 
-// NT = 64: one wavefront per workgroup; NT = 256: four wavefronts share the
-// staged chunk (less LDS per wavefront).  The 256-thread form asks for 4
-// workgroups per CU but its 41 KB of LDS admits 3 (3 waves per SIMD); the
-// register allocation under that request gives the tightest entity loops
-// (asking for 3 lets it take 144 VGPRs, and the edge and face loops grow by
-// 7 and 9 instructions).
-template <int NT>
-__global__ __launch_bounds__(NT, NT == 64 ? 2 : 4) void k_p2p_topo(const int32_t *__restrict__ blk, int nblk,
+// Memory that no thread writes during the launch: uniform reads of it go to
+// the scalar unit whatever the compiler can prove about aliasing.
+template <typename T>
+using ScalarMem = T __attribute__((address_space(4)));
+template <typename T>
+__device__ __forceinline__ const ScalarMem<T> *scalar_mem(const T *p)
+{
+    return (const ScalarMem<T> *)p;
+}
+
+// Work item: up to 64 targets of one source block, one wavefront, one target
+// per lane, all chunks of the block.  Splitting a block's targets over
+// wavefronts, not one wavefront a block, fills the chip on small meshes (806
+// blocks of a 17^3 cube: 4.7 -> 0.45 ms).  The chunk's entities are the same for
+// every lane, so they are read on the scalar path, and only the corner
+// distances R, each lane its own column, live in LDS; no barrier is needed.
+// Corner distances and per-entity constants are all that the terms need (see
+// AtanhFar); the few targets close to an edge or face take a vote of the
+// wavefront into the shifted forms or, closer still, put the pair off to a
+// second loop.  The block's target list is ordered by distance, so that few
+// wavefronts hold such targets.
+// Bound: FP64 issue, about 45 slots a (target, edge) and 43 a (target, face);
+// the vector unit is busy 0.77 of the time.  40^3 cube (160M pairs, 11.7 tets a
+// block): 4.05 -> 2.1 ms against the form with difference vectors, cross
+// products and branch-free selects; 14.2 -> 11.0 ms on 853M pairs of a sphere
+// with 45 tets a block.  4 wavefronts a SIMD without spills beat 5 with 13
+// spilled registers (2.30 against 2.45 ms, field weights included); 2 and 4
+// wavefronts a workgroup were slower (+9%, +33%: their slots free up together).
+__global__ __launch_bounds__(64, 4) void k_p2p_topo(const int32_t *__restrict__ item, int nitems,
                                                     const int32_t *__restrict__ ch_i, const double *__restrict__ ch_c,
-                                                    const double *__restrict__ nw, const int32_t *__restrict__ eab,
-                                                    const double *__restrict__ eil, const int32_t *__restrict__ fpqr,
-                                                    const double *__restrict__ fn, const double *__restrict__ fa2,
-                                                    const double *__restrict__ A,
-                                                    const double *__restrict__ Bc, const int32_t *__restrict__ idx,
+                                                    const double *__restrict__ nw, const TopoEdge *__restrict__ edge,
+                                                    const TopoFace *__restrict__ face,
+                                                    const TopoEdgeW *__restrict__ edge_w,
+                                                    const TopoFaceW *__restrict__ face_w,
+                                                    const int32_t *__restrict__ idx,
                                                     const double *__restrict__ tgt_xyz,
                                                     const int32_t *__restrict__ tgt_perm, int64_t N,
                                                     double *__restrict__ u)
 {
-    __shared__ double s_w[kTopoNodes][4];  // rows of 4: node offsets are shifts, not multiplies
-    __shared__ double s_R[kTopoNodes][NT];
-    __shared__ int s_ea[kTopoEdges], s_eb[kTopoEdges];
-    __shared__ double s_il[kTopoEdges], s_B[kTopoEdges][11];
-    __shared__ int s_fp[kTopoFaces], s_fq[kTopoFaces], s_fr[kTopoFaces];
-    __shared__ double s_fn[kTopoFaces][3], s_fa[kTopoFaces], s_A[kTopoFaces][4];
-    const int b = xcd_item(nblk);
-    if (b < 0) return;
-    const int cb = blk[4 * b], ce = blk[4 * b + 1], ib = blk[4 * b + 2], ie = blk[4 * b + 3];
-    const int lane = threadIdx.x;
+    __shared__ double s_R[kTopoNodes][64];
+    const int lane = (int)threadIdx.x;
+    const int it = xcd_item(nitems);
+    if (it < 0) return;
+    const int cb = item[4 * it], ce = item[4 * it + 1], ib = item[4 * it + 2], ie = item[4 * it + 3];
+    const int s = idx[min(ib + lane, ie - 1)];  // the lanes past the end repeat the last target
+    const double x[3] = {tgt_xyz[s], tgt_xyz[N + s], tgt_xyz[2 * N + s]};
+    double *R = &s_R[0][lane];
+    double acc = 0.0;
+    // The scalar loads below each wait for their line; from HBM that would be
+    // most of the time.  So the lines of a chunk are all brought into L2 at
+    // once, by one vector load a lane, while the chunk before it is worked on.
+    auto line = [&](const auto *p, int n) {  // one of the 128-byte lines of p[0 .. n)
+        const uint32_t at = 128u * (uint32_t)lane;
+        return at < (uint32_t)(n * sizeof(*p)) ? *(const int32_t *)((const char *)p + at) : 0;
+    };
+    auto touch = [&](int ch) {
+        const int64_t eo = ch_i[8 * ch + 4], fo = ch_i[8 * ch + 6];
+        const int ne = ch_i[8 * ch + 5], nf = ch_i[8 * ch + 7];
+        return line(edge + eo, ne) + line(edge_w + eo, ne) + line(face + fo, nf) + line(face_w + fo, nf);
+    };
+    int seen = touch(cb);
     for (int ch = cb; ch < ce; ++ch) {
+        asm volatile("" ::"v"(seen));
+        seen = touch(min(ch + 1, ce - 1));
         const int noff = ch_i[8 * ch + 2], nn = ch_i[8 * ch + 3], eoff = ch_i[8 * ch + 4], ne = ch_i[8 * ch + 5],
                   foff = ch_i[8 * ch + 6], nf = ch_i[8 * ch + 7];
-        const double c[3] = {ch_c[3 * ch], ch_c[3 * ch + 1], ch_c[3 * ch + 2]};
-        __syncthreads();
-        for (int i = lane; i < nn * 3; i += NT) s_w[i / 3][i % 3] = nw[(int64_t)noff * 3 + i];
-        for (int i = lane; i < ne; i += NT) {
-            s_ea[i] = eab[2 * ((int64_t)eoff + i)];
-            s_eb[i] = eab[2 * ((int64_t)eoff + i) + 1];
-            s_il[i] = eil[eoff + i];
+        const double y[3] = {x[0] - ch_c[3 * ch], x[1] - ch_c[3 * ch + 1], x[2] - ch_c[3 * ch + 2]};
+        const ScalarMem<double> *w = scalar_mem(nw + 4 * (int64_t)noff);
+#pragma unroll 2
+        for (int j = 0; j < nn; ++j) {
+            const double d0 = w[4 * j] - y[0], d1 = w[4 * j + 1] - y[1], d2 = w[4 * j + 2] - y[2];
+            R[64 * j] = sqrt_nr((d0 * d0 + d1 * d1) + d2 * d2);
         }
-        for (int i = lane; i < ne * 11; i += NT) (&s_B[0][0])[i] = Bc[(int64_t)eoff * 11 + i];
-        for (int i = lane; i < nf; i += NT) {
-            s_fp[i] = fpqr[3 * ((int64_t)foff + i)];
-            s_fq[i] = fpqr[3 * ((int64_t)foff + i) + 1];
-            s_fr[i] = fpqr[3 * ((int64_t)foff + i) + 2];
-        }
-        for (int i = lane; i < nf * 3; i += NT) (&s_fn[0][0])[i] = fn[(int64_t)foff * 3 + i];
-        for (int i = lane; i < nf; i += NT) s_fa[i] = fa2[foff + i];
-        for (int i = lane; i < nf * 4; i += NT) (&s_A[0][0])[i] = A[(int64_t)foff * 4 + i];
-        __syncthreads();
-        for (int i = ib + lane; i < ie; i += NT) {
-            const int s = idx[i];
-            const double y[3] = {tgt_xyz[s] - c[0], tgt_xyz[N + s] - c[1], tgt_xyz[2 * N + s] - c[2]};
-            const double m[10] = {1.0,         y[0],        y[1],        y[2],        y[0] * y[0],
-                                  y[0] * y[1], y[0] * y[2], y[1] * y[1], y[1] * y[2], y[2] * y[2]};
-#pragma unroll 1
-            for (int j = 0; j < nn; ++j) {
-                const double d0 = s_w[j][0] - y[0], d1 = s_w[j][1] - y[1], d2 = s_w[j][2] - y[2];
-                s_R[j][lane] = sqrt((d0 * d0 + d1 * d1) + d2 * d2);
-            }
-            double acc = 0.0;
-#pragma unroll 1
-            for (int e = 0; e < ne; ++e) {
-                const int a = s_ea[e], bb = s_eb[e];
-                const double il = s_il[e];
-                const double da[3] = {s_w[a][0] - y[0], s_w[a][1] - y[1], s_w[a][2] - y[2]};
-                const double db[3] = {s_w[bb][0] - y[0], s_w[bb][1] - y[1], s_w[bb][2] - y[2]};
-                const double Ra = s_R[a][lane], Rb = s_R[bb][lane];
-                const double Dab = da[0] * db[0] + da[1] * db[1] + da[2] * db[2];
-                const double la = fma(-Ra, Ra, Dab) * il;  // (v_a - x) . e_hat
-                const double lb = fma(Rb, Rb, -Dab) * il;  // (v_b - x) . e_hat
-                const double cx0 = da[1] * db[2] - da[2] * db[1], cx1 = da[2] * db[0] - da[0] * db[2],
-                             cx2 = da[0] * db[1] - da[1] * db[0];
-                const double r0sq = (cx0 * cx0 + cx1 * cx1 + cx2 * cx2) * (il * il);
-                const double f = edge_log<false>(Ra, Rb, la, lb, r0sq);
-                const double g = r0sq * f + lb * Rb - la * Ra;
-                const double *Be = s_B[e];
-                double bq = Be[0];
+        const double m[9] = {y[0],        y[1],        y[2],        y[0] * y[0], y[0] * y[1],
+                             y[0] * y[2], y[1] * y[1], y[1] * y[2], y[2] * y[2]};
+        // Entities are taken in pairs, which share one reciprocal.  Software
+        // pipeline: at the top of a pair its field weights, the next pair's
+        // geometry and (record e names the corners of e + 2) its corner
+        // distances are asked for, and waited for once, before the weights
+        // are used.  Two register sets, alternating without copies.
+        if (ne > 0) {
+            const AtanhFar atanh_far;
+            const ScalarMem<TopoEdge> *E0 = scalar_mem(edge + eoff);
+            const ScalarMem<TopoEdgeW> *W0 = scalar_mem(edge_w + eoff);
+            uint64_t near = 0;  // edges with a target of this wavefront too close, taken after the others
+            struct Ops {
+                uint32_t next;
+                double L, il, l2, Ra, Rb;
+            };
+            auto load = [&](Ops (&o)[2], int e, uint32_t c0, uint32_t c1) {
 #pragma unroll
-                for (int q = 1; q < 10; ++q) bq = fma(Be[q], m[q], bq);
-                acc = fma(f * il, bq, fma(Be[10], g, acc));
-            }
+                for (int k = 0; k < 2; ++k) {
+                    const ScalarMem<TopoEdge> &E = E0[e + k];
+                    o[k].next = E.next;
+                    o[k].L = E.L;
+                    o[k].il = E.il;
+                    o[k].l2 = E.l2;
+                    o[k].Ra = R[64 * ((k ? c1 : c0) & 255)];
+                    o[k].Rb = R[64 * ((k ? c1 : c0) >> 8)];
+                }
+            };
+            auto step = [&](const Ops (&o)[2], Ops (&next)[2], int e) {
+                double Bq[2][11];
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int q = 0; q < 11; ++q) Bq[k][q] = W0[e + k].B[q];
+                load(next, e + 2 < ne ? e + 2 : e, o[0].next, o[1].next);
+                const double S[2] = {o[0].Ra + o[0].Rb, o[1].Ra + o[1].Rb};
+                const double ri = rcp_nr(S[0] * S[1]);
+                double sv[2] = {o[0].L * (ri * S[1]), o[1].L * (ri * S[0])};
+                double lin[2] = {sv[0], sv[1]};
+                if (__any(fmax(sv[0], sv[1]) > kEdgeFar)) {
+                    // At a corner of the edge f does not count (its weight is
+                    // zero to rounding) and any finite value serves; a target
+                    // past kEdgeMid puts the pair off; between the two
+                    // atanh(s) = atanh(c) + atanh((s - c)/(1 - c s)).
+                    double c[2], den[2];
+                    bool put_off = false;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const bool close = sv[k] > kEdgeFar && fmin(o[k].Ra, o[k].Rb) > 0.0;
+                        put_off = put_off || (close && sv[k] > kEdgeMid);
+                        c[k] = close ? kEdgeShift : 0.0;
+                        den[k] = fma(-c[k], o[k].L, S[k]);
+                    }
+                    if (__any(put_off)) {
+                        near |= 3ull << e;
+                        return;
+                    }
+                    const double r2 = rcp_nr(den[0] * den[1]);
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        sv[k] = fma(-c[k], S[k], o[k].L) * (r2 * den[1 - k]);
+                        lin[k] = fma(c[k], kEdgeShiftAtanh / kEdgeShift, sv[k]);
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const double t = (o[k].Rb - o[k].Ra) * o[k].il, t2 = t * t, SL = S[k] * o[k].L;
+                    const double F = atanh_far(sv[k], lin[k]);  // f / 2 and 2 g
+                    const double g = fma(fma(S[k], S[k], -o[k].l2) * (1.0 - t2), F, fma(t2, SL, SL));
+                    double bq = Bq[k][1] * m[0];
+#pragma unroll
+                    for (int q = 1; q < 9; ++q) bq = fma(Bq[k][q + 1], m[q], bq);
+                    bq += Bq[k][0];
+                    acc = fma(F, bq, fma(Bq[k][10], g, acc));
+                }
+            };
+            Ops oa[2], ob[2];
+            load(oa, 0, E0[0].own, E0[1].own);
 #pragma unroll 1
-            for (int fi = 0; fi < nf; ++fi) {
-                const int pp = s_fp[fi], qq = s_fq[fi], rr = s_fr[fi];
-                const double dp[3] = {s_w[pp][0] - y[0], s_w[pp][1] - y[1], s_w[pp][2] - y[2]};
-                const double dq[3] = {s_w[qq][0] - y[0], s_w[qq][1] - y[1], s_w[qq][2] - y[2]};
-                const double dr[3] = {s_w[rr][0] - y[0], s_w[rr][1] - y[1], s_w[rr][2] - y[2]};
-                const double Rp = s_R[pp][lane], Rq = s_R[qq][lane], Rr = s_R[rr][lane];
-                const double Dpq = dp[0] * dq[0] + dp[1] * dq[1] + dp[2] * dq[2];
-                const double Dpr = dp[0] * dr[0] + dp[1] * dr[1] + dp[2] * dr[2];
-                const double Dqr = dq[0] * dr[0] + dq[1] * dr[1] + dq[2] * dr[2];
-                const double den = Rp * Rq * Rr + Dpq * Rr + Dpr * Rq + Dqr * Rp;
-                const double h = s_fn[fi][0] * dp[0] + s_fn[fi][1] * dp[1] + s_fn[fi][2] * dp[2];
-                // [d_p, d_q, d_r] = d_p . ((q - p) x (r - p)) = h |(q - p) x (r - p)|
-                const double det = h * s_fa[fi];
-                const double af = s_A[fi][0] + (s_A[fi][1] * y[0] + s_A[fi][2] * y[1] + s_A[fi][3] * y[2]);
-                acc = fma(-af * h, 2.0 * atan2_nr(det, den), acc);
+            for (int e = 0; e < ne; e += 4) {
+                step(oa, ob, e);
+                if (e + 2 >= ne) break;
+                step(ob, oa, e + 2);
             }
-            atomicAdd(&u[tgt_perm[s]], acc * kInv4Pi);
+            while (near) {
+                const int e = __builtin_ctzll(near);
+                near &= near - 1;
+                const ScalarMem<TopoEdge> &E = E0[e];
+                const int a = E.own & 255, b = E.own >> 8;
+                const double Ra = R[64 * a], Rb = R[64 * b], S = Ra + Rb;
+                const double sv = E.L * rcp_nr(S);
+                const bool off = Ra > 0.0 && Rb > 0.0;  // at a corner f does not count
+                double F, g;
+                if (!__any(off && sv > kEdgeMid)) {
+                    const double t = (Rb - Ra) * E.il, t2 = t * t, SL = S * E.L;
+                    F = 0.5 * log_ratio<true>(S + E.L, S - E.L);
+                    F = off ? F : 0.0;
+                    g = fma(fma(S, S, -E.l2) * (1.0 - t2), F, fma(t2, SL, SL));
+                } else {
+                    const ScalarMem<double> *wa = w + 4 * a, *wb = w + 4 * b;
+                    const double da[3] = {wa[0] - y[0], wa[1] - y[1], wa[2] - y[2]};
+                    const double db[3] = {wb[0] - y[0], wb[1] - y[1], wb[2] - y[2]};
+                    const double Dab = da[0] * db[0] + da[1] * db[1] + da[2] * db[2];
+                    const double la = fma(-Ra, Ra, Dab) * E.il;  // (v_a - x) . e_hat
+                    const double lb = fma(Rb, Rb, -Dab) * E.il;  // (v_b - x) . e_hat
+                    const double cx0 = da[1] * db[2] - da[2] * db[1], cx1 = da[2] * db[0] - da[0] * db[2],
+                                 cx2 = da[0] * db[1] - da[1] * db[0];
+                    const double r0sq = (cx0 * cx0 + cx1 * cx1 + cx2 * cx2) * (E.il * E.il);
+                    const double f = edge_log<false, true>(Ra, Rb, la, lb, r0sq);
+                    F = 0.5 * f;
+                    g = 2.0 * (r0sq * f + lb * Rb - la * Ra);
+                }
+                const ScalarMem<TopoEdgeW> &W = W0[e];
+                double bq = W.B[1] * m[0];
+#pragma unroll
+                for (int q = 1; q < 9; ++q) bq = fma(W.B[q + 1], m[q], bq);
+                bq += W.B[0];
+                acc = fma(F, bq, fma(W.B[10], g, acc));
+            }
+        }
+        if (nf > 0) {
+            const AtanFar atan_far;
+            const ScalarMem<TopoFace> *F0 = scalar_mem(face + foff);
+            const ScalarMem<TopoFaceW> *W0 = scalar_mem(face_w + foff);
+            uint64_t near = 0;
+            struct Ops {
+                uint32_t next;
+                double l2pq, l2pr, l2qr, Rp, Rq, Rr;
+            };
+            auto load = [&](Ops (&o)[2], int f, uint32_t c0, uint32_t c1) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const ScalarMem<TopoFace> &K = F0[f + k];
+                    const uint32_t c = k ? c1 : c0;
+                    o[k].next = K.next;
+                    o[k].l2pq = K.l2pq;
+                    o[k].l2pr = K.l2pr;
+                    o[k].l2qr = K.l2qr;
+                    o[k].Rp = R[64 * (c & 255)];
+                    o[k].Rq = R[64 * (c >> 8 & 255)];
+                    o[k].Rr = R[64 * (c >> 16)];
+                }
+            };
+            auto step = [&](const Ops (&o)[2], Ops (&next)[2], int f) {
+                double n[2][3], h0[2], a4[2], A[2][4];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const ScalarMem<TopoFace> &K = F0[f + k];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) n[k][q] = K.n[q];
+                    h0[k] = K.h0;
+                    a4[k] = K.a4;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) A[k][q] = W0[f + k].A[q];
+                }
+                load(next, f + 2 < nf ? f + 2 : f, o[0].next, o[1].next);
+                double P[2], den[2], h[2], num[2], tn[2];  // den: twice the denominator; h: height; tn: tan(Omega/2)
+                bool bad = false;
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    P[k] = (o[k].Rp + o[k].Rq) * (o[k].Rq + o[k].Rr) * (o[k].Rr + o[k].Rp);
+                    den[k] = P[k] - fma(o[k].l2pq, o[k].Rr, fma(o[k].l2pr, o[k].Rq, o[k].l2qr * o[k].Rp));
+                    bad = bad || !(den[k] >= kFaceCond * P[k]);
+                }
+                const double ri = rcp_nr(den[0] * den[1]);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    h[k] = h0[k] - (n[k][0] * y[0] + n[k][1] * y[1] + n[k][2] * y[2]);
+                    num[k] = h[k] * a4[k];
+                    tn[k] = num[k] * (ri * den[1 - k]);
+                }
+                bad = bad || !(fmax(fabs(tn[0]), fabs(tn[1])) <= kFaceTan);
+                double lin[2] = {tn[0], tn[1]};
+                if (__any(bad)) {
+                    // At a corner of the face h is zero (to rounding) and any
+                    // denominator serves; a denominator small against P puts
+                    // the pair off, as does t > 1 / kFaceTan; between the two
+                    // atan(t) = pi/4 + atan((t - 1)/(t + 1)).
+                    double top[2], dn[2], off[2];
+                    bool put_off = false;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const bool corner = !(fmin(fmin(o[k].Rp, o[k].Rq), o[k].Rr) > 0.0);
+                        const double d = corner ? 1.0 : den[k], an = fabs(num[k]);
+                        const bool wide = an > kFaceTan * d;
+                        put_off = put_off || (!corner && (!(d >= kFaceCond * P[k]) || kFaceTan * an > d));
+                        top[k] = copysign(wide ? an - d : an, num[k]);
+                        top[k] = wide && an < d ? -top[k] : top[k];
+                        dn[k] = wide ? an + d : d;
+                        off[k] = wide ? copysign(0.78539816339744827900, num[k]) : 0.0;
+                    }
+                    if (__any(put_off)) {
+                        near |= 3ull << f;
+                        return;
+                    }
+                    const double r2 = rcp_nr(dn[0] * dn[1]);
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        tn[k] = top[k] * (r2 * dn[1 - k]);
+                        lin[k] = tn[k] + off[k];
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const double af = A[k][0] + (A[k][1] * y[0] + A[k][2] * y[1] + A[k][3] * y[2]);
+                    acc = fma(af * h[k], atan_far(tn[k], lin[k]), acc);
+                }
+            };
+            Ops oa[2], ob[2];
+            load(oa, 0, F0[0].own, F0[1].own);
+#pragma unroll 1
+            for (int f = 0; f < nf; f += 4) {
+                step(oa, ob, f);
+                if (f + 2 >= nf) break;
+                step(ob, oa, f + 2);
+            }
+            while (near) {
+                const int f = __builtin_ctzll(near);
+                near &= near - 1;
+                const ScalarMem<TopoFace> &K = F0[f];
+                const int p = K.own & 255, q = K.own >> 8 & 255, r = K.own >> 16;
+                const double Rp = R[64 * p], Rq = R[64 * q], Rr = R[64 * r];
+                const double P = (Rp + Rq) * (Rq + Rr) * (Rr + Rp);
+                const double den = P - fma(K.l2pq, Rr, fma(K.l2pr, Rq, K.l2qr * Rp));
+                const double h = K.h0 - (K.n[0] * y[0] + K.n[1] * y[1] + K.n[2] * y[2]);
+                const bool off = Rp > 0.0 && Rq > 0.0 && Rr > 0.0;  // at a corner h = 0
+                double num = h * K.a4, dn = off ? den : 1.0;
+                if (__any(off && !(den >= kFaceCond * P))) {
+                    const ScalarMem<double> *wp = w + 4 * p, *wq = w + 4 * q, *wr = w + 4 * r;
+                    const double dp[3] = {wp[0] - y[0], wp[1] - y[1], wp[2] - y[2]};
+                    const double dq[3] = {wq[0] - y[0], wq[1] - y[1], wq[2] - y[2]};
+                    const double dr[3] = {wr[0] - y[0], wr[1] - y[1], wr[2] - y[2]};
+                    const double Dpq = dp[0] * dq[0] + dp[1] * dq[1] + dp[2] * dq[2];
+                    const double Dpr = dp[0] * dr[0] + dp[1] * dr[1] + dp[2] * dr[2];
+                    const double Dqr = dq[0] * dr[0] + dq[1] * dr[1] + dq[2] * dr[2];
+                    // [d_p, d_q, d_r] = d_p . ((q - p) x (r - p)) = h |(q - p) x (r - p)|
+                    num *= 0.5;
+                    dn = Rp * Rq * Rr + Dpq * Rr + Dpr * Rq + Dqr * Rp;
+                }
+                const ScalarMem<TopoFaceW> &W = W0[f];
+                const double af = W.A[0] + (W.A[1] * y[0] + W.A[2] * y[1] + W.A[3] * y[2]);
+                acc = fma(af * h, atan2_nr<true>(num, dn), acc);
+            }
         }
     }
+    asm volatile("" ::"v"(seen));
+    if (ib + lane < ie) atomicAdd(&u[tgt_perm[s]], acc * kInv4Pi);
 }
 
 // ---------------------------------------------------------------------------
@@ -2397,18 +2674,13 @@ void run_p2p(DevicePlan &dp, bool direct, const double *M, int32_t F, double *u,
     if (!band_skip && F == 1 && dp.p2p_topo && dp.n_topo_ch > 0) {
         const HostPlan &hp = dp.hp;
         k_topo_coef<<<dim3((unsigned)((dp.n_topo_ch + kTopoChunksPerWave - 1) / kTopoChunksPerWave)), dim3(64), 0, st>>>(dp.topo_ch_i, dp.topo_ch_c, dp.n_topo_ch, dp.topo_inc,
-                                                             dp.tet_xyz, dp.tet_node, hp.n_tets, M, dp.topo_A,
-                                                             dp.topo_B);
+                                                             dp.tet_xyz, dp.tet_node, hp.n_tets, M,
+                                                             dp.topo_edge, dp.topo_edge_w, dp.topo_face_w);
         hip_check(hipGetLastError(), "k_topo_coef launch");
-        const int nblk = dp.n_p2p_blk;
-        if (dp.p2p_wide)
-            k_p2p_topo<256><<<dim3(xcd_grid(nblk)), dim3(256), 0, st>>>(
-                dp.topo_blk, nblk, dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_ab, dp.topo_il, dp.topo_pqr,
-                dp.topo_n, dp.topo_a2, dp.topo_A, dp.topo_B, dp.p2p_idx, dp.tgt_xyz, dp.tgt_perm, hp.n_targets, u);
-        else
-            k_p2p_topo<64><<<dim3(xcd_grid(nblk)), dim3(64), 0, st>>>(
-                dp.topo_blk, nblk, dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_ab, dp.topo_il, dp.topo_pqr,
-                dp.topo_n, dp.topo_a2, dp.topo_A, dp.topo_B, dp.p2p_idx, dp.tgt_xyz, dp.tgt_perm, hp.n_targets, u);
+        if (dp.n_topo_items == 0) return;
+        k_p2p_topo<<<dim3(xcd_grid(dp.n_topo_items)), dim3(64), 0, st>>>(
+            dp.topo_item, dp.n_topo_items, dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_edge, dp.topo_face,
+            dp.topo_edge_w, dp.topo_face_w, dp.p2p_idx, dp.tgt_xyz, dp.tgt_perm, hp.n_targets, u);
         hip_check(hipGetLastError(), "k_p2p_topo launch");
         return;
     }
@@ -2777,6 +3049,15 @@ void build_tet_moments(DevicePlan &dp)
     hip_check(hipDeviceSynchronize(), "k_tet_moments");
 }
 
+void build_topo_records(DevicePlan &dp, const int32_t *ab, const int32_t *pqr)
+{
+    if (dp.n_topo_ch == 0) return;
+    k_topo_static<<<dim3((unsigned)dp.n_topo_ch), dim3(64)>>>(dp.topo_ch_i, dp.n_topo_ch, dp.topo_w, ab, pqr,
+                                                              dp.topo_edge, dp.topo_face);
+    hip_check(hipGetLastError(), "k_topo_static launch");
+    hip_check(hipDeviceSynchronize(), "k_topo_static");
+}
+
 void build_m2l_table(DevicePlan &dp)
 {
     if (dp.n_m2l_keys == 0) return;
@@ -3084,13 +3365,16 @@ void autotune(DevicePlan &dp, hipStream_t st)
             free_tiles(dp, dp.m2l_tiles[0]);
         else
             free_m2l_packs(dp);
-        bool best_wide = false;
-        for (bool wide : {false, true}) {
-            dp.p2p_wide = wide;
-            const float t = time_config(dp, M, u, st);
-            if (!wide || t < best) best = t, best_wide = wide;
+        // the per-tet near field's workgroup shape, where one field runs it
+        if (dp.sur_mode != TFMM_SUR_OFF && !dp.near_stored && !hp.points) {
+            bool best_wide = false;
+            for (bool wide : {false, true}) {
+                dp.p2p_wide = wide;
+                const float t = time_config(dp, M, u, st);
+                if (!wide || t < best) best = t, best_wide = wide;
+            }
+            dp.p2p_wide = best_wide;
         }
-        dp.p2p_wide = best_wide;
         ++dp.schedule_gen;
         prepare_evaluate(dp, 1);
         hip_check(hipStreamSynchronize(st), "hipStreamSynchronize");

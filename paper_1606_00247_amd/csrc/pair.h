@@ -236,6 +236,100 @@ __device__ __forceinline__ double rsqrt_nr(double a)
     return fma(0.5 * r, e, r);
 }
 
+// A constant formed at this place in a scalar or vector register pair, opaque
+// to the compiler.  Left to itself it keeps the constants of polynomials in
+// vector registers around all loops and copies each before a two-address
+// multiply-add, twice the instructions.
+constexpr unsigned long long dbits(double c) { return __builtin_bit_cast(unsigned long long, c); }
+template <unsigned long long kBits>
+__device__ __forceinline__ double scalar_const()
+{
+    int lo, hi;
+    asm volatile("s_mov_b32 %0, %1" : "=s"(lo) : "n"((int)(kBits & 0xffffffffull)));
+    asm volatile("s_mov_b32 %0, %1" : "=s"(hi) : "n"((int)(kBits >> 32)));
+    return __hiloint2double(hi, lo);
+}
+template <unsigned long long kBits>
+__device__ __forceinline__ double vector_const()
+{
+    int lo, hi;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(lo) : "n"((int)(kBits & 0xffffffffull)));
+    asm volatile("v_mov_b32 %0, %1" : "=v"(hi) : "n"((int)(kBits >> 32)));
+    return __hiloint2double(hi, lo);
+}
+
+// a b + c with c in a scalar register pair.
+__device__ __forceinline__ double fma_sv(double a, double b, double c)
+{
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+    return d;
+}
+
+// c[0] z^(n-1) + ... + c[n-1] by three-address multiply-adds (see scalar_const).
+__device__ __forceinline__ double poly11(const double (&c)[11], double z)
+{
+    double q;
+    asm("v_fma_f64 %0, %2, %1, %3\n\t"
+        "v_fma_f64 %0, %0, %1, %4\n\t"
+        "v_fma_f64 %0, %0, %1, %5\n\t"
+        "v_fma_f64 %0, %0, %1, %6\n\t"
+        "v_fma_f64 %0, %0, %1, %7\n\t"
+        "v_fma_f64 %0, %0, %1, %8\n\t"
+        "v_fma_f64 %0, %0, %1, %9\n\t"
+        "v_fma_f64 %0, %0, %1, %10\n\t"
+        "v_fma_f64 %0, %0, %1, %11\n\t"
+        "v_fma_f64 %0, %0, %1, %12"
+        : "=&v"(q)
+        : "v"(z), "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]), "v"(c[4]), "v"(c[5]), "v"(c[6]), "v"(c[7]), "v"(c[8]),
+          "v"(c[9]), "v"(c[10]));
+    return q;
+}
+
+__device__ __forceinline__ double poly13(const double (&c)[13], double z)
+{
+    double q;
+    asm("v_fma_f64 %0, %2, %1, %3\n\t"
+        "v_fma_f64 %0, %0, %1, %4\n\t"
+        "v_fma_f64 %0, %0, %1, %5\n\t"
+        "v_fma_f64 %0, %0, %1, %6\n\t"
+        "v_fma_f64 %0, %0, %1, %7\n\t"
+        "v_fma_f64 %0, %0, %1, %8\n\t"
+        "v_fma_f64 %0, %0, %1, %9\n\t"
+        "v_fma_f64 %0, %0, %1, %10\n\t"
+        "v_fma_f64 %0, %0, %1, %11\n\t"
+        "v_fma_f64 %0, %0, %1, %12\n\t"
+        "v_fma_f64 %0, %0, %1, %13\n\t"
+        "v_fma_f64 %0, %0, %1, %14"
+        : "=&v"(q)
+        : "v"(z), "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]), "v"(c[4]), "v"(c[5]), "v"(c[6]), "v"(c[7]), "v"(c[8]),
+          "v"(c[9]), "v"(c[10]), "v"(c[11]), "v"(c[12]));
+    return q;
+}
+
+// 1/d for finite nonzero d of moderate range: the hardware estimate (relative
+// error e below 2^-22) and one cubic step r <- r + r (e + e^2), e = 1 - d r.
+__device__ __forceinline__ double rcp_nr(double d)
+{
+    const double r = __builtin_amdgcn_rcp(d);
+    const double e = fma(-d, r, 1.0);
+    return fma(r, fma(e, e, e), r);
+}
+
+// sqrt(a) for zero or positive finite normal a: the hardware estimate of
+// 1/sqrt(a), one coupled Newton step on g ~ sqrt(a), h ~ 1/(2 sqrt(a)), then
+// the residual correction g <- g + h (a - g^2).
+__device__ __forceinline__ double sqrt_nr(double a)
+{
+    const double y = __builtin_amdgcn_rsq(a);
+    double g = a * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, a), h, g);
+    return a > 0.0 ? g : 0.0;
+}
+
 // ln(num / den) for positive finite num, den, with one division: writing
 // num = a 2^i, den = b 2^j (a, b in [1/2, 1)), the ratio a/b is brought into
 // [1/sqrt2, sqrt2) by a factor 2 on a or b (the differences below are then
@@ -244,6 +338,18 @@ __device__ __forceinline__ double rsqrt_nr(double a)
 // s^21/21 / (1 - s^2) < 4.1e-18, 2.4e-17 relative to 2 atanh(s));
 // the power of two enters as (i - j) ln 2 with ln 2 split into a 32-bit-exact
 // head and a tail (Cody & Waite).
+// With kRare (a call in a branch that is seldom taken) the constants are formed
+// at the call instead of being kept in registers around it.
+template <bool kRare, unsigned long long kBits>
+__device__ __forceinline__ double poly_step(double q, double z)
+{
+    if constexpr (kRare)
+        return fma_sv(q, z, scalar_const<kBits>());
+    else
+        return fma(q, z, __builtin_bit_cast(double, kBits));
+}
+
+template <bool kRare = false>
 __device__ __forceinline__ double log_ratio(double num, double den)
 {
     int ei, ej;
@@ -256,15 +362,15 @@ __device__ __forceinline__ double log_ratio(double num, double den)
     const int e = ei - ej + (hi ? 1 : 0) - (lo ? 1 : 0);
     const double sv = div_nr(a - b, a + b);
     const double z = sv * sv;
-    double q = 1.0 / 19.0;
-    q = fma(q, z, 1.0 / 17.0);
-    q = fma(q, z, 1.0 / 15.0);
-    q = fma(q, z, 1.0 / 13.0);
-    q = fma(q, z, 1.0 / 11.0);
-    q = fma(q, z, 1.0 / 9.0);
-    q = fma(q, z, 1.0 / 7.0);
-    q = fma(q, z, 1.0 / 5.0);
-    q = fma(q, z, 1.0 / 3.0);
+    double q = kRare ? scalar_const<dbits(1.0 / 19.0)>() : 1.0 / 19.0;
+    q = poly_step<kRare, dbits(1.0 / 17.0)>(q, z);
+    q = poly_step<kRare, dbits(1.0 / 15.0)>(q, z);
+    q = poly_step<kRare, dbits(1.0 / 13.0)>(q, z);
+    q = poly_step<kRare, dbits(1.0 / 11.0)>(q, z);
+    q = poly_step<kRare, dbits(1.0 / 9.0)>(q, z);
+    q = poly_step<kRare, dbits(1.0 / 7.0)>(q, z);
+    q = poly_step<kRare, dbits(1.0 / 5.0)>(q, z);
+    q = poly_step<kRare, dbits(1.0 / 3.0)>(q, z);
     const double t = 2.0 * sv * z * q;  // 2 atanh(s) - 2 s
     const double kLn2Hi = 6.93147180369123816490e-01, kLn2Lo = 1.90821492927058770002e-10;
     const double de = (double)e;
@@ -285,7 +391,7 @@ __device__ __forceinline__ double log_ratio(double num, double den)
 // final select, which copies bits and never propagates it: four selects
 // fewer, which the shared-entity loop gains from, while the per-tet kernel
 // (measured at 16 fields) is faster with the mask.
-template <bool kMask = true>
+template <bool kMask = true, bool kRare = false>
 __device__ __forceinline__ double edge_log(double Ra, double Rb, double la, double lb, double r0sq)
 {
     const bool fwd = la >= 0.0, mid = !fwd && lb > 0.0;
@@ -293,7 +399,7 @@ __device__ __forceinline__ double edge_log(double Ra, double Rb, double la, doub
     const double num = mid ? p * q : p;
     const double den = mid ? r0sq : q;
     const bool ok = (Ra > 0.0) && (Rb > 0.0) && (den > 0.0) && (num > 0.0);
-    const double f = kMask ? log_ratio(ok ? num : 1.0, ok ? den : 1.0) : log_ratio(num, den);
+    const double f = kMask ? log_ratio<kRare>(ok ? num : 1.0, ok ? den : 1.0) : log_ratio<kRare>(num, den);
     const double fs = (fwd || mid) ? f : -f;
     return ok ? fs : 0.0;
 }
@@ -305,6 +411,7 @@ __device__ __forceinline__ double edge_log(double Ra, double Rb, double la, doub
 // polynomial interpolating (atan(sqrt z)/sqrt z - 1)/z at the Chebyshev
 // points of [0, tan(pi/8)^2] (relative error of atan(t) below 5e-18); the
 // octant and quadrant follow by pi/2 - r and pi - r, the sign from y.
+template <bool kRare = false>
 __device__ __forceinline__ double atan2_nr(double y, double x)
 {
     const double ay = fabs(y), ax = fabs(x);
@@ -315,17 +422,17 @@ __device__ __forceinline__ double atan2_nr(double y, double x)
     const double den = big ? b + a : (b > 0.0 ? b : 1.0);
     const double t = div_nr(num, den);
     const double z = t * t;
-    double q = -1.91768871190622589893e-2;
-    q = fma(q, z, 3.923165829558719130283e-2);
-    q = fma(q, z, -5.085449737940259861323e-2);
-    q = fma(q, z, 5.858148912802209881646e-2);
-    q = fma(q, z, -6.664511447381948000098e-2);
-    q = fma(q, z, 7.692183190826086563693e-2);
-    q = fma(q, z, -9.090904578123901890479e-2);
-    q = fma(q, z, 1.111111101525636172749e-1);
-    q = fma(q, z, -1.428571428466654292249e-1);
-    q = fma(q, z, 1.999999999999552067782e-1);
-    q = fma(q, z, -3.333333333333333015966e-1);
+    double q = kRare ? scalar_const<dbits(-1.91768871190622589893e-2)>() : -1.91768871190622589893e-2;
+    q = poly_step<kRare, dbits(3.923165829558719130283e-2)>(q, z);
+    q = poly_step<kRare, dbits(-5.085449737940259861323e-2)>(q, z);
+    q = poly_step<kRare, dbits(5.858148912802209881646e-2)>(q, z);
+    q = poly_step<kRare, dbits(-6.664511447381948000098e-2)>(q, z);
+    q = poly_step<kRare, dbits(7.692183190826086563693e-2)>(q, z);
+    q = poly_step<kRare, dbits(-9.090904578123901890479e-2)>(q, z);
+    q = poly_step<kRare, dbits(1.111111101525636172749e-1)>(q, z);
+    q = poly_step<kRare, dbits(-1.428571428466654292249e-1)>(q, z);
+    q = poly_step<kRare, dbits(1.999999999999552067782e-1)>(q, z);
+    q = poly_step<kRare, dbits(-3.333333333333333015966e-1)>(q, z);
     const double at = fma(t * z, q, t);
     const double kPi = 3.141592653589793116, kPi2 = 1.5707963267948965580, kPi4 = 0.78539816339744827900;
     double r = big ? kPi4 - at : at;
@@ -333,6 +440,80 @@ __device__ __forceinline__ double atan2_nr(double y, double x)
     r = x < 0.0 ? kPi - r : r;
     return copysign(r, y);
 }
+
+// ---------------------------------------------------------------------------
+// Edge and face terms from corner distances alone.  With S = R_a + R_b,
+// D = R_b - R_a and L the edge's length,
+//   f    = ln((S + L)/(S - L)) = 2 atanh(s),  s = L/S,
+//   R0^2 = (S^2 - L^2)(L^2 - D^2) / (4 L^2)            (Heron),
+//   l_b R_b - l_a R_a = S (L + D^2/L) / 2,
+// so g = R0^2 f + l_b R_b - l_a R_a = ((S^2 - L^2)(1 - t^2) f/2 + S L (1 + t^2)) / 2
+// with t = D/L; and for a face with corner distances R_p, R_q, R_r
+//   2 (R_p R_q R_r + sum D_ij R_k) = P - (L_pq^2 R_r + L_pr^2 R_q + L_qr^2 R_p),
+//   P = (R_p + R_q)(R_q + R_r)(R_r + R_p),
+// so tan(Omega/2) needs no difference vectors but the height.  Both are well
+// conditioned away from the edge or face (s bounded away from 1, the face's
+// denominator not small against P); closer targets take the forms below.
+// ---------------------------------------------------------------------------
+constexpr double kEdgeFar = 0.5;   // atanh_far's range of s
+constexpr double kEdgeShift = 0.75, kEdgeShiftAtanh = 0.97295507452765665255;  // c, atanh(c)
+constexpr double kEdgeMid = 0.9;   // S - L keeps all but about 4 bits of S
+constexpr double kFaceTan = 0.414213562373095;  // tan(pi/8): atan_far's range
+constexpr double kFaceCond = 0.0625;  // least denominator over P
+
+// atanh(s) for |s| <= kEdgeFar: s + s^3 Q(s^2), Q of degree 12 interpolating
+// (atanh(sqrt z)/sqrt z - 1)/z at the Chebyshev points of [0, 1/4] (relative
+// error below 3e-17).
+struct AtanhFar {
+    double c[13];
+    __device__ __forceinline__ AtanhFar()
+        : c{vector_const<dbits(1.97454264785334926424e-01)>(),
+            vector_const<dbits(-1.09516507426128548164e-01)>(),
+            vector_const<dbits(1.14547545108890203025e-01)>(),
+            vector_const<dbits(2.69135450515010227202e-02)>(),
+            vector_const<dbits(5.65994173773324837917e-02)>(),
+            vector_const<dbits(5.83095311569123558870e-02)>(),
+            vector_const<dbits(6.67117797972938270101e-02)>(),
+            vector_const<dbits(7.69204426675997310348e-02)>(),
+            vector_const<dbits(9.09091891139124363974e-02)>(),
+            vector_const<dbits(1.11111108941550865148e-01)>(),
+            vector_const<dbits(1.42857142881957860370e-01)>(),
+            vector_const<dbits(1.99999999999888822266e-01)>(),
+            vector_const<dbits(3.33333333333333425852e-01)>()}
+    {
+    }
+    // atanh(s) - s + lin
+    __device__ __forceinline__ double operator()(double s, double lin) const
+    {
+        const double z = s * s;
+        return fma(s * z, poly13(c, z), lin);
+    }
+};
+
+// atan(t) for |t| <= tan(pi/8) (the polynomial of atan2_nr).
+struct AtanFar {
+    double c[11];
+    __device__ __forceinline__ AtanFar()
+        : c{vector_const<dbits(-1.91768871190622589893e-2)>(),
+            vector_const<dbits(3.923165829558719130283e-2)>(),
+            vector_const<dbits(-5.085449737940259861323e-2)>(),
+            vector_const<dbits(5.858148912802209881646e-2)>(),
+            vector_const<dbits(-6.664511447381948000098e-2)>(),
+            vector_const<dbits(7.692183190826086563693e-2)>(),
+            vector_const<dbits(-9.090904578123901890479e-2)>(),
+            vector_const<dbits(1.111111101525636172749e-1)>(),
+            vector_const<dbits(-1.428571428466654292249e-1)>(),
+            vector_const<dbits(1.999999999999552067782e-1)>(),
+            vector_const<dbits(-3.333333333333333015966e-1)>()}
+    {
+    }
+    // atan(t) - t + lin
+    __device__ __forceinline__ double operator()(double t, double lin) const
+    {
+        const double z = t * t;
+        return fma(t * z, poly11(c, z), lin);
+    }
+};
 
 // Geometric integrals of one pair (target x, tet G): the face integrals I0_k,
 // the edge terms g_e, the signed heights h_k and d_0 = v_0 - x; the potential

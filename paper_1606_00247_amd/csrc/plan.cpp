@@ -788,46 +788,36 @@ void build_near_topology(const HostPlan &hp, const std::vector<int32_t> &blk, Ne
                 }
             }
             // chunk record
-            const int32_t noff = (int32_t)(out.nd_w.size() / 3), eoff = (int32_t)out.ed_il.size(),
-                          foff = (int32_t)(out.fc_n.size() / 3);
+            const int32_t noff = (int32_t)(out.nd_w.size() / 4), eoff = (int32_t)(out.ed_ab.size() / 2),
+                          foff = (int32_t)(out.fc_pqr.size() / 3);
             double c[3] = {0.0, 0.0, 0.0};
             for (int32_t id : nodes)
                 for (int k = 0; k < 3; ++k) c[k] += hp.nodes[3 * (size_t)id + k];
             for (int k = 0; k < 3; ++k) c[k] /= (double)nodes.size();
             auto local = [&](int32_t id) { return find(nodes, &id, 1); };
             auto pos = [&](int32_t id, int k) { return hp.nodes[3 * (size_t)id + k] - c[k]; };
-            for (int32_t id : nodes)
+            for (int32_t id : nodes) {
                 for (int k = 0; k < 3; ++k) out.nd_w.push_back(pos(id, k));
+                out.nd_w.push_back(0.0);
+            }
             for (size_t e = 0; e < edges.size() / 2; ++e) {
-                const int32_t a = edges[2 * e], bb = edges[2 * e + 1];
-                out.ed_ab.push_back(local(a));
-                out.ed_ab.push_back(local(bb));
-                double d2 = 0.0;
-                for (int k = 0; k < 3; ++k) {
-                    const double dk = pos(bb, k) - pos(a, k);
-                    d2 += dk * dk;
-                }
-                out.ed_il.push_back(1.0 / std::sqrt(d2));
+                out.ed_ab.push_back(local(edges[2 * e]));
+                out.ed_ab.push_back(local(edges[2 * e + 1]));
             }
             for (size_t f = 0; f < faces.size() / 3; ++f) {
-                const int32_t pp = faces[3 * f], qq = faces[3 * f + 1], rr = faces[3 * f + 2];
-                out.fc_pqr.push_back(local(pp));
-                out.fc_pqr.push_back(local(qq));
-                out.fc_pqr.push_back(local(rr));
-                double u[3], w[3];
-                for (int k = 0; k < 3; ++k) {
-                    u[k] = pos(qq, k) - pos(pp, k);
-                    w[k] = pos(rr, k) - pos(pp, k);
-                }
-                const double n[3] = {u[1] * w[2] - u[2] * w[1], u[2] * w[0] - u[0] * w[2], u[0] * w[1] - u[1] * w[0]};
-                const double il = 1.0 / std::sqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
-                for (int k = 0; k < 3; ++k) out.fc_n.push_back(n[k] * il);
-                out.fc_a2.push_back(1.0 / il);
+                for (int k = 0; k < 3; ++k) out.fc_pqr.push_back(local(faces[3 * f + k]));
             }
-            const int32_t rec[8] = {s, t - s, noff, (int32_t)nodes.size(), eoff, (int32_t)(edges.size() / 2), foff,
-                                    (int32_t)(faces.size() / 3)};
+            if (edges.size() / 2 % 2)
+                for (int k = 0; k < 2; ++k) out.ed_ab.push_back(out.ed_ab[out.ed_ab.size() - 2]);
+            if (faces.size() / 3 % 2)
+                for (int k = 0; k < 3; ++k) out.fc_pqr.push_back(out.fc_pqr[out.fc_pqr.size() - 3]);
+            const int32_t rec[8] = {s,    t - s, noff, (int32_t)nodes.size(),
+                                    eoff, (int32_t)(out.ed_ab.size() / 2) - eoff,
+                                    foff, (int32_t)(out.fc_pqr.size() / 3) - foff};
             out.ch_i.insert(out.ch_i.end(), rec, rec + 8);
             out.ch_c.insert(out.ch_c.end(), c, c + 3);
+            out.pad.push_back((uint8_t)(edges.size() / 2 % 2));
+            out.pad.push_back((uint8_t)(faces.size() / 3 % 2));
             s = t;
         }
         out.blk.push_back((int32_t)(out.ch_i.size() / 8));

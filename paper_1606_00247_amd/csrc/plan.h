@@ -101,22 +101,22 @@ void build_m2l_packs(const HostPlan &hp, int nb, int tpg, int max_grp, M2LPacks 
 // of one leaf, [tbeg, tend) in octree order) is cut into chunks of at most
 // kTopoTets tets with at most kTopoNodes distinct nodes, kTopoEdges edges and
 // kTopoFaces faces; per chunk the distinct nodes (positions relative to the
-// chunk's node centroid), edges (canonical direction: lower node id first,
-// inverse length) and faces (nodes in increasing id order, unit normal of
-// that order), and per tet the chunk-local indices of its 6 edges (corner
-// pairs (0,1),(0,2),(0,3),(1,2),(1,3),(2,3)) and 4 faces (face k opposite
-// corner k).
+// chunk's node centroid), edges (canonical direction: lower node id first)
+// and faces (nodes in increasing id order), and per tet the chunk-local
+// indices of its 6 edges (corner pairs (0,1),(0,2),(0,3),(1,2),(1,3),(2,3))
+// and 4 faces (face k opposite corner k).  Edges and faces come in pairs, the
+// last listed twice where their number is odd.  The entities' geometry is
+// formed from these on the device.
+// (even numbers of edges and faces: see the pairs above)
 constexpr int kTopoTets = 16, kTopoNodes = 16, kTopoEdges = 48, kTopoFaces = 40;
 struct NearTopo {
     std::vector<int32_t> blk;     // [nblk][4]: chunk begin, chunk end, target begin, target end
     std::vector<int32_t> ch_i;    // [nch][8]: tbeg, ntets, node off, nodes, edge off, edges, face off, faces
     std::vector<double> ch_c;     // [nch][3] node centroid
-    std::vector<double> nd_w;     // [nodes][3] position - centroid
+    std::vector<double> nd_w;     // [nodes][4] position - centroid, padded
     std::vector<int32_t> ed_ab;   // [edges][2] chunk-local nodes
-    std::vector<double> ed_il;    // [edges] 1 / length
     std::vector<int32_t> fc_pqr;  // [faces][3] chunk-local nodes
-    std::vector<double> fc_n;     // [faces][3] unit normal of (q - p) x (r - p)
-    std::vector<double> fc_a2;    // [faces] |(q - p) x (r - p)| (twice the area)
+    std::vector<uint8_t> pad;     // [nch][2] edges and faces listed twice
     std::vector<int32_t> inc;     // [T][10] per tet: 6 edge, 4 face chunk-local indices
 };
 
