@@ -113,9 +113,10 @@ T *dev_upload(const std::vector<T> &h, int64_t &bytes)
 namespace tfmm {
 
 // A device list needed only while the plan is uploaded.
+template <typename E>
 struct ScratchList {
-    int32_t *d;
-    explicit ScratchList(int32_t *p) : d(p) {}
+    E *d;
+    explicit ScratchList(E *p) : d(p) {}
     ScratchList(const ScratchList &) = delete;
     ScratchList &operator=(const ScratchList &) = delete;
     ~ScratchList() { (void)hipFree(d); }
@@ -312,6 +313,16 @@ void upload_plan(DevicePlan &dp)
             int64_t tmp = 0;
             ScratchList ab{dev_upload(tp.ed_ab, tmp)}, pqr{dev_upload(tp.fc_pqr, tmp)};
             build_topo_records(dp, ab.d, pqr.d);
+            std::vector<int64_t> row((size_t)T);
+            for (int64_t t = 0; t < T; ++t) {
+                row[t] = dp.near_rows;
+                dp.near_rows += 1 + 3 * __builtin_popcount(tp.skin[t]);
+            }
+            room(dp.near_tet, (size_t)T);
+            ScratchList corner{dev_upload(tp.corner, tmp)};
+            ScratchList skin{dev_upload(tp.skin, tmp)};
+            ScratchList rows{dev_upload(row, tmp)};
+            build_near_tets(dp, corner.d, skin.d, rows.d);
         }
     }
     {
@@ -355,7 +366,7 @@ void free_plan(DevicePlan &dp)
     void *ptrs[] = {dp.tet_xyz, dp.tet_node, dp.tet_perm, dp.tgt_xyz, dp.tgt_perm, dp.tgt_leaf, dp.cell_c, dp.cell_i,
                     dp.p2m_cells, dp.m2m_cells, dp.l2l_cells, dp.p2p_blk, dp.p2p_idx, dp.quad, dp.far_rule, dp.node_lump, dp.tet_mom, dp.Q,
                     dp.L, dp.Qt, dp.Qtf, dp.m2l_keys, dp.m2l_D, dp.m2l_Df, dp.sur_w, dp.sur_wb, dp.band_pairs, dp.band_rule, dp.topo_item,
-                    dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_inc, dp.topo_edge, dp.topo_face, dp.topo_edge_w, dp.topo_face_w,
+                    dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_inc, dp.topo_edge, dp.topo_face, dp.topo_edge_w, dp.topo_face_w, dp.near_tet, dp.near_w,
                     dp.near_off, dp.near_nc, dp.near_cols, dp.near_val, dp.near_items};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);

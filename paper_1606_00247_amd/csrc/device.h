@@ -65,6 +65,23 @@ struct TopoFaceW {
     double A[4];  // -2 times the affine weight (1, y0, y1, y2)
 };
 
+// Geometry of a tet for the near field of several fields (see k_p2p_fields),
+// relative to its chunk's centroid; once per plan (k_tet_static).
+struct NearTet {
+    uint32_t corner;   // chunk-local node indices, a byte each
+    uint32_t skin;     // faces on the chunk's boundary (bit k: opposite corner k)
+    int64_t row;       // first row of field weights: the tet's, then three per skin face
+    double c[3];       // centroid
+    double lam[3][3];  // gradients of barycentric coordinates 1..3
+    double v12;        // 12 |V|
+    double l2[6];      // squared edge lengths
+    double kap[4];     // 6|V| / (2 A_k)^2
+    double G[6];       // 6|V| grad lambda_i . grad lambda_k, by the edge (i, k)
+    double il2[6];     // 1 / l2
+    double C[4][2][3]; // -(E_i . E_e) / (8 (2 A_k)^2): face k, its corners 1 and 2, its edges (opposite corner 0, 1, 2)
+    double L[6];       // edge lengths
+};
+
 struct DevicePlan {
     HostPlan hp;
     int device = -1;
@@ -156,6 +173,11 @@ struct DevicePlan {
     TopoEdgeW *topo_edge_w = nullptr;
     TopoFaceW *topo_face_w = nullptr;
     int32_t n_topo_ch = 0, n_topo_items = 0;
+    // several fields: the tets' geometry, and the field weights of one pass
+    // ([near_rows][fields of the pass], near_w_cap doubles)
+    NearTet *near_tet = nullptr;
+    int64_t near_rows = 0, near_w_cap = 0;
+    double *near_w = nullptr;
     int64_t topo_evals[3] = {0, 0, 0};  // (target, node / edge / face) evaluations per one-field evaluation
     bool p2p_topo = true;  // single-field near field over shared entities
     // stored near-field operator (optional, built by store_near): per cell
@@ -237,6 +259,9 @@ void build_tet_moments(DevicePlan &dp);
 // Geometry of the entity records (after the chunks are uploaded): edges' and
 // faces' chunk-local corners ab [ne][2], pqr [nf][3] (device).
 void build_topo_records(DevicePlan &dp, const int32_t *ab, const int32_t *pqr);
+// Geometry of the tets (after the chunks are uploaded): chunk-local corners,
+// boundary faces and first weight row of every tet (device, [T] each).
+void build_near_tets(DevicePlan &dp, const uint32_t *corner, const uint8_t *skin, const int64_t *row);
 // Fill the M2L derivative tables (after the keys are uploaded).
 void build_m2l_table(DevicePlan &dp);
 // Tiles of tpt target cells (16, 8, 4, 2 or 1), built and uploaded once.

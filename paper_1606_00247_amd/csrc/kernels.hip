@@ -2185,6 +2185,463 @@ __global__ __launch_bounds__(64, 4) void k_p2p_topo(const int32_t *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------
+// Near field of several fields.
+//
+// The nodal M is continuous over the mesh, so in
+//   4 pi u(x) = sum_faces int_F M.n / R  -  sum_T div M_T int_T 1/R
+// the surface charges of a face between two tets of a chunk cancel, and a
+// field enters a (target, tet) pair only with its divergence and, on the
+// chunk's boundary faces, with three corner charges: 1 + 3 x 1.7 numbers a tet
+// where the coefficients of the whole pair formula are 26.  With the
+// barycentric coordinates lambda of the target in the tet, F' = f / (2 L) of an
+// edge (see AtanhFar) and a_k the half solid angle of face k,
+//   lambda_i^(k) = lambda_i - 6V (grad lambda_i . grad lambda_k) mu_k,
+//                  mu_k = lambda_k 6V / (2 A_k)^2     (of the foot on face k),
+//   I_k = int_Fk 1/R / (4 A_k) = sum_{i != k} lambda_i^(k) F'_{edge opposite i in k} - mu_k a_k,
+//   int_T 1/R = 6V sum_k lambda_k I_k,
+//   int_Fk lambda_i/R / (4 A_k) = lambda_i^(k) I_k + sum_e C_{k,i,e} g'_e,
+//   g' = 2 g / L = (S^2 - L^2)(1 - t^2) F' + S (1 + t^2),  tan a_k = 12V lambda_k / den_k.
+// ---------------------------------------------------------------------------
+// edge joining corners a and b
+constexpr int kEdgeOf[4][4] = {{-1, 0, 1, 2}, {0, -1, 3, 4}, {1, 3, -1, 5}, {2, 4, 5, -1}};
+constexpr int kNearFieldsMax = 16;  // fields of one pass
+
+// One lane per tet of a chunk.
+__global__ __launch_bounds__(64) void k_tet_static(const int32_t *__restrict__ ch_i, const double *__restrict__ ch_c,
+                                                   int nch, const double *__restrict__ tet_xyz, int64_t T,
+                                                   const uint8_t *__restrict__ skin, const int64_t *__restrict__ row,
+                                                   const uint32_t *__restrict__ corner, NearTet *__restrict__ out)
+{
+    const int ch = blockIdx.x;
+    if (ch >= nch || (int)threadIdx.x >= ch_i[8 * ch + 1]) return;
+    const int64_t t = ch_i[8 * ch] + (int64_t)threadIdx.x;
+    NearTet &K = out[t];
+    K.corner = corner[t];
+    K.skin = skin[t];
+    K.row = row[t];
+    double v[4][3];
+    for (int c = 0; c < 4; ++c)
+        for (int k = 0; k < 3; ++k) v[c][k] = tet_xyz[(int64_t)(3 * c + k) * T + t] - ch_c[3 * ch + k];
+    double N[4][3];  // |.| = 2 A_k, outward: -6V grad lambda_k
+    for (int f = 0; f < 4; ++f) {
+        const int a = kFv[f][0], b = kFv[f][1], c = kFv[f][2];
+        const double p[3] = {v[b][0] - v[a][0], v[b][1] - v[a][1], v[b][2] - v[a][2]};
+        const double q[3] = {v[c][0] - v[a][0], v[c][1] - v[a][1], v[c][2] - v[a][2]};
+        N[f][0] = p[1] * q[2] - p[2] * q[1];
+        N[f][1] = p[2] * q[0] - p[0] * q[2];
+        N[f][2] = p[0] * q[1] - p[1] * q[0];
+    }
+    const double e[3] = {v[1][0] - v[0][0], v[1][1] - v[0][1], v[1][2] - v[0][2]};
+    const double v6 = -(e[0] * N[1][0] + e[1] * N[1][1] + e[2] * N[1][2]), iv = 1.0 / v6;
+    K.v12 = 2.0 * v6;
+    for (int i = 1; i < 4; ++i) {
+        for (int k = 0; k < 3; ++k) K.lam[i - 1][k] = -N[i][k] * iv;
+    }
+    for (int k = 0; k < 3; ++k) K.c[k] = 0.25 * ((v[0][k] + v[1][k]) + (v[2][k] + v[3][k]));
+    for (int k = 0; k < 4; ++k) K.kap[k] = v6 / (N[k][0] * N[k][0] + N[k][1] * N[k][1] + N[k][2] * N[k][2]);
+    for (int i = 0; i < 6; ++i) {
+        const int a = kEa[i], b = kEb[i];
+        double d2 = 0.0, g = 0.0;
+        for (int k = 0; k < 3; ++k) {
+            d2 += (v[b][k] - v[a][k]) * (v[b][k] - v[a][k]);
+            g += N[a][k] * N[b][k];
+        }
+        K.l2[i] = d2;
+        K.il2[i] = 1.0 / d2;
+        K.L[i] = sqrt(d2);
+        K.G[i] = g * iv;
+    }
+    for (int f = 0; f < 4; ++f) {
+        const int *c = kFv[f];
+        const double a2 = N[f][0] * N[f][0] + N[f][1] * N[f][1] + N[f][2] * N[f][2];
+        for (int i = 1; i < 3; ++i)
+            for (int j = 0; j < 3; ++j) {  // E_i . E_j of the edges opposite corners i and j, in cyclic direction
+                const double *p = v[c[(i + 1) % 3]], *q = v[c[(i + 2) % 3]], *r = v[c[(j + 1) % 3]], *s = v[c[(j + 2) % 3]];
+                double d = 0.0;
+                for (int k = 0; k < 3; ++k) d += (q[k] - p[k]) * (s[k] - r[k]);
+                K.C[f][i - 1][j] = -d / (8.0 * a2);
+            }
+    }
+}
+
+// Field weights of one pass, [rows][FC]: per tet -6V div M, then per boundary
+// face w_0, w_1 - w_0, w_2 - w_0 with w_i = 4 A_k n_k . M at its corner i (zero
+// past the last field).  Thread (tet, field), fields consecutive.
+template <int FC>
+__global__ __launch_bounds__(256) void k_near_weights(const NearTet *__restrict__ tet, int64_t T,
+                                                      const double *__restrict__ tet_xyz,
+                                                      const int32_t *__restrict__ tet_node,
+                                                      const double *__restrict__ M, int64_t n_nodes, int f0, int F,
+                                                      double *__restrict__ W)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, t = i / FC;
+    const int f = (int)(i % FC);
+    if (t >= T || tet[t].row < 0) return;
+    double v[4][3], m[4][3];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int64_t nd = tet_node[(int64_t)c * T + t];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            v[c][k] = tet_xyz[(int64_t)(3 * c + k) * T + t];
+            m[c][k] = f0 + f < F ? M[((int64_t)(f0 + f) * n_nodes + nd) * 3 + k] : 0.0;
+        }
+    }
+    double N[4][3], div = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int a = kFv[q][0], b = kFv[q][1], c = kFv[q][2];
+        const double p[3] = {v[b][0] - v[a][0], v[b][1] - v[a][1], v[b][2] - v[a][2]};
+        const double r[3] = {v[c][0] - v[a][0], v[c][1] - v[a][1], v[c][2] - v[a][2]};
+        N[q][0] = p[1] * r[2] - p[2] * r[1];
+        N[q][1] = p[2] * r[0] - p[0] * r[2];
+        N[q][2] = p[0] * r[1] - p[1] * r[0];
+        div += N[q][0] * m[q][0] + N[q][1] * m[q][1] + N[q][2] * m[q][2];  // -6V grad lambda_q . M_q
+    }
+    double *w = W + tet[t].row * FC + f;
+    w[0] = div;
+    const uint32_t skin = tet[t].skin;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (!(skin >> q & 1)) continue;
+        double s[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double *mm = m[kFv[q][j]];
+            s[j] = 2.0 * (N[q][0] * mm[0] + N[q][1] * mm[1] + N[q][2] * mm[2]);
+        }
+        w[FC] = s[0];
+        w[2 * FC] = s[1] - s[0];
+        w[3 * FC] = s[2] - s[0];
+        w += 3 * FC;
+    }
+}
+
+// q <- q z + c of N values, c a scalar constant (see scalar_const).
+template <int N, unsigned long long kBits>
+__device__ __forceinline__ void horner(double (&q)[N], const double (&z)[N])
+{
+    const double c = scalar_const<kBits>();
+    static_assert(N == 4 || N == 6, "faces or edges of a tet");
+    if constexpr (N == 4)
+        asm("v_fma_f64 %0, %0, %4, %8\n\tv_fma_f64 %1, %1, %5, %8\n\t"
+            "v_fma_f64 %2, %2, %6, %8\n\tv_fma_f64 %3, %3, %7, %8"
+            : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3])
+            : "v"(z[0]), "v"(z[1]), "v"(z[2]), "v"(z[3]), "s"(c));
+    else
+        asm("v_fma_f64 %0, %0, %6, %12\n\tv_fma_f64 %1, %1, %7, %12\n\tv_fma_f64 %2, %2, %8, %12\n\t"
+            "v_fma_f64 %3, %3, %9, %12\n\tv_fma_f64 %4, %4, %10, %12\n\tv_fma_f64 %5, %5, %11, %12"
+            : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]), "+v"(q[4]), "+v"(q[5])
+            : "v"(z[0]), "v"(z[1]), "v"(z[2]), "v"(z[3]), "v"(z[4]), "v"(z[5]), "s"(c));
+}
+template <int N, unsigned long long... kBits>
+__device__ __forceinline__ void horner_all(double (&q)[N], const double (&z)[N])
+{
+    (horner<N, kBits>(q, z), ...);
+}
+// AtanhFar's and AtanFar's polynomials of z, of all edges or faces of a tet
+__device__ __forceinline__ void atanh_poly(double (&q)[6], const double (&z)[6])
+{
+#pragma unroll
+    for (int e = 0; e < 6; ++e) q[e] = 1.97454264785334926424e-01;
+    horner_all<6, dbits(-1.09516507426128548164e-01), dbits(1.14547545108890203025e-01),
+               dbits(2.69135450515010227202e-02), dbits(5.65994173773324837917e-02),
+               dbits(5.83095311569123558870e-02), dbits(6.67117797972938270101e-02),
+               dbits(7.69204426675997310348e-02), dbits(9.09091891139124363974e-02),
+               dbits(1.11111108941550865148e-01), dbits(1.42857142881957860370e-01),
+               dbits(1.99999999999888822266e-01), dbits(3.33333333333333425852e-01)>(q, z);
+}
+__device__ __forceinline__ void atan_poly(double (&q)[4], const double (&z)[4])
+{
+#pragma unroll
+    for (int k = 0; k < 4; ++k) q[k] = -1.91768871190622589893e-2;
+    horner_all<4, dbits(3.923165829558719130283e-2), dbits(-5.085449737940259861323e-2),
+               dbits(5.858148912802209881646e-2), dbits(-6.664511447381948000098e-2),
+               dbits(7.692183190826086563693e-2), dbits(-9.090904578123901890479e-2),
+               dbits(1.111111101525636172749e-1), dbits(-1.428571428466654292249e-1),
+               dbits(1.999999999999552067782e-1), dbits(-3.333333333333333015966e-1)>(q, z);
+}
+
+// Work items, chunks, corner distances and closer forms as in k_p2p_topo; the
+// tets of a chunk are taken one at a time, all edges and faces of a tet side
+// by side, those with a close target in a second loop.  Bound: FP64 issue, about
+// 390 slots a (target, tet) pair and 6 more a field (the whole pair formula in
+// every lane took 935 and 27); the vector unit is busy 0.63 of the time, the
+// rest is waiting for the scalar reads of geometry and weights.  16 fields on
+// a 26^3 cube (81M pairs): 4.8 -> 2.0 ms; 5 fields on a 21^3 cube: 1.77 ->
+// 0.57; 64 on an 18^3 cube: 9.9 -> 4.6.  32 fields a pass leave two wavefronts
+// a SIMD and a quarter of the rate.  Four wavefronts a workgroup: the kernel
+// alone takes the same, but the expansion kernels beside it find room sooner
+// (whole evaluation 4.71 -> 4.43 ms at 16 fields).
+constexpr int kFieldWaves = 4;
+
+template <int FC>
+__global__ __launch_bounds__(64 * kFieldWaves, 3) void k_p2p_fields(
+    const int32_t *__restrict__ item, int nitems, const int32_t *__restrict__ ch_i, const double *__restrict__ ch_c,
+    const double *__restrict__ nw, const NearTet *__restrict__ tet, const double *__restrict__ W,
+    const int32_t *__restrict__ idx, const double *__restrict__ tgt_xyz, const int32_t *__restrict__ tgt_perm,
+    int64_t N, int f0, int F, double *__restrict__ u)
+{
+    __shared__ double s_R[kFieldWaves][kTopoNodes][64];
+    const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wg = xcd_item((nitems + kFieldWaves - 1) / kFieldWaves), it = wg * kFieldWaves + wave;
+    if (wg < 0 || it >= nitems) return;
+    const int cb = item[4 * it], ce = item[4 * it + 1], ib = item[4 * it + 2], ie = item[4 * it + 3];
+    const int s = idx[min(ib + lane, ie - 1)];
+    const double x[3] = {tgt_xyz[s], tgt_xyz[N + s], tgt_xyz[2 * N + s]};
+    double *R = &s_R[wave][0][lane];
+    double acc[FC];
+#pragma unroll
+    for (int f = 0; f < FC; ++f) acc[f] = 0.0;
+    // brings the lines of a chunk's records and weights into L2 while the chunk
+    // before it is worked on (see k_p2p_topo)
+    auto touch = [&](int ch) {
+        const int t0 = ch_i[8 * ch], n = ch_i[8 * ch + 1];
+        const ScalarMem<NearTet> *K = scalar_mem(tet + t0);
+        const int64_t r0 = K[0].row, rows = K[n - 1].row + 1 + 3 * __builtin_popcount(K[n - 1].skin) - r0;
+        const uint32_t nk = (uint32_t)(n * sizeof(NearTet)), nw = (uint32_t)(rows * FC * sizeof(double));
+        const char *pk = (const char *)(tet + t0), *pw = (const char *)(W + r0 * FC);
+        int v = 0;
+        const uint32_t at = 128u * (uint32_t)lane;
+#pragma unroll
+        for (uint32_t j = 0; j < 2; ++j)
+            if (at + 8192u * j < nk) v ^= *(const int32_t *)(pk + at + 8192u * j);
+#pragma unroll
+        for (uint32_t j = 0; j < (FC >= 16 ? 2 : 1); ++j)
+            if (at + 8192u * j < nw) v ^= *(const int32_t *)(pw + at + 8192u * j);
+        return v;
+    };
+    int seen = touch(cb);
+    for (int ch = cb; ch < ce; ++ch) {
+        asm volatile("" ::"v"(seen));
+        seen = touch(min(ch + 1, ce - 1));
+        const int tb = ch_i[8 * ch], nt = ch_i[8 * ch + 1], noff = ch_i[8 * ch + 2], nn = ch_i[8 * ch + 3];
+        const double y[3] = {x[0] - ch_c[3 * ch], x[1] - ch_c[3 * ch + 1], x[2] - ch_c[3 * ch + 2]};
+        const ScalarMem<double> *w = scalar_mem(nw + 4 * (int64_t)noff);
+#pragma unroll 2
+        for (int j = 0; j < nn; ++j) {
+            const double d0 = w[4 * j] - y[0], d1 = w[4 * j + 1] - y[1], d2 = w[4 * j + 2] - y[2];
+            R[64 * j] = sqrt_nr((d0 * d0 + d1 * d1) + d2 * d2);
+        }
+        // barycentric coordinates of the target in tet K
+        auto coords = [&](const ScalarMem<NearTet> &K, double (&lam)[4]) {
+            const double yc[3] = {y[0] - K.c[0], y[1] - K.c[1], y[2] - K.c[2]};
+            double off = 0.0;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const double g = K.lam[i][0] * yc[0] + K.lam[i][1] * yc[1] + K.lam[i][2] * yc[2];
+                lam[i + 1] = 0.25 + g;
+                off += g;
+            }
+            lam[0] = 0.25 - off;
+        };
+        // Adds tet K to the sums of all fields: F' of its edges, half solid
+        // angles of its faces, g' of an edge on demand.
+        auto add = [&](const ScalarMem<NearTet> &K, const double (&lam)[4], const double (&Fe)[6],
+                       const double (&at)[4], auto &&edge_g) {
+            const ScalarMem<double> *wr = scalar_mem(W) + K.row * FC, *w0 = wr;
+            const uint32_t skin = K.skin;
+            double vol = 0.0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int *c = kFv[k];
+                const double mu = K.kap[k] * lam[k];
+                double foot[3], I = -mu * at[k];
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    foot[j] = fma(-K.G[kEdgeOf[c[j]][k]], mu, lam[c[j]]);
+                    I = fma(foot[j], Fe[kEdgeOf[c[(j + 1) % 3]][c[(j + 2) % 3]]], I);
+                }
+                vol = fma(lam[k], I, vol);
+                if (!(skin >> k & 1)) continue;
+                wr += 3 * FC;
+                double s1 = foot[1] * I, s2 = foot[2] * I;
+#pragma unroll
+                for (int m = 0; m < 3; ++m) {
+                    const double g = edge_g(kEdgeOf[c[(m + 1) % 3]][c[(m + 2) % 3]]);
+                    s1 = fma(K.C[k][0][m], g, s1);
+                    s2 = fma(K.C[k][1][m], g, s2);
+                }
+#pragma unroll
+                for (int f = 0; f < FC; ++f)
+                    acc[f] = fma(wr[f], s2, fma(wr[f - FC], s1, fma(wr[f - 2 * FC], I, acc[f])));
+            }
+#pragma unroll
+            for (int f = 0; f < FC; ++f) acc[f] = fma(w0[f], vol, acc[f]);
+        };
+        // F' = a + a z Q(z) (shifted by as - a) and the half angles t + t^3 Q(t^2)
+        // (shifted by ts - t).
+        auto series = [&](const double (&z)[6], const double (&a)[6], const double (&as)[6], const double (&t)[4],
+                          const double (&ts)[4], double (&Fe)[6], double (&at)[4]) {
+            double q[6], r[4], zf[4];
+            atanh_poly(q, z);
+#pragma unroll
+            for (int e = 0; e < 6; ++e) Fe[e] = fma(a[e] * z[e], q[e], as[e]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) zf[k] = t[k] * t[k];
+            atan_poly(r, zf);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) at[k] = fma(t[k] * zf[k], r[k], ts[k]);
+        };
+        auto far_g = [&](const ScalarMem<NearTet> &K, const double (&Rc)[4], const double (&Fe)[6], int e) {
+            const double D = Rc[kEb[e]] - Rc[kEa[e]], S = Rc[kEa[e]] + Rc[kEb[e]], t2 = D * (D * K.il2[e]);
+            return fma(fma(S, S, -K.l2[e]) * (1.0 - t2), Fe[e], fma(t2, S, S));
+        };
+        uint32_t near = 0;  // tets with a target of this wavefront too close, taken after the others
+#pragma unroll 1
+        for (int j = 0; j < nt; ++j) {
+            const ScalarMem<NearTet> &K = *scalar_mem(tet + tb + j);
+            const uint32_t cn = K.corner;
+            double Rc[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) Rc[c] = R[64 * (cn >> (8 * c) & 255)];
+            double S[6], z[6], iv[6], top = 0.0;
+#pragma unroll
+            for (int e = 0; e < 6; ++e) S[e] = Rc[kEa[e]] + Rc[kEb[e]];
+#pragma unroll
+            for (int e = 0; e < 6; e += 2) {
+                const double ri = rcp_nr(S[e] * S[e + 1]);
+                iv[e] = ri * S[e + 1];
+                iv[e + 1] = ri * S[e];
+            }
+#pragma unroll
+            for (int e = 0; e < 6; ++e) {
+                z[e] = K.l2[e] * (iv[e] * iv[e]);
+                top = fmax(top, z[e]);
+            }
+            double lam[4], den[4], tn[4];
+            coords(K, lam);
+            bool bad = !(top <= kEdgeFar * kEdgeFar);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int a = kFv[k][0], b = kFv[k][1], c = kFv[k][2];
+                const int ea = kEdgeOf[b][c], eb = kEdgeOf[a][c], ec = kEdgeOf[a][b];
+                const double P = S[ec] * S[ea] * S[eb];
+                den[k] = P - fma(K.l2[ec], Rc[c], fma(K.l2[eb], Rc[b], K.l2[ea] * Rc[a]));
+                bad = bad || !(den[k] >= kFaceCond * P);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; k += 2) {
+                const double ri = rcp_nr(den[k] * den[k + 1]) * K.v12;
+                tn[k] = lam[k] * (ri * den[k + 1]);
+                tn[k + 1] = lam[k + 1] * (ri * den[k]);
+            }
+            bad = bad || !(fmax(fmax(fabs(tn[0]), fabs(tn[1])), fmax(fabs(tn[2]), fabs(tn[3]))) <= kFaceTan);
+            if (__any(bad)) {
+                near |= 1u << j;
+                continue;
+            }
+            double Fe[6], at[4];
+            series(z, iv, iv, tn, tn, Fe, at);
+            add(K, lam, Fe, at, [&](int e) { return far_g(K, Rc, Fe, e); });
+        }
+        // the shifted forms (see k_p2p_topo), or closer still the branch-free
+        // forms of the pair formula
+        while (near) {
+            const int j = __builtin_ctz(near);
+            near &= near - 1;
+            const ScalarMem<NearTet> &K = *scalar_mem(tet + tb + j);
+            const uint32_t cn = K.corner;
+            double Rc[4], lam[4], Fe[6], gp[6], at[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) Rc[c] = R[64 * (cn >> (8 * c) & 255)];
+            coords(K, lam);
+            bool close = false;
+            double c[6], nm[4], df[4], of[4];
+#pragma unroll
+            for (int e = 0; e < 6; ++e) {
+                const double Ra = Rc[kEa[e]], Rb = Rc[kEb[e]], Sm = Ra + Rb;
+                const bool in = kEdgeFar * Sm < K.L[e] && fmin(Ra, Rb) > 0.0;
+                close = close || (in && kEdgeMid * Sm < K.L[e]);
+                c[e] = in ? kEdgeShift : 0.0;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double Ra = Rc[kFv[k][0]], Rb = Rc[kFv[k][1]], Rd = Rc[kFv[k][2]];
+                const double Pk = (Ra + Rb) * (Rb + Rd) * (Rd + Ra);
+                const double dk = Pk - fma(K.l2[kEdgeOf[kFv[k][0]][kFv[k][1]]], Rd,
+                                           fma(K.l2[kEdgeOf[kFv[k][0]][kFv[k][2]]], Rb,
+                                               K.l2[kEdgeOf[kFv[k][1]][kFv[k][2]]] * Ra));
+                const bool corner = !(fmin(fmin(Ra, Rb), Rd) > 0.0);
+                const double nk = K.v12 * lam[k], an = fabs(nk), d = corner ? 1.0 : dk;
+                const bool wide = an > kFaceTan * d;
+                close = close || (!corner && (!(d >= kFaceCond * Pk) || kFaceTan * an > d));
+                const double p = copysign(wide ? an - d : an, nk);
+                nm[k] = wide && an < d ? -p : p;
+                df[k] = wide ? an + d : d;
+                of[k] = wide ? copysign(0.78539816339744827900, nk) : 0.0;
+            }
+            if (!__any(close)) {
+                double zs[6], as[6], a1[6], ts[4], t1[4];
+#pragma unroll
+                for (int e = 0; e < 6; e += 2) {
+                    const double S0 = Rc[kEa[e]] + Rc[kEb[e]], S1 = Rc[kEa[e + 1]] + Rc[kEb[e + 1]];
+                    const double d0 = fma(-c[e], K.L[e], S0), d1 = fma(-c[e + 1], K.L[e + 1], S1);
+                    const double ri = rcp_nr(d0 * d1);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const double sv = fma(-c[e + j], j ? S1 : S0, K.L[e + j]) * (ri * (j ? d0 : d1));
+                        const double il = K.L[e + j] * K.il2[e + j];
+                        zs[e + j] = sv * sv;
+                        a1[e + j] = sv * il;
+                        as[e + j] = fma(c[e + j], kEdgeShiftAtanh / kEdgeShift, sv) * il;
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 4; k += 2) {
+                    const double ri = rcp_nr(df[k] * df[k + 1]);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        t1[k + j] = nm[k + j] * (ri * df[k + 1 - j]);
+                        ts[k + j] = t1[k + j] + of[k + j];
+                    }
+                }
+                series(zs, a1, as, t1, ts, Fe, at);
+#pragma unroll
+                for (int e = 0; e < 6; ++e) gp[e] = far_g(K, Rc, Fe, e);
+            } else {
+                double d[4][3];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const ScalarMem<double> *v = w + 4 * (cn >> (8 * q) & 255);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) d[q][k] = v[k] - y[k];
+                }
+#pragma unroll
+                for (int e = 0; e < 6; ++e) {
+                    const int p = kEa[e], q = kEb[e];
+                    const double il2 = K.il2[e], il = K.L[e] * il2;
+                    const double dab = d[p][0] * d[q][0] + d[p][1] * d[q][1] + d[p][2] * d[q][2];
+                    const double la = fma(-Rc[p], Rc[p], dab) * il, lb = fma(Rc[q], Rc[q], -dab) * il;
+                    const double c0 = d[p][1] * d[q][2] - d[p][2] * d[q][1],
+                                 c1 = d[p][2] * d[q][0] - d[p][0] * d[q][2],
+                                 c2 = d[p][0] * d[q][1] - d[p][1] * d[q][0];
+                    const double r0sq = (c0 * c0 + c1 * c1 + c2 * c2) * il2;
+                    const double f = edge_log<false, true>(Rc[p], Rc[q], la, lb, r0sq);
+                    Fe[e] = 0.5 * f * il;
+                    gp[e] = 2.0 * il * (r0sq * f + lb * Rc[q] - la * Rc[p]);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int i0 = kFv[k][0], i1 = kFv[k][1], i2 = kFv[k][2];
+                    auto dt = [&](int p, int q) { return d[p][0] * d[q][0] + d[p][1] * d[q][1] + d[p][2] * d[q][2]; };
+                    at[k] = atan2_nr<true>(0.5 * (K.v12 * lam[k]), Rc[i0] * Rc[i1] * Rc[i2] + dt(i0, i1) * Rc[i2] +
+                                                                       dt(i0, i2) * Rc[i1] + dt(i1, i2) * Rc[i0]);
+                }
+            }
+            add(K, lam, Fe, at, [&](int e) { return gp[e]; });
+        }
+    }
+    asm volatile("" ::"v"(seen));
+    if (ib + lane < ie) {
+        const int64_t o = tgt_perm[s];
+#pragma unroll
+        for (int f = 0; f < FC; ++f)
+            if (f0 + f < F) atomicAdd(&u[(int64_t)(f0 + f) * N + o], acc[f] * kInv4Pi);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Stored near-field operator (Sec. 2.1: the direct part is linear in the
 // nodal magnetisation, so its node-to-node coefficients can be kept for a
 // fixed mesh).  u_T(x) = sum_{corners c, axes j} C_{T,c,j}(x) M_{node(T,c), j}
@@ -2504,7 +2961,6 @@ void hip_check(hipError_t e, const char *what)
 
 namespace {
 
-// Calls fn with std::integral_constant<int, field_chunk(F)>.
 // Calls fn with std::integral_constant<int, p> for 1 <= p <= kPmax.
 template <class Fn>
 void with_order(int p, Fn &&fn)
@@ -2523,6 +2979,7 @@ void with_order(int p, Fn &&fn)
     }
 }
 
+// Calls fn with std::integral_constant<int, field_chunk(F)>.
 template <class Fn>
 void launch_fc(int F, Fn &&fn)
 {
@@ -2661,6 +3118,69 @@ void run_p2p_points(DevicePlan &dp, bool direct, const double *M, int32_t F, dou
     }
 }
 
+// One field over the shared mesh entities.
+void run_p2p_topo(DevicePlan &dp, const double *M, double *u, hipStream_t st)
+{
+    const HostPlan &hp = dp.hp;
+    if (dp.n_topo_items == 0) return;
+    k_topo_coef<<<dim3((unsigned)((dp.n_topo_ch + kTopoChunksPerWave - 1) / kTopoChunksPerWave)), dim3(64), 0, st>>>(
+        dp.topo_ch_i, dp.topo_ch_c, dp.n_topo_ch, dp.topo_inc, dp.tet_xyz, dp.tet_node, hp.n_tets, M, dp.topo_edge,
+        dp.topo_edge_w, dp.topo_face_w);
+    hip_check(hipGetLastError(), "k_topo_coef launch");
+    k_p2p_topo<<<dim3(xcd_grid(dp.n_topo_items)), dim3(64), 0, st>>>(
+        dp.topo_item, dp.n_topo_items, dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_edge, dp.topo_face,
+        dp.topo_edge_w, dp.topo_face_w, dp.p2p_idx, dp.tgt_xyz, dp.tgt_perm, hp.n_targets, u);
+    hip_check(hipGetLastError(), "k_p2p_topo launch");
+}
+
+// Fields of the pass that starts with `left` fields to go: the geometry of a
+// pair (about 390 issue slots) costs as much as the fields' part of 65 fields
+// (6 slots each), so the next power of two covers what is left, padded, rather
+// than two passes; one field alone takes the shared entities.
+int near_pass(int left)
+{
+    int fc = 1;
+    while (fc < left && fc < kNearFieldsMax) fc *= 2;
+    return fc;
+}
+
+// Calls fn with the pass width as an integral constant (2, 4, ..., kNearFieldsMax).
+template <class Fn>
+void with_near_pass(int fc, Fn &&fn)
+{
+    switch (fc) {
+    case 16: fn(std::integral_constant<int, 16>{}); break;
+    case 8: fn(std::integral_constant<int, 8>{}); break;
+    case 4: fn(std::integral_constant<int, 4>{}); break;
+    default: fn(std::integral_constant<int, 2>{}); break;
+    }
+}
+
+// Several fields, in passes.
+void run_p2p_fields(DevicePlan &dp, const double *M, int32_t F, double *u, hipStream_t st)
+{
+    const HostPlan &hp = dp.hp;
+    if (dp.n_topo_items == 0) return;
+    for (int f = 0; f < F;) {
+        const int fc = near_pass(F - f);
+        if (fc == 1) {
+            run_p2p_topo(dp, M + (int64_t)f * hp.n_nodes * 3, u + (int64_t)f * hp.n_targets, st);
+        } else {
+            if (dp.near_w_cap < dp.near_rows * fc) throw DeviceError{"near-field weights not prepared"};
+            with_near_pass(fc, [&](auto c) {
+                constexpr int FC = decltype(c)::value;
+                k_near_weights<FC><<<dim3((unsigned)((hp.n_tets * FC + 255) / 256)), dim3(256), 0, st>>>(
+                    dp.near_tet, hp.n_tets, dp.tet_xyz, dp.tet_node, M, hp.n_nodes, f, F, dp.near_w);
+                k_p2p_fields<FC><<<dim3(xcd_grid((dp.n_topo_items + kFieldWaves - 1) / kFieldWaves)), dim3(64 * kFieldWaves), 0, st>>>(
+                    dp.topo_item, dp.n_topo_items, dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.near_tet, dp.near_w,
+                    dp.p2p_idx, dp.tgt_xyz, dp.tgt_perm, hp.n_targets, f, F, u);
+            });
+            hip_check(hipGetLastError(), "k_p2p_fields launch");
+        }
+        f += fc;
+    }
+}
+
 // Near field by the pair integrals: point dipoles (or, direct, the dipole
 // sum); one field of tets over the shared mesh entities; otherwise the
 // per-tet kernel, without the band's pairs when band_skip.
@@ -2671,17 +3191,11 @@ void run_p2p(DevicePlan &dp, bool direct, const double *M, int32_t F, double *u,
         return;
     }
     if (direct) throw DeviceError{"the tet direct sum runs in k_direct"};
-    if (!band_skip && F == 1 && dp.p2p_topo && dp.n_topo_ch > 0) {
-        const HostPlan &hp = dp.hp;
-        k_topo_coef<<<dim3((unsigned)((dp.n_topo_ch + kTopoChunksPerWave - 1) / kTopoChunksPerWave)), dim3(64), 0, st>>>(dp.topo_ch_i, dp.topo_ch_c, dp.n_topo_ch, dp.topo_inc,
-                                                             dp.tet_xyz, dp.tet_node, hp.n_tets, M,
-                                                             dp.topo_edge, dp.topo_edge_w, dp.topo_face_w);
-        hip_check(hipGetLastError(), "k_topo_coef launch");
-        if (dp.n_topo_items == 0) return;
-        k_p2p_topo<<<dim3(xcd_grid(dp.n_topo_items)), dim3(64), 0, st>>>(
-            dp.topo_item, dp.n_topo_items, dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_edge, dp.topo_face,
-            dp.topo_edge_w, dp.topo_face_w, dp.p2p_idx, dp.tgt_xyz, dp.tgt_perm, hp.n_targets, u);
-        hip_check(hipGetLastError(), "k_p2p_topo launch");
+    if (!band_skip && dp.p2p_topo && dp.n_topo_ch > 0) {
+        if (F == 1)
+            run_p2p_topo(dp, M, u, st);
+        else
+            run_p2p_fields(dp, M, F, u, st);
         return;
     }
     int f = 0;
@@ -3058,6 +3572,17 @@ void build_topo_records(DevicePlan &dp, const int32_t *ab, const int32_t *pqr)
     hip_check(hipDeviceSynchronize(), "k_topo_static");
 }
 
+void build_near_tets(DevicePlan &dp, const uint32_t *corner, const uint8_t *skin, const int64_t *row)
+{
+    if (dp.n_topo_ch == 0) return;
+    // tets outside every block (leaves without near targets) keep row -1
+    (void)hipMemset(dp.near_tet, 0xff, sizeof(NearTet) * (size_t)dp.hp.n_tets);
+    k_tet_static<<<dim3((unsigned)dp.n_topo_ch), dim3(64)>>>(dp.topo_ch_i, dp.topo_ch_c, dp.n_topo_ch, dp.tet_xyz,
+                                                             dp.hp.n_tets, skin, row, corner, dp.near_tet);
+    hip_check(hipGetLastError(), "k_tet_static launch");
+    hip_check(hipDeviceSynchronize(), "k_tet_static");
+}
+
 void build_m2l_table(DevicePlan &dp)
 {
     if (dp.n_m2l_keys == 0) return;
@@ -3268,6 +3793,14 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
         hip_check(hipEventCreateWithFlags(&dp.ev_join, hipEventDisableTiming), "hipEventCreate");
     }
     ensure_expansions(dp, F);
+    if (F > 1 && !dp.near_stored && dp.sur_mode == TFMM_SUR_OFF && dp.near_w_cap < dp.near_rows * near_pass(F)) {
+        ++dp.schedule_gen;  // a captured graph may hold the old weights
+        if (dp.near_w) (void)hipFree(dp.near_w);
+        dp.near_w = nullptr;
+        dp.near_w_cap = 0;
+        hip_check(hipMalloc(&dp.near_w, sizeof(double) * (size_t)(dp.near_rows * near_pass(F))), "hipMalloc near weights");
+        dp.near_w_cap = dp.near_rows * near_pass(F);
+    }
     if (m2l_packed(dp, F)) {
         ensure_m2l_packs(dp, F);
     } else {

@@ -737,6 +737,9 @@ void build_near_topology(const HostPlan &hp, const std::vector<int32_t> &blk, Ne
     static const int kFv[4][3] = {{1, 2, 3}, {0, 3, 2}, {0, 1, 3}, {0, 2, 1}};
     out = NearTopo{};
     out.inc.assign((size_t)hp.n_tets * 10, -1);
+    out.skin.assign((size_t)hp.n_tets, 0);
+    out.corner.assign((size_t)hp.n_tets, 0);
+    std::vector<int32_t> owners, turn;  // per face of a chunk: its tets, and their orientations' sum
     const size_t nblk = blk.size() / 4;
     std::vector<int32_t> nodes, edges, faces;  // chunk: node ids, (a,b) id pairs, (p,q,r) id triples
     auto find = [](const std::vector<int32_t> &v, const int32_t *key, int w) -> int {
@@ -787,6 +790,29 @@ void build_near_topology(const HostPlan &hp, const std::vector<int32_t> &blk, Ne
                     out.inc[10 * (size_t)t + 6 + k] = find(faces, key, 3);
                 }
             }
+            // A face between two tets of the chunk, one on either side, is an
+            // inner one; every other face is on the chunk's boundary.
+            owners.assign(faces.size() / 3, 0);
+            turn.assign(faces.size() / 3, 0);
+            auto side = [&](int32_t i, int k) {  // sign of the outward corner order against the sorted one
+                const int32_t *v = &hp.tet_nodes[4 * (size_t)i];
+                const int32_t a = v[kFv[k][0]], b = v[kFv[k][1]], c = v[kFv[k][2]];
+                return ((a < b) + (b < c) + (c < a)) == 2 ? 1 : -1;
+            };
+            for (int32_t i = s; i < t; ++i)
+                for (int k = 0; k < 4; ++k) {
+                    const int32_t f = out.inc[10 * (size_t)i + 6 + k];
+                    ++owners[f];
+                    turn[f] += side(i, k);
+                }
+            for (int32_t i = s; i < t; ++i)
+                for (int c = 0; c < 4; ++c)
+                    out.corner[(size_t)i] |= (uint32_t)find(nodes, &hp.tet_nodes[4 * (size_t)i + c], 1) << (8 * c);
+            for (int32_t i = s; i < t; ++i)
+                for (int k = 0; k < 4; ++k) {
+                    const int32_t f = out.inc[10 * (size_t)i + 6 + k];
+                    if (!(owners[f] == 2 && turn[f] == 0)) out.skin[(size_t)i] |= (uint8_t)(1 << k);
+                }
             // chunk record
             const int32_t noff = (int32_t)(out.nd_w.size() / 4), eoff = (int32_t)(out.ed_ab.size() / 2),
                           foff = (int32_t)(out.fc_pqr.size() / 3);

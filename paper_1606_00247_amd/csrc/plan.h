@@ -117,6 +117,8 @@ struct NearTopo {
     std::vector<int32_t> ed_ab;   // [edges][2] chunk-local nodes
     std::vector<int32_t> fc_pqr;  // [faces][3] chunk-local nodes
     std::vector<uint8_t> pad;     // [nch][2] edges and faces listed twice
+    std::vector<uint32_t> corner; // [T] chunk-local corners, a byte each
+    std::vector<uint8_t> skin;    // [T] faces (bit k: opposite corner k) on the boundary of the tet's chunk
     std::vector<int32_t> inc;     // [T][10] per tet: 6 edge, 4 face chunk-local indices
 };
 

@@ -1,4 +1,4 @@
-"""One-field near field over shared entities: its far, shifted and close forms
+"""Near field of one and of several fields: its far, shifted and close forms
 against the oracle's direct sum, with every pair in the near field (theta so
 small that nothing is accepted), and the work items' edges."""
 import numpy as np
@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 def _evaluate(nodes, tets, M, targets, leaf):
+    """u [F, n] of M [F, n_nodes, 3]."""
     import torch
 
     import paper_1606_00247_amd as T
@@ -59,3 +60,31 @@ def test_work_item_edges_vs_oracle(mesh, n):
     u = _evaluate(nodes, tets, M, x, 64)
     ref = oracle.direct(nodes, tets, M, targets=x)
     assert np.abs(u - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("F", [2, 3, 5, 9, 17, 33])
+@pytest.mark.parametrize("eps", [0.0, 1e-9, 1e-3, 0.2])
+def test_several_fields_vs_oracle(eps, F):
+    """Passes of 2, 4, 8 and 16 fields, full and padded, and a last field alone."""
+    rng = np.random.default_rng(F)
+    nodes, tets = meshgen.box_mesh((3, 2, 3), seed=2)
+    M = meshgen.random_fields(len(nodes), F=F, seed=9)
+    x = _close_targets(nodes, tets, eps, rng, n=30)
+    u = _evaluate(nodes, tets, M, x, 13)
+    ref = oracle.direct(nodes, tets, M, targets=x)
+    for f in range(F):
+        assert np.linalg.norm(u[f] - ref[f]) <= 1e-12 * np.linalg.norm(ref[f])
+
+
+@pytest.mark.parametrize("F", [1, 4])
+def test_faces_shared_in_odd_ways_vs_oracle(F):
+    """Faces of three tets, of two tets on the same side and of a tet listed
+    twice: only a face between two tets, one on either side, cancels."""
+    nodes = np.array([[0.0, 0, 0], [1, 0, 0], [0, 1, 0], [0, 0, 1], [0.2, 0.2, 0.7], [0.3, 0.3, -0.8], [1.1, 0.9, 0.8]])
+    tets = np.array([[0, 1, 2, 3], [0, 1, 2, 4], [0, 2, 1, 5], [1, 2, 3, 6], [1, 2, 3, 6]], dtype=np.int32)
+    M = meshgen.random_fields(len(nodes), F=F, seed=5)
+    x = np.random.default_rng(1).uniform(-0.5, 1.5, (70, 3))
+    u = _evaluate(nodes, tets, M, x, 64).reshape(F, -1)
+    ref = oracle.direct(nodes, tets, M, targets=x).reshape(F, -1)
+    for f in range(F):
+        assert np.linalg.norm(u[f] - ref[f]) <= 1e-12 * np.linalg.norm(ref[f])
