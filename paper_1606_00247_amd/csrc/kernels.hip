@@ -208,18 +208,28 @@ __global__ __launch_bounds__(kMomThreads) void k_tet_moments(const int32_t *__re
 }
 
 // ---------------------------------------------------------------------------
-// P2M.  One workgroup per leaf holding tets (XCD-contiguous), FC fields per
-// workgroup (blockIdx.y = field chunk).  With the per-tet moments
+// P2M.  One workgroup per leaf holding tets and FC fields (XCD-contiguous, the
+// field chunks of a leaf next to each other).  With the per-tet moments
 // S_m = int_T (y - c)^m (exact, once per plan) and, per field, the affine
 // magnetisation M(y) = M(c) + G (y - c) of the tet,
-//   Q_n = sum_T sum_k n_k [M_k(c) S_{n-e_k} + sum_d G_kd S_{n-e_k+e_d}].
-// Tets are staged kP2MStage at a time: their moments and the 12 field values
-// of every (tet, field) pair (one thread each) go to LDS, then every thread
-// accumulates its coefficients n over the staged tets for all FC fields.
+//   Q_n = sum_T sum_k n_k [M_k(c) S_{n-e_k} + sum_d G_kd S_{n-e_k+e_d}]
+//       = sum_k n_k [U_k,{n-e_k} + sum_d U_kd,{n-e_k+e_d}],
+//   U_j,m = sum_T W_jT S_m,T   (j the 12 field values of a tet),
+// a contraction over the leaf's tets on the FP64 matrix cores: A = W (rows
+// field x 12 values), B = the moments, straight from memory in their operand
+// layout (four rows of 128 consecutive bytes), columns dealt to the four
+// wavefronts.  The shifts by e_k and e_d are taken once per leaf, on U in LDS.
+// Bound: the moments' bytes (507 MB on the 40^3 cube, one field: 105 us at the
+// rate of a large copy).  One field there 416 -> 239 us, on a film of 387k tets
+// (17 a leaf) 1.23 -> 0.44 ms, 16 fields on a 26^3 cube 0.60 -> 0.33 ms, against
+// one coefficient a thread with its 12 gathers a tet from LDS; the rest is the
+// field values of a leaf, formed before its contraction can start.
 // ---------------------------------------------------------------------------
-__host__ __device__ constexpr int field_chunk(int F) { return F >= 16 ? 16 : (F >= 4 ? 4 : 1); }
+__host__ __device__ constexpr int field_chunk(int F) { return F >= 3 ? 4 : 1; }
 constexpr int kP2MThreads = 256;
 constexpr int kP2MStage = 16;
+// column tiles (16 coefficients) of each of the four wavefronts
+__host__ __device__ constexpr int p2m_tiles(int p) { return ((ncoef_of(p) + 15) / 16 + 3) / 4; }
 
 // M(c) [3] and G [3][3] of tet t for one field (nodal values Mf).
 __device__ inline void tet_affine_field(const double *__restrict__ tet_xyz, const int32_t *__restrict__ tet_node,
@@ -275,93 +285,97 @@ __device__ inline void tet_affine_field(const double *__restrict__ tet_xyz, cons
     }
 }
 
-// Dynamic LDS: S [kP2MStage][ncoef], W [kP2MStage][FC][12] doubles.
-template <int FC>
-__global__ __launch_bounds__(kP2MThreads) void k_p2m(const int32_t *__restrict__ cells, const int32_t *__restrict__ cell_i,
+// Dynamic LDS: U [12][64 NT] doubles.
+template <int FC, int NT>
+__global__ __launch_bounds__(kP2MThreads, FC == 1 ? 4 : (NT <= 3 ? 3 : 2)) void k_p2m(const int32_t *__restrict__ cells, const int32_t *__restrict__ cell_i,
                                                      const double *__restrict__ cell_c, int64_t C,
                                                      const double *__restrict__ tet_xyz, const int32_t *__restrict__ tet_node,
                                                      int64_t T, const double *__restrict__ mom,
                                                      const double *__restrict__ M, int64_t n_nodes, int F, int p,
                                                      int ncells, int points, LevelOrders lo, double *__restrict__ Q)
 {
-    extern __shared__ double s_dyn[];
-    const int ncoef = ncoef_of(p);
-    double *s_S = s_dyn;                        // [kP2MStage][ncoef]
-    double *s_W = s_dyn + kP2MStage * ncoef;    // [kP2MStage][FC][12]
-    const int item = xcd_item(ncells);
+    using v4 = double __attribute__((ext_vector_type(4)));
+    constexpr int NROW = FC == 1 ? 16 : 12 * FC, NRT = NROW / 16;  // rows, row tiles
+    extern __shared__ double s_U[];
+    __shared__ double s_W[kP2MStage][NROW];
+    const int ncoef = ncoef_of(p), nch = (F + FC - 1) / FC;
+    const int item = xcd_item(ncells * nch);
     if (item < 0) return;
-    const int cell = cells[item];
-    const int f0 = blockIdx.y * FC;
+    const int cell = cells[item / nch], f0 = item % nch * FC;
     const int tbeg = cell_i[CI_N * cell + CI_TBEG], tend = cell_i[CI_N * cell + CI_TEND];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, kq = lane >> 4;
     const double cc[3] = {cell_c[cell], cell_c[C + cell], cell_c[2 * C + cell]};
-    double acc[2][FC];
+    v4 acc[NRT][NT];
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int rt = 0; rt < NRT; ++rt)
 #pragma unroll
-        for (int j = 0; j < FC; ++j) acc[r][j] = 0.0;
+        for (int j = 0; j < NT; ++j) acc[rt][j] = v4{0, 0, 0, 0};
+    for (int i = tid; i < kP2MStage * NROW; i += kP2MThreads) (&s_W[0][0])[i] = 0.0;
     for (int sb = tbeg; sb < tend; sb += kP2MStage) {
-        const int nt = min(kP2MStage, tend - sb);
+        const int nt = min(kP2MStage, tend - sb), nk = (nt + 3) >> 2;
         __syncthreads();
-        for (int i = tid; i < nt * ncoef; i += blockDim.x) s_S[i] = mom[(int64_t)sb * ncoef + i];
-        for (int i = tid; i < nt * FC; i += blockDim.x) {
+        for (int i = tid; i < 4 * nk * FC; i += kP2MThreads) {
             const int t = i / FC, j = i - t * FC;
-            if (f0 + j < F && points) {  // a dipole: M(c) = its moment, no gradient
+            double *w = &s_W[t][12 * j];
+            if (t >= nt || f0 + j >= F)
+                for (int q = 0; q < 12; ++q) w[q] = 0.0;
+            else if (points) {  // a dipole: M(c) = its moment, no gradient
                 const double *m = M + ((int64_t)(f0 + j) * n_nodes + tet_node[sb + t]) * 3;
-                double *w = s_W + (t * FC + j) * 12;
                 for (int q = 0; q < 12; ++q) w[q] = q < 3 ? m[q] : 0.0;
-            } else if (f0 + j < F)
-                tet_affine_field(tet_xyz, tet_node, T, sb + t, M + (int64_t)(f0 + j) * n_nodes * 3, cc,
-                                 s_W + (t * FC + j) * 12);
-            else
-                for (int q = 0; q < 12; ++q) s_W[(t * FC + j) * 12 + q] = 0.0;
+            } else
+                tet_affine_field(tet_xyz, tet_node, T, sb + t, M + (int64_t)(f0 + j) * n_nodes * 3, cc, w);
         }
+        // moments of the first four tets, on their way during the field values
+        auto moments = [&](double (&b)[NT], int ks) {
+            const double *S = mom + (int64_t)(sb + min(4 * ks + kq, nt - 1)) * ncoef;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) b[j] = S[min(16 * (wave + 4 * j) + col, ncoef - 1)];
+        };
+        double b[2][NT];
+        moments(b[0], 0);
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int n = tid + r * kP2MThreads;
-            if (n >= ncoef) continue;
-            const int nv[3] = {c_mi.v[n][0], c_mi.v[n][1], c_mi.v[n][2]};
-            // indices of S_{n-e_k} and S_{n-e_k+e_d}
-            int si[3][4];
+        for (int ks = 0; ks < kP2MStage / 4; ++ks) {
+            if (ks >= nk) break;
+            if (ks + 1 < kP2MStage / 4) moments(b[(ks + 1) & 1], ks + 1);
+            double a[NRT];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                int b[3] = {nv[0], nv[1], nv[2]};
-                b[k] = b[k] > 0 ? b[k] - 1 : 0;
-                si[k][0] = mi_index(b[0], b[1], b[2]);
-                si[k][1] = mi_index(b[0] + 1, b[1], b[2]);
-                si[k][2] = mi_index(b[0], b[1] + 1, b[2]);
-                si[k][3] = mi_index(b[0], b[1], b[2] + 1);
-            }
-            for (int t = 0; t < nt; ++t) {
-                const double *S = s_S + t * ncoef;
-                double sv[3][4];
+            for (int rt = 0; rt < NRT; ++rt) a[rt] = s_W[4 * ks + kq][16 * rt + col];
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
+            for (int j = 0; j < NT; ++j)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) sv[k][q] = nv[k] ? nv[k] * S[si[k][q]] : 0.0;
-#pragma unroll
-                for (int j = 0; j < FC; ++j) {
-                    const double *w = s_W + (t * FC + j) * 12;
-                    double sacc = acc[r][j];
-#pragma unroll
-                    for (int k = 0; k < 3; ++k)
-                        sacc += w[k] * sv[k][0] + w[3 + 3 * k] * sv[k][1] + w[4 + 3 * k] * sv[k][2] +
-                                w[5 + 3 * k] * sv[k][3];
-                    acc[r][j] = sacc;
-                }
-            }
+                for (int rt = 0; rt < NRT; ++rt)
+                    acc[rt][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rt], b[ks & 1][j], acc[rt][j], 0, 0, 0);
         }
     }
     // kept to the order of the leaf's level (the rest stays zero)
     const int nkeep = ncoef_of(lo.q[cell_i[CI_N * cell + CI_LEVEL]]);
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int n = tid + r * kP2MThreads;
-        if (n >= ncoef) continue;
+    for (int f = 0; f < FC; ++f) {
+        if (f0 + f >= F) break;
+        __syncthreads();
 #pragma unroll
-        for (int j = 0; j < FC; ++j)
-            if (f0 + j < F) Q[((int64_t)(f0 + j) * C + cell) * ncoef + n] = n < nkeep ? acc[r][j] : 0.0;
+        for (int g = 3 * f; g < 3 * f + 3; ++g)  // rows 4 g + kq: the field's values 4 (g - 3 f) + kq
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                s_U[(4 * (g - 3 * f) + kq) * 64 * NT + 16 * (wave + 4 * j) + col] = acc[g >> 2][j][g & 3];
+        __syncthreads();
+        for (int n = tid; n < ncoef; n += kP2MThreads) {
+            const int nv[3] = {c_mi.v[n][0], c_mi.v[n][1], c_mi.v[n][2]};
+            double q = 0.0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                if (nv[k] == 0 || n >= nkeep) continue;
+                int b[3] = {nv[0], nv[1], nv[2]};
+                --b[k];
+                const double *U = s_U + (3 + 3 * k) * 64 * NT;
+                q += nv[k] * (s_U[k * 64 * NT + mi_index(b[0], b[1], b[2])] + U[mi_index(b[0] + 1, b[1], b[2])] +
+                              U[64 * NT + mi_index(b[0], b[1] + 1, b[2])] +
+                              U[2 * 64 * NT + mi_index(b[0], b[1], b[2] + 1)]);
+            }
+            Q[((int64_t)(f0 + f) * C + cell) * ncoef + n] = q;
+        }
     }
 }
 
@@ -2979,16 +2993,25 @@ void with_order(int p, Fn &&fn)
     }
 }
 
-// Calls fn with std::integral_constant<int, field_chunk(F)>.
+// Calls fn with the field chunk and the column tiles of P2M.
 template <class Fn>
-void launch_fc(int F, Fn &&fn)
+void with_p2m(int F, int p, Fn &&fn)
 {
-    switch (field_chunk(F)) {
-    case 16: fn(std::integral_constant<int, 16>{}); break;
-    case 4: fn(std::integral_constant<int, 4>{}); break;
-    default: fn(std::integral_constant<int, 1>{}); break;
-    }
+    auto tiles = [&](auto fc) {
+        switch (p2m_tiles(p)) {
+        case 1: fn(fc, std::integral_constant<int, 1>{}); break;
+        case 2: fn(fc, std::integral_constant<int, 2>{}); break;
+        case 3: fn(fc, std::integral_constant<int, 3>{}); break;
+        case 4: fn(fc, std::integral_constant<int, 4>{}); break;
+        default: fn(fc, std::integral_constant<int, 5>{}); break;
+        }
+    };
+    if (field_chunk(F) == 1)
+        tiles(std::integral_constant<int, 1>{});
+    else
+        tiles(std::integral_constant<int, 4>{});
 }
+static_assert(p2m_tiles(kPmax) <= 5, "column tiles of P2M");
 
 hipEvent_t pool_event(DevicePlan &dp)
 {
@@ -3953,10 +3976,10 @@ void run_evaluate(DevicePlan &dp, const double *M, int32_t F, double *u, hipStre
     const size_t shift_lds = sizeof(double) * 2 * kShiftItems * (size_t)dp.ncoef;
     {
         KTimer kt(dp, KT_P2M, st);
-        if (dp.n_p2m_cells > 0) launch_fc(F, [&](auto fc) {
-            constexpr int FC = decltype(fc)::value;
-            const size_t lds = sizeof(double) * (size_t)kP2MStage * (dp.ncoef + 12 * FC);
-            k_p2m<FC><<<dim3(xcd_grid(dp.n_p2m_cells), (F + FC - 1) / FC), dim3(kP2MThreads), lds, st>>>(
+        if (dp.n_p2m_cells > 0) with_p2m(F, p, [&](auto fc, auto nt) {
+            constexpr int FC = decltype(fc)::value, NT = decltype(nt)::value;
+            k_p2m<FC, NT><<<dim3(xcd_grid(dp.n_p2m_cells * ((F + FC - 1) / FC))), dim3(kP2MThreads),
+                            sizeof(double) * 12 * 64 * NT, st>>>(
                 dp.p2m_cells, dp.cell_i, dp.cell_c, C, dp.tet_xyz, dp.tet_node, hp.n_tets, dp.tet_mom, M, hp.n_nodes, F,
                 p, dp.n_p2m_cells, hp.points ? 1 : 0, dp.lo, dp.Q);
             hip_check(hipGetLastError(), "k_p2m launch");
