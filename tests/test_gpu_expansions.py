@@ -34,5 +34,13 @@ def test_expansions_vs_oracle(p, leaf, F):
         g, o = T.tfmm_plan_expansions(plan, which), ref.expansions(which)[order]
         used = cells[:, count] > 0
         scale = np.abs(o).max(axis=1)
+        if which == "L":
+            # a cell's local is a sum over hundreds of source cells and may cancel: one
+            # rounding of the field moves a cell of the first case, 4000 times smaller
+            # than its neighbours, by 2.3e-12 of itself in the oracle.  Roundings are
+            # relative to the terms, which have the size of the level's locals.
+            for lv in np.unique(cells[used, 0]):
+                at_level = used & (cells[:, 0] == lv)
+                scale[at_level] = scale[at_level].max()
         assert (np.abs(g - o).max(axis=1)[used] <= 1e-12 * scale[used]).all(), which
     T.tfmm_plan_destroy(plan)
