@@ -332,7 +332,7 @@ void upload_plan(DevicePlan &dp)
         hip_check(hipMalloc(&dp.m2l_D, tb), "hipMalloc M2L table");
         B += (int64_t)tb;
         build_m2l_table(dp);
-        dp.qpad = (m2l_reduced_width(hp.p) + 3) / 4 * 4;
+        dp.qpad = (m2l_reduced_width(hp.p) + 4) / 4 * 4;  // beyond the last column step of M2L
         ensure_m2l_tiles(dp, 16);
     }
     {
@@ -365,7 +365,7 @@ void free_plan(DevicePlan &dp)
     dp.event_pool.clear();
     void *ptrs[] = {dp.tet_xyz, dp.tet_node, dp.tet_perm, dp.tgt_xyz, dp.tgt_perm, dp.tgt_leaf, dp.cell_c, dp.cell_i,
                     dp.p2m_cells, dp.m2m_cells, dp.l2l_cells, dp.p2p_blk, dp.p2p_idx, dp.quad, dp.far_rule, dp.node_lump, dp.tet_mom, dp.Q,
-                    dp.L, dp.Qt, dp.Qtf, dp.m2l_keys, dp.m2l_D, dp.m2l_Df, dp.sur_w, dp.sur_wb, dp.band_pairs, dp.band_rule, dp.topo_item,
+                    dp.L, dp.Qt ? dp.Qt - 1 : nullptr, dp.Qtf, dp.m2l_keys, dp.m2l_D, dp.m2l_Df, dp.sur_w, dp.sur_wb, dp.band_pairs, dp.band_rule, dp.topo_item,
                     dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_inc, dp.topo_edge, dp.topo_face, dp.topo_edge_w, dp.topo_face_w, dp.near_tet, dp.near_w,
                     dp.near_off, dp.near_nc, dp.near_cols, dp.near_val, dp.near_items};
     for (void *p : ptrs)
@@ -606,7 +606,7 @@ int64_t tfmm_plan_lists(tfmm_plan plan, int32_t kind, int32_t *out)
     if (kind == 3) {  // the pairs as the packed form (one field, the plan's order) schedules them
         tfmm::M2LPacks pk;
         try {
-            tfmm::build_m2l_packs(hp, hp.p <= 8 ? 128 : 64, 16, plan->dp.m2l_max_grp, pk);
+            tfmm::build_m2l_packs(hp, tfmm::m2l_pack_slots(hp.p), 16, plan->dp.m2l_max_grp, pk);
         } catch (const tfmm::PlanError &e) {
             return set_error(e.code, e.msg);
         }

@@ -989,9 +989,7 @@ __global__ __launch_bounds__(64 * kM2LWaves, 2) void k_m2l_mfma(
 //
 // Each wavefront takes a contiguous run of the item's groups (consecutive
 // groups mostly share the key).  The key's derivative row is staged in the
-// wavefront's own LDS row when the key changes; the multipoles of the next
-// group are loaded into registers while the matrix cores work on the
-// current one (two register sets, loop unrolled by two).
+// wavefront's own LDS row when the key changes.
 // ---------------------------------------------------------------------------
 __host__ __device__ constexpr int m2l_all_steps(int P)
 {
@@ -999,160 +997,188 @@ __host__ __device__ constexpr int m2l_all_steps(int P)
     for (int rt = 0; rt < m2l_nrt(P); ++rt) s += m2l_ks(P, rt);
     return s;
 }
-// LDS accumulator slots (target cell x field) of one packed block
-__host__ __device__ constexpr int m2lp_slots(int P) { return P <= 8 ? 128 : 64; }
-constexpr int kM2LPWaves = 4;
+// One workgroup a CU, with a block of m2l_pack_slots(P) accumulator slots (target
+// cell x field) in its LDS: the larger block fills the matrix-core columns better
+// (40^3 cube: 0.91 with 256 slots, 0.85 with 128).  Two wavefronts a SIMD keep a
+// whole group's multipoles in registers; three spill (2.34 against 2.16 ms).
+constexpr int kM2LPWaves = 8;
 
-template <typename T, int P>
-__global__ __launch_bounds__(64 * kM2LPWaves, P <= 8 ? 2 : 1) void k_m2l_pack(
+// Column steps of the packed form.  A step contracts four columns n, one for
+// each quarter kq of the wavefront; row tile rt takes the first m2l_ks(P, rt)
+// steps, so within a run of steps that the same row tiles take (a segment) the
+// columns may be dealt freely: quarter kq takes consecutive ones, and a lane
+// loads its column's multipoles two at a time (a load of a wavefront touches the
+// lines of 16 sources, whatever its width: 2.50 ms with one at a time, 2.34 with
+// two; 40^3 cube, three wavefronts a SIMD).
+__host__ __device__ constexpr int m2lp_seg_end(int P, int ks)  // end of the segment of step ks
+{
+    int e = m2l_ks(P, 0);
+    for (int rt = 1; rt < m2l_nrt(P); ++rt)
+        if (m2l_ks(P, rt) > ks && m2l_ks(P, rt) < e) e = m2l_ks(P, rt);
+    return e;
+}
+__host__ __device__ constexpr int m2lp_seg_begin(int P, int ks)
+{
+    int b = 0;
+    for (int rt = 0; rt < m2l_nrt(P); ++rt)
+        if (m2l_ks(P, rt) <= ks && m2l_ks(P, rt) > b) b = m2l_ks(P, rt);
+    return b;
+}
+// n = m2lp_col0 + m2lp_len * kq
+__host__ __device__ constexpr int m2lp_len(int P, int ks) { return m2lp_seg_end(P, ks) - m2lp_seg_begin(P, ks); }
+__host__ __device__ constexpr int m2lp_col0(int P, int ks) { return 1 + 3 * m2lp_seg_begin(P, ks) + ks; }
+// whether step ks is loaded together with the step before it
+__host__ __device__ constexpr bool m2lp_second(int P, int ks) { return (ks - m2lp_seg_begin(P, ks)) % 2 == 1; }
+// whether step ks + 1 is loaded together with step ks
+__host__ __device__ constexpr bool m2lp_first(int P, int ks) { return !m2lp_second(P, ks) && ks + 1 < m2lp_seg_end(P, ks); }
+
+template <int P>
+__global__ __launch_bounds__(64 * kM2LPWaves, 2) void k_m2l_pack(
     const int32_t *__restrict__ item, int nitems, const int32_t *__restrict__ blk_cells, int nb, int tpg,
     const int32_t *__restrict__ grp_key, const int32_t *__restrict__ grp_src, const uint8_t *__restrict__ grp_slot,
-    const int32_t *__restrict__ keys, const T *__restrict__ Dtab, int dstr, const T *__restrict__ Qr, int qpad,
+    const int32_t *__restrict__ keys, const double *__restrict__ Dtab, int dstr, const double *__restrict__ Qr, int qpad,
     int64_t C, int fpt, int F, double *__restrict__ Lr, int lrs)
 {
-    using v4 = typename Mfma<T>::v4;
+    using v4 = Mfma<double>::v4;
+    constexpr int NW = kM2LPWaves;
     constexpr int NR = nr_of(P), ND = nd_of(P), NROW = m2l_nrows(P), NRT = m2l_nrt(P), KS0 = m2l_ks(P, 0);
-    constexpr int NS = m2l_all_steps(P), NSLOT = m2lp_slots(P), DSTR = ND + 1;
+    constexpr int NS = m2l_all_steps(P), NSLOT = m2l_pack_slots(P), DSTR = ND + 1;
     // odd row stride of the accumulators: the 16 columns of an output
     // register (the same row of 16 slots) fall in 16 different bank pairs
     // when their slots differ mod 16, as the packer arranges
     constexpr int LSTR = NROW | 1;
     __shared__ double s_L[NSLOT * LSTR];
-    __shared__ T s_D[kM2LPWaves][2][DSTR];
+    __shared__ double s_D[NW][DSTR];
     const int it = blockIdx.x;
     if (it >= nitems) return;
     // the wavefront index made visibly uniform: the group bounds, keys and
-    // the key-change branch then live in scalar registers, and reading a key
-    // does not wait for the vector loads of the prefetched multipoles
+    // the key-change branch then live in scalar registers
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int col = lane & 15, pair = col / fpt, fsub = col % fpt, field = (int)blockIdx.y * fpt + fsub;
+    const int col = lane & 15, kq = lane >> 4, pair = col / fpt, fsub = col % fpt, field = (int)blockIdx.y * fpt + fsub;
     const bool fok = field < F;
     for (int i = tid; i < NSLOT * LSTR; i += blockDim.x) s_L[i] = 0.0;
-    if (lane < 2) s_D[w][lane][ND] = (T)0;  // the zero slot of each row
-    // this lane's table index of the A operand of every step (ks-major,
-    // row tiles inner; the zero slot outside |n| + |m| <= P)
-    int didx[NS];
+    double *D = s_D[w];
+    if (lane == 0) D[ND] = 0.0;  // the zero slot
+    // this lane's place in the derivative row of the A operand of every step
+    // (ks-major, row tiles inner; the zero slot outside |n| + |m| <= P)
+    const double *ap[NS];
     {
         int s = 0;
 #pragma unroll
         for (int ks = 0; ks < KS0; ++ks) {
-            const int n = 1 + 4 * ks + (lane >> 4);
+            const int n = m2lp_col0(P, ks) + m2lp_len(P, ks) * kq;
 #pragma unroll
             for (int rt = 0; rt < NRT; ++rt)
                 if (ks < m2l_ks(P, rt)) {
-                    const int m = 16 * rt + (lane & 15);
+                    const int m = 16 * rt + col;
                     int di = ND;
                     if (m < NROW && n < NR && c_red.r[m][3] + c_red.r[n][3] <= P)
                         di = didx_of(c_red.r[m][0] + c_red.r[n][0], c_red.r[m][1] + c_red.r[n][1],
                                      c_red.r[m][2] + c_red.r[n][2]);
-                    didx[s++] = di;
+                    ap[s++] = D + di;
                 }
         }
     }
     __syncthreads();
     const int blk = item[3 * it], g0 = item[3 * it + 1], g1 = item[3 * it + 2];
-    const int wg0 = g0 + (int)((int64_t)(g1 - g0) * w / kM2LPWaves);
-    const int wg1 = g0 + (int)((int64_t)(g1 - g0) * (w + 1) / kM2LPWaves);
-    const T *qf = Qr + (int64_t)(fok ? field : 0) * C * qpad;
+    const int wg0 = g0 + (int)((int64_t)(g1 - g0) * w / NW), wg1 = g0 + (int)((int64_t)(g1 - g0) * (w + 1) / NW);
+    const double *qf = Qr + (int64_t)(fok ? field : 0) * C * qpad;
     constexpr int DREG = (ND + 63) / 64;
-    struct Ops {
-        T b[KS0], d[DREG];
-        int slot, key, dl;
-        bool ok, newkey;
-    };
-    // loads of group g (the derivative row too when its key differs from
-    // the previous group's): clamped addresses, masked when used
-    auto fetch = [&](Ops &o, int g) {
-        const int src = grp_src[(int64_t)g * tpg + pair];
-        o.slot = grp_slot[(int64_t)g * tpg + pair];
-        o.ok = fok && src >= 0;
-        const T *q = qf + (int64_t)(o.ok ? src : 0) * qpad;
-#pragma unroll
-        for (int ks = 0; ks < KS0; ++ks) {
-            const int n = 1 + 4 * ks + (lane >> 4);
-            o.b[ks] = q[n < NR ? n : NR - 1];
-        }
-        o.key = grp_key[g];
-        o.newkey = g == wg0 || grp_key[g - 1] != o.key;  // uniform over the wavefront
-        if (o.newkey) {
-            o.dl = keys[4 * o.key];
-#pragma unroll
-            for (int j = 0; j < DREG; ++j) {
-                const int k = lane + 64 * j;
-                o.d[j] = Dtab[(int64_t)o.key * dstr + (k < ND ? k : ND - 1)];
+    // Software pipeline, in one register set: the sources of group g + 2 are
+    // on their way while group g runs, and the multipoles of group g + 1 are
+    // loaded into the registers of group g as its matrix steps are issued.
+    // Loads go to in-bounds addresses unconditionally (a row of Qr holds
+    // qpad > 4 KS0 entries) and are masked when used.
+    if (wg0 < wg1) {
+        auto source = [&](int g) { return grp_src[(int64_t)min(g, wg1 - 1) * tpg + pair]; };
+        auto place = [&](int g) { return (int)grp_slot[(int64_t)min(g, wg1 - 1) * tpg + pair]; };
+        // multipoles of step ks, or of steps ks - 1 and ks once both are used
+        auto load = [&](double (&b)[KS0], const double *q, int ks) {
+            using two = double __attribute__((ext_vector_type(2), aligned(8)));
+            if (m2lp_first(P, ks)) return;
+            if (m2lp_second(P, ks)) {
+                const two v = *reinterpret_cast<const two *>(q + m2lp_col0(P, ks - 1) + m2lp_len(P, ks) * kq);
+                b[ks - 1] = v.x;
+                b[ks] = v.y;
+            } else {
+                b[ks] = q[m2lp_col0(P, ks) + m2lp_len(P, ks) * kq];
             }
-        }
-    };
-    int buf = 0, dl = 0;
-    auto run = [&](const Ops &o, int g) {
-        if (o.newkey) {
-            buf ^= 1;
-            T *D = s_D[w][buf];
+        };
+        double b[KS0], d[DREG];
+        int src = source(wg0), slot = place(wg0), src1 = source(wg0 + 1), slot1 = place(wg0 + 1);
+        {
+            const double *q = qf + (int64_t)(fok && src >= 0 ? src : 0) * qpad;
 #pragma unroll
-            for (int j = 0; j < DREG; ++j) {
-                const int k = lane + 64 * j;
-                if (k < ND) D[k] = o.d[j];
-            }
-            dl = o.dl;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            for (int ks = 0; ks < KS0; ++ks) load(b, q, ks);
+        }
+        int key = grp_key[wg0], dl = keys[4 * key];
+        auto row = [&](int k) {
+#pragma unroll
+            for (int j = 0; j < DREG; ++j) d[j] = Dtab[(int64_t)k * dstr + min(lane + 64 * j, ND - 1)];
+        };
+        auto stage = [&]() {  // a wavefront's LDS operations keep their order
+#pragma unroll
+            for (int j = 0; j < DREG; ++j)
+                if (lane + 64 * j < ND) D[lane + 64 * j] = d[j];
+        };
+        row(key);
+        stage();
+        for (int g = wg0; g < wg1; ++g) {
+            const bool ok = fok && src >= 0;
+            const int src2 = source(g + 2), slot2 = place(g + 2);
+            const int next = grp_key[min(g + 1, wg1 - 1)];
+            if (next != key) row(next);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
-        const T *D = s_D[w][buf];
-        // B operand: the multipoles times 2^(-dl |n|) (exact).  Columns of
-        // empty slots and rows n >= NR hold finite values that meet zero A
-        // entries or are never added out, so they need no masking.
-        T b[KS0];
-        if (dl == 0) {  // uniform over the wavefront
+            // B operand: the multipoles times 2^(-dl |n|) (exact).  Columns of
+            // empty slots and rows n >= NR hold finite values that meet zero A
+            // entries or are never added out, so they need no masking.
+            if (dl != 0) {  // uniform over the wavefront
 #pragma unroll
-            for (int ks = 0; ks < KS0; ++ks) b[ks] = o.b[ks];
-        } else {
+                for (int ks = 0; ks < KS0; ++ks) {
+                    const int n = m2lp_col0(P, ks) + m2lp_len(P, ks) * kq;
+                    const int deg = (int)sqrtf((float)n);  // exact: degree d starts at d^2
+                    b[ks] = ldexp(b[ks], -dl * deg);
+                }
+            }
+            const double *q = qf + (int64_t)(fok && src1 >= 0 ? src1 : 0) * qpad;
+            v4 acc[NRT], acc0[2] = {v4{0, 0, 0, 0}, v4{0, 0, 0, 0}};
+#pragma unroll
+            for (int rt = 0; rt < NRT; ++rt) acc[rt] = v4{0, 0, 0, 0};
+            int s = 0;
 #pragma unroll
             for (int ks = 0; ks < KS0; ++ks) {
-                const int n = 1 + 4 * ks + (lane >> 4);
-                const int deg = (int)sqrtf((float)n);  // exact: the degree block of n starts at deg^2
-                b[ks] = (T)ldexp(o.b[ks], -dl * deg);
-            }
-        }
-        v4 acc[NRT], acc0[2] = {v4{0, 0, 0, 0}, v4{0, 0, 0, 0}};
 #pragma unroll
-        for (int rt = 0; rt < NRT; ++rt) acc[rt] = v4{0, 0, 0, 0};
-        int s = 0, r0 = 0;
-#pragma unroll
-        for (int ks = 0; ks < KS0; ++ks)
-#pragma unroll
-            for (int rt = 0; rt < NRT; ++rt)
-                if (ks < m2l_ks(P, rt)) {
-                    const T a = D[didx[s++]];
-                    if (rt == 0) {
-                        acc0[r0 & 1] = Mfma<T>::mma(a, b[ks], acc0[r0 & 1]);
-                        ++r0;
-                    } else {
-                        acc[rt] = Mfma<T>::mma(a, b[ks], acc[rt]);
+                for (int rt = 0; rt < NRT; ++rt)
+                    if (ks < m2l_ks(P, rt)) {
+                        const double a = *ap[s++];
+                        if (rt == 0)
+                            acc0[ks & 1] = Mfma<double>::mma(a, b[ks], acc0[ks & 1]);
+                        else
+                            acc[rt] = Mfma<double>::mma(a, b[ks], acc[rt]);
                     }
-                }
-        acc[0] = acc0[0] + acc0[1];
-        if (o.ok) {
-            double *Ls = s_L + (o.slot * fpt + fsub) * LSTR;
-#pragma unroll
-            for (int rt = 0; rt < NRT; ++rt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int m = 16 * rt + Mfma<T>::row(lane, r);
-                    if (m < NROW) atomicAdd(&Ls[m], (double)acc[rt][r]);
-                }
-        }
-    };
-    if (wg0 < wg1) {
-        Ops oa, ob;
-        fetch(oa, wg0);
-        for (int g = wg0; g < wg1; g += 2) {
-            if (g + 1 < wg1) fetch(ob, g + 1);
-            run(oa, g);
-            if (g + 1 < wg1) {
-                if (g + 2 < wg1) fetch(oa, g + 2);
-                run(ob, g + 1);
+                load(b, q, ks);
             }
+            acc[0] = acc0[0] + acc0[1];
+            if (next != key) {
+                key = next;
+                dl = keys[4 * key];
+                stage();
+            }
+            if (ok) {
+                double *Ls = s_L + (slot * fpt + fsub) * LSTR;
+#pragma unroll
+                for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int m = 16 * rt + Mfma<double>::row(lane, r);
+                        if (m < NROW) atomicAdd(&Ls[m], acc[rt][r]);
+                    }
+            }
+            src = src1;
+            slot = slot1;
+            src1 = src2;
+            slot1 = slot2;
         }
     }
     __syncthreads();
@@ -3386,38 +3412,21 @@ void launch_m2l_t(DevicePlan &dp, const DevicePlan::Tiles &tl, const T *D, const
     }
 }
 
-template <typename T, int P>
-void launch_m2l_pack_p(DevicePlan &dp, const DevicePlan::Packs &k, const T *D, const T *Qt, int fpt, int32_t F,
-                       hipStream_t st)
+// The translations of one pack list at order p (the plan's or a level's).
+void launch_m2l_pack(DevicePlan &dp, const DevicePlan::Packs &k, int fpt, int32_t F, hipStream_t st, int p)
 {
     const HostPlan &hp = dp.hp;
     if (k.nitems == 0) return;
-    if (k.nb * fpt != m2lp_slots(P) || k.tpg * fpt != 16 || k.p != P)
+    if (k.nb * fpt != m2l_pack_slots(p) || k.tpg * fpt != 16 || k.p != p)
         throw DeviceError{"M2L packs do not match the translation order"};
     const unsigned groups = (unsigned)((F + fpt - 1) / fpt);
-    k_m2l_pack<T, P><<<dim3((unsigned)k.nitems, groups), dim3(64 * kM2LPWaves), 0, st>>>(
-        k.item, k.nitems, k.blk_cells, k.nb, k.tpg, k.grp_key, k.grp_src, k.grp_slot, dp.m2l_keys, D,
-        m2l_table_width(hp.p), Qt, dp.qpad, (int64_t)hp.cells.size(), fpt, F, dp.Lr, m2l_nrows(hp.p));
+    with_order(p, [&](auto pc) {
+        constexpr int P = decltype(pc)::value;
+        k_m2l_pack<P><<<dim3((unsigned)k.nitems, groups), dim3(64 * kM2LPWaves), 0, st>>>(
+            k.item, k.nitems, k.blk_cells, k.nb, k.tpg, k.grp_key, k.grp_src, k.grp_slot, dp.m2l_keys, dp.m2l_D,
+            m2l_table_width(hp.p), dp.Qt, dp.qpad, (int64_t)hp.cells.size(), fpt, F, dp.Lr, m2l_nrows(hp.p));
+    });
     hip_check(hipGetLastError(), "k_m2l_pack launch");
-}
-
-template <typename T>
-void launch_m2l_pack_t(DevicePlan &dp, const DevicePlan::Packs &k, const T *D, const T *Qt, int fpt, int32_t F,
-                       hipStream_t st, int p)
-{
-    switch (p) {
-    case 1: launch_m2l_pack_p<T, 1>(dp, k, D, Qt, fpt, F, st); break;
-    case 2: launch_m2l_pack_p<T, 2>(dp, k, D, Qt, fpt, F, st); break;
-    case 3: launch_m2l_pack_p<T, 3>(dp, k, D, Qt, fpt, F, st); break;
-    case 4: launch_m2l_pack_p<T, 4>(dp, k, D, Qt, fpt, F, st); break;
-    case 5: launch_m2l_pack_p<T, 5>(dp, k, D, Qt, fpt, F, st); break;
-    case 6: launch_m2l_pack_p<T, 6>(dp, k, D, Qt, fpt, F, st); break;
-    case 7: launch_m2l_pack_p<T, 7>(dp, k, D, Qt, fpt, F, st); break;
-    case 8: launch_m2l_pack_p<T, 8>(dp, k, D, Qt, fpt, F, st); break;
-    case 9: launch_m2l_pack_p<T, 9>(dp, k, D, Qt, fpt, F, st); break;
-    case 10: launch_m2l_pack_p<T, 10>(dp, k, D, Qt, fpt, F, st); break;
-    default: throw DeviceError{"unsupported expansion order"};
-    }
 }
 
 // Scaled multipoles, then the translations, in the plan's M2L precision.
@@ -3427,6 +3436,17 @@ int m2l_fpt(int32_t F)
     int fpt = 1;
     while (fpt * 2 <= std::min<int32_t>(F, 16)) fpt *= 2;
     return fpt;
+}
+
+// Field width of the packed form for F fields: the width whose passes carry the
+// fewest padded fields, the widest among equals.  (5 fields on a 21^3 cube: two
+// passes of 4 take 1.37 ms, five of 1 1.01.)
+int m2l_pack_fpt(int32_t F)
+{
+    int best = 1;
+    for (int fpt = 2; fpt <= 8; fpt *= 2)
+        if ((F + fpt - 1) / fpt * fpt <= (F + best - 1) / best * best) best = fpt;
+    return best;
 }
 
 // Whether M2L runs in the packed form: FP64 translations of fewer than 16
@@ -3476,11 +3496,12 @@ void run_m2l(DevicePlan &dp, int32_t F, hipStream_t st)
     }
     hip_check(hipGetLastError(), "k_qreduce launch");
     if (m2l_packed(dp, F)) {
+        const int fpt = m2l_pack_fpt(F);
         if (dp.lr_cap < F) throw DeviceError{"M2L buffers not prepared"};
         const int lrs = m2l_nrows(hp.p);
         fill(dp.Lr, (int64_t)F * C * lrs, 0.0, st);
         auto go = [&](const DevicePlan::Packs &k, int p) {
-            launch_m2l_pack_t<double>(dp, k, dp.m2l_D, dp.Qt, fpt, F, st, p);
+            launch_m2l_pack(dp, k, fpt, F, st, p);
         };
         if (!dp.level_orders) {
             go(dp.m2l_packs[m2l_pack_slot(fpt)], hp.p);
@@ -3739,10 +3760,17 @@ void free_m2l_packs(DevicePlan &dp)
 }
 
 // Packs of fpt fields for translations of order p (all levels, or one).
-static void build_packs(DevicePlan &dp, int fpt, int p, int only_level, DevicePlan::Packs &k)
+static void build_packs(DevicePlan &dp, int fpt, int32_t F, int p, int only_level, DevicePlan::Packs &k)
 {
+    // Work items of at most m2l_max_grp groups, fewer on small meshes: 512 items
+    // are two rounds of the chip's workgroups; 48 groups, six a wavefront, are the
+    // least that carry an item's clearing and summing up.  (M2L of an 8^3 cube, 6,400
+    // groups: 64 us in items of 256, 36 in items of 48.  A batch of 170,000 groups:
+    // .37 ms in items of 256, .45 in items of 166.)
+    const int64_t groups = (int64_t)dp.hp.m2l_src.size() * fpt / 16 * ((F + fpt - 1) / fpt);
+    const int cut = (int)std::min<int64_t>(dp.m2l_max_grp, std::max<int64_t>(48, groups / 512));
     M2LPacks h;
-    build_m2l_packs(dp.hp, m2lp_slots(p) / fpt, 16 / fpt, dp.m2l_max_grp, h, only_level);
+    build_m2l_packs(dp.hp, m2l_pack_slots(p) / fpt, 16 / fpt, cut, h, only_level);
     auto up = [&](const auto &v, auto *&d) {
         using E = typename std::decay_t<decltype(v)>::value_type;
         const size_t b = sizeof(E) * std::max<size_t>(v.size(), 1);
@@ -3771,13 +3799,13 @@ static void ensure_m2l_packs(DevicePlan &dp, int32_t F)
 {
     if (!m2l_packed(dp, F)) return;
     const HostPlan &hp = dp.hp;
-    const int fpt = m2l_fpt(F);
+    const int fpt = m2l_pack_fpt(F);
     if (!dp.level_orders) {
         DevicePlan::Packs &k = dp.m2l_packs[m2l_pack_slot(fpt)];
         if (k.nb == 0 || k.max_grp != dp.m2l_max_grp || k.p != hp.p) {
             ++dp.schedule_gen;
             free_packs(dp, k);
-            build_packs(dp, fpt, hp.p, -1, k);
+            build_packs(dp, fpt, F, hp.p, -1, k);
         }
     } else {
         bool ok = dp.lvl_packs.size() == (size_t)hp.depth + 1;
@@ -3789,7 +3817,7 @@ static void ensure_m2l_packs(DevicePlan &dp, int32_t F)
             ++dp.schedule_gen;
             for (auto &k : dp.lvl_packs) free_packs(dp, k);
             dp.lvl_packs.assign((size_t)hp.depth + 1, DevicePlan::Packs{});
-            for (int lv = 0; lv <= hp.depth; ++lv) build_packs(dp, fpt, dp.lo.q[lv], lv, dp.lvl_packs[lv]);
+            for (int lv = 0; lv <= hp.depth; ++lv) build_packs(dp, fpt, F, dp.lo.q[lv], lv, dp.lvl_packs[lv]);
         }
     }
     if (dp.lr_cap < F) {
@@ -3887,10 +3915,11 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
         }
     } else if (dp.qt_cap < F) {
         ++dp.schedule_gen;
-        if (dp.Qt) (void)hipFree(dp.Qt);
+        if (dp.Qt) (void)hipFree(dp.Qt - 1);
         dp.Qt = nullptr;
         dp.qt_cap = 0;
-        hip_check(hipMalloc(&dp.Qt, sizeof(double) * (size_t)F * C * dp.qpad), "hipMalloc Qt");
+        hip_check(hipMalloc(&dp.Qt, sizeof(double) * ((size_t)F * C * dp.qpad + 2)), "hipMalloc Qt");
+        dp.Qt += 1;  // entry 1 of every row (the first that counts) on a 16-byte boundary
         dp.qt_cap = F;
     }
 }

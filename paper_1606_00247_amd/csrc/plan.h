@@ -95,6 +95,8 @@ struct M2LPacks {
     std::vector<int32_t> grp_src;    // [ngrp][tpg] source cell (-1: empty)
     std::vector<uint8_t> grp_slot;   // [ngrp][tpg] target slot in the block
 };
+// LDS accumulator slots (target cell x field) of one block at order p.
+constexpr int m2l_pack_slots(int p) { return p <= 8 ? 256 : 128; }
 void build_m2l_packs(const HostPlan &hp, int nb, int tpg, int max_grp, M2LPacks &out, int only_level = -1);
 
 // Mesh entities of the near-field source blocks.  Each P2P block (<= 64 tets
