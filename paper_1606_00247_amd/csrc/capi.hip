@@ -340,12 +340,7 @@ void upload_plan(DevicePlan &dp)
         std::vector<double> q = simplex_rule(hp.p, &np);
         dp.nq = np;
         dp.quad = dev_upload(q, B);
-        std::vector<double> far;
-        for (int deg : kFarDeg) {
-            int nf = 0;
-            std::vector<double> r = simplex_rule(deg, &nf);
-            far.insert(far.end(), r.begin(), r.end());
-        }
+        const std::vector<double> far = far_tables();
         dp.far_rule = dev_upload(far, B);
         const size_t mb = sizeof(double) * std::max<size_t>(1, (size_t)T * dp.ncoef);
         hip_check(hipMalloc(&dp.tet_mom, mb), "hipMalloc tet moments");

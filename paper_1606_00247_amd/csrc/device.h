@@ -18,13 +18,31 @@ inline int m2l_table_width(int p) { return 1 + 3 * p * (p + 1) / 2; }
 
 // Far pairs of the direct sum (targets at least kFarRatio[0] longest edges
 // from a tet's centroid) are integrated by collapsed Gauss-Jacobi rules of
-// degree 13, 11, 9 and 7 (7^3, 6^3, 5^3 and 4^3 points, concatenated at
-// kFarOff) for the distance bands [3, 6), [6, 12), [12, 24) and [24, inf)
-// diameters.
-constexpr int kFarBands = 4;
-constexpr int kFarDeg[kFarBands] = {13, 11, 9, 7};
-constexpr int kFarOff[kFarBands + 1] = {0, 343, 559, 684, 748};
-constexpr double kFarRatio[kFarBands] = {3.0, 6.0, 12.0, 24.0};
+// kFarPts[i]^3 points from kFarRatio[i] longest edges on.  A rule's error falls
+// as (0.3 diameters / distance)^(2 n); relative to |M| V / d^2 it is, at most over
+// tet shapes from needles to flat and over directions, 2.7e-14 at 3 (7^3 points),
+// 6.7e-15 at 5 (6^3), 8.5e-15 at 9 (5^3) and 8.2e-15 at 24 (4^3).
+constexpr int kFarRules = 4;
+constexpr int kFarPts[kFarRules] = {7, 6, 5, 4};
+constexpr double kFarRatio[kFarRules] = {3.0, 5.0, 9.0, 24.0};
+// One-dimensional nodes and weight products of a rule of n^3 points: n rows of
+// FarC (weight 1), then n rows of FarB (weight 1 - t), then n of FarA ((1 - t)^2).
+struct FarC {
+    double c, w, wc, wcc;
+};
+struct FarB {
+    double b, u, w, wb, wbb, wu, wbu, wuu;  // u = 1 - b
+};
+struct FarA {
+    double a, t, w, wa, waa, wt, wat, wtt;  // t = 1 - a
+};
+constexpr int kFarRow = 20;  // doubles of the three rows of one node
+constexpr int far_offset(int rule)  // of rule's table, in doubles
+{
+    int o = 0;
+    for (int i = 0; i < rule; ++i) o += kFarRow * kFarPts[i];
+    return o;
+}
 
 // Expansion order of every octree level (levels beyond the tree unused),
 // passed to kernels by value.
@@ -197,7 +215,7 @@ struct DevicePlan {
     double *quad = nullptr;
     int32_t nq = 0;
     // far-pair rules of the direct sum (degrees 11, 9, 7 concatenated, rows as quad)
-    double *far_rule = nullptr;
+    double *far_rule = nullptr;  // tables of the direct sum's far rules (far_offset)
     // lumped node volumes (sum of V_T / 4 over the tets of a node), built on
     // the first nodal-field request
     double *node_lump = nullptr;
@@ -334,5 +352,7 @@ void run_band_pairs(DevicePlan &dp, int mode, const double *M, int32_t F, double
 // Collapsed Gauss-Jacobi rule on the unit simplex exact to total degree `deg`:
 // rows lambda1, lambda2, lambda3, weight (weights sum to 1/6).
 std::vector<double> simplex_rule(int deg, int *npts);
+// One-dimensional tables of the direct sum's far rules, at far_offset(rule).
+std::vector<double> far_tables();
 
 }  // namespace tfmm

@@ -103,6 +103,16 @@ __device__ __forceinline__ int xcd_item(int n)
     return item < n ? item : -1;
 }
 
+// Memory that no thread writes during the launch: uniform reads of it go to
+// the scalar unit whatever the compiler can prove about aliasing.
+template <typename T>
+using ScalarMem = T __attribute__((address_space(4)));
+template <typename T>
+__device__ __forceinline__ const ScalarMem<T> *scalar_mem(const T *p)
+{
+    return (const ScalarMem<T> *)p;
+}
+
 // cell int fields
 enum { CI_TBEG = 0, CI_TEND, CI_XBEG, CI_XEND, CI_CBEG, CI_NCHILD, CI_PARENT, CI_LEVEL, CI_N };
 
@@ -1574,37 +1584,117 @@ __global__ __launch_bounds__(p2p_threads(FCH, WIDE), 2) void k_p2p(const int32_t
 // (d/diam)^4 eps (d = |x - centroid|, diam = the longest edge).  From 3
 // diameters on the pair is instead integrated by a collapsed Gauss-Jacobi
 // rule of the integrand of eq. approx1,
-//   4 pi u_T(x) = 6|V| sum_q w_q M(y_q) . (x - y_q) / |x - y_q|^3
-//               = 6|V| sum_i M_i . K_i,
-//   K_i = sum_q w_q lambda_i(q) (x - y_q) / |x - y_q|^3,
-// K independent of the field, with the rules of degree 13, 11, 9 and 7 for
-// the bands [3, 6), [6, 12), [12, 24) and [24, inf) diameters (rule error
-// below ~1e-14 of |M| V / (4 pi d^2)).  One workgroup of 256 threads per DT consecutive tets
-// staged in LDS; every thread takes targets lane, lane + 256, ... and adds
-// its sums over the staged tets atomically.
+//   4 pi u_T(x) = 6|V| sum_q w_q M(y_q) . (x - y_q) / |x - y_q|^3.
+// With y = v_0 + sum_i lambda_i e_i, M = M_0 + sum_i lambda_i (M_i - M_0) this is
+//   6|V| (M_0 . S + sum_i (M_i - M_0) . K_i),
+//   S = x' A_0 - sum_j A_j e_j,  K_i = x' A_i - sum_j A_ij e_j,  x' = x - v_0,
+// of the ten moments A_0, A_i, A_ij of |x - y_q|^-3 with w_q (1, lambda_i,
+// lambda_i lambda_j): independent of the field and summed loop by loop of the
+// collapsed rule (far_moments), three multiply-adds a point and nothing read
+// but one-dimensional tables in scalar registers.
+//
+// Bound by FP64 issue: 15 slots a point (2 for the squared distance, 4 for the
+// hardware estimate of its root's reciprocal, 6 to refine and cube it, 3 for the
+// moments) and 20 for each row of points.  10,368 tets, 2,197 targets, 2 fields:
+// 15.8 ms with a rule per lane and 40 slots a point, now 3.2; 5 fields: 31.8 in
+// two passes, now 3.4.
+//
+// A workgroup stages DT consecutive tets in LDS and takes 256 targets at a time:
+// the pairs are sorted by class (rule, or closed form) and its wavefronts take 64
+// pairs of one class after another, the most points first, so that no lane waits
+// for another's larger rule (5,700 slots a pair with the wavefront's largest, 4,000
+// sorted) and the loops stay uniform.  The sums are kept in LDS and added to u once
+// a target and workgroup.
 // ---------------------------------------------------------------------------
-struct FarTet {
+struct DirectTet {
     double c[3];     // centroid
     double id2;      // 1 / diam^2
     double e[3][3];  // v_1 - v_0, v_2 - v_0, v_3 - v_0
     double vol6;     // 6 |V|
 };
-__host__ __device__ constexpr int direct_stage(int FCH) { return FCH >= 32 ? 4 : (FCH >= 16 ? 8 : 16); }
+constexpr int kDirectFieldsMax = 16;
+__host__ __device__ constexpr int direct_stage(int FCH) { return FCH >= 16 ? 4 : 16; }
+
+// Moments m = (A_0, A_1, A_2, A_3, A_11, A_12, A_13, A_22, A_23, A_33) of one
+// tet (edge vectors e[i] = v_(i+1) - v_0) at x = target - v_0 by the rule of N^3
+// points lambda = (a, (1-a) b, (1-a)(1-b) c).
+template <int N>
+__device__ __forceinline__ void far_moments(const double (&x)[3], const double (&e)[3][3], const double *table,
+                                            double (&m)[10])
+{
+    const ScalarMem<FarC> *C = (const ScalarMem<FarC> *)scalar_mem(table);
+    const ScalarMem<FarB> *Bt = (const ScalarMem<FarB> *)(scalar_mem(table) + 4 * N);
+    const ScalarMem<FarA> *At = (const ScalarMem<FarA> *)(scalar_mem(table) + 12 * N);
+    const double e33 = e[2][0] * e[2][0] + e[2][1] * e[2][1] + e[2][2] * e[2][2];
+    const double k0 = scalar_const<dbits(1.5)>(), k1 = vector_const<dbits(1.875)>();
+#pragma unroll
+    for (int i = 0; i < 10; ++i) m[i] = 0.0;
+#pragma unroll 1
+    for (int ia = 0; ia < N; ++ia) {
+        const ScalarMem<FarA> &a = At[ia];
+        const double xa[3] = {fma(-a.a, e[0][0], x[0]), fma(-a.a, e[0][1], x[1]), fma(-a.a, e[0][2], x[2])};
+        const double t = a.t, e2[3] = {t * e[1][0], t * e[1][1], t * e[1][2]};
+        double b0 = 0.0, b1 = 0.0, b2 = 0.0, c0 = 0.0, c1 = 0.0, d0 = 0.0;
+#pragma unroll 1
+        for (int ib = 0; ib < N; ++ib) {
+            const ScalarMem<FarB> &b = Bt[ib];
+            const double xb[3] = {fma(-b.b, e2[0], xa[0]), fma(-b.b, e2[1], xa[1]), fma(-b.b, e2[2], xa[2])};
+            // |xb - s c e_3|^2 = alpha + c (beta + c gamma)
+            const double s = t * b.u;
+            const double alpha = fma(xb[0], xb[0], fma(xb[1], xb[1], xb[2] * xb[2]));
+            const double beta = -2.0 * s * fma(xb[0], e[2][0], fma(xb[1], e[2][1], xb[2] * e[2][2]));
+            const double gamma = s * s * e33;
+            double g0 = 0.0, g1 = 0.0, g2 = 0.0;
+#pragma unroll
+            for (int ic = 0; ic < N; ++ic) {
+                const ScalarMem<FarC> &c = C[ic];
+                const double r2 = fma(c.c, fma(c.c, gamma, beta), alpha);
+                // r^-3 = y^3 (1 - h)^(-3/2), y^2 = (1 - h) / r^2, |h| < 2^-20
+                const double y = __builtin_amdgcn_rsq(r2), y2 = y * y, y3 = y2 * y;
+                const double h = fma(-r2, y2, 1.0);
+                const double g = fma(y3, h * fma_sv(h, k1, k0), y3);
+                g0 = fma(g, c.w, g0);
+                g1 = fma(g, c.wc, g1);
+                g2 = fma(g, c.wcc, g2);
+            }
+            b0 = fma(g0, b.w, b0);
+            b1 = fma(g0, b.wb, b1);
+            b2 = fma(g0, b.wbb, b2);
+            c0 = fma(g1, b.wu, c0);
+            c1 = fma(g1, b.wbu, c1);
+            d0 = fma(g2, b.wuu, d0);
+        }
+        m[0] = fma(b0, a.w, m[0]);
+        m[1] = fma(b0, a.wa, m[1]);
+        m[2] = fma(b1, a.wt, m[2]);
+        m[3] = fma(c0, a.wt, m[3]);
+        m[4] = fma(b0, a.waa, m[4]);
+        m[5] = fma(b1, a.wat, m[5]);
+        m[6] = fma(c0, a.wat, m[6]);
+        m[7] = fma(b2, a.wtt, m[7]);
+        m[8] = fma(c1, a.wtt, m[8]);
+        m[9] = fma(d0, a.wtt, m[9]);
+    }
+}
 
 template <int FCH>
-__global__ __launch_bounds__(256, 2) void k_direct(int nblk, int64_t T, const double *__restrict__ tet_xyz,
+__global__ __launch_bounds__(256, 3) void k_direct(int nblk, int64_t T, const double *__restrict__ tet_xyz,
                                                 const int32_t *__restrict__ tet_node,
                                                 const double *__restrict__ tgt_xyz,
                                                 const int32_t *__restrict__ tgt_perm, int64_t N,
-                                                const double *__restrict__ M, int64_t n_nodes, int f0,
-                                                const double *__restrict__ rule, double *__restrict__ u)
+                                                const double *__restrict__ M, int64_t n_nodes, int f0, int F,
+                                                const double *__restrict__ rules, double *__restrict__ u)
 {
     constexpr int DT = direct_stage(FCH);
     static_assert(DT * FCH <= 256, "one thread per staged tet and field");
     __shared__ TetGeom s_g[DT];
     __shared__ TetField s_f[DT][FCH];
-    __shared__ FarTet s_t[DT];
-    __shared__ double s_m[DT][FCH][12];
+    __shared__ DirectTet s_t[DT];
+    __shared__ double s_m[DT][FCH][12];  // M_0 and M_i - M_0
+    constexpr int NC = kFarRules + 1;    // classes: the far rules, then the closed form
+    __shared__ double s_x[3][256], s_u[FCH][256];
+    __shared__ uint16_t s_pair[DT * 256];
+    __shared__ int s_cnt[NC], s_next;
     const int b = xcd_item(nblk);
     if (b < 0) return;
     const int64_t tb = (int64_t)b * DT;
@@ -1614,13 +1704,13 @@ __global__ __launch_bounds__(256, 2) void k_direct(int nblk, int64_t T, const do
         const int t = lane / FCH, f = lane % FCH;
         if (t < nt) {
             const int64_t tt = tb + t;
-            const double *Mf = M + (int64_t)(f0 + f) * n_nodes * 3;
+            const double *Mf = M + (int64_t)min(f0 + f, F - 1) * n_nodes * 3;
             tet_prepare(tet_xyz, tet_node, T, tt, Mf, f == 0 ? &s_g[t] : nullptr, s_f[t][f]);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const int64_t nd = tet_node[(int64_t)c * T + tt];
 #pragma unroll
-                for (int k = 0; k < 3; ++k) s_m[t][f][3 * c + k] = Mf[3 * nd + k];
+                for (int k = 0; k < 3; ++k) s_m[t][f][3 * c + k] = Mf[3 * nd + k] - (c ? s_m[t][f][k] : 0.0);
             }
             if (f == 0) {
                 double v[4][3];
@@ -1628,7 +1718,7 @@ __global__ __launch_bounds__(256, 2) void k_direct(int nblk, int64_t T, const do
                 for (int c = 0; c < 4; ++c)
 #pragma unroll
                     for (int k = 0; k < 3; ++k) v[c][k] = tet_xyz[(int64_t)(3 * c + k) * T + tt];
-                FarTet &F = s_t[t];
+                DirectTet &D = s_t[t];
                 double l2 = 0.0;
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
@@ -1637,76 +1727,148 @@ __global__ __launch_bounds__(256, 2) void k_direct(int nblk, int64_t T, const do
                         const double dx = v[q][0] - v[a][0], dy = v[q][1] - v[a][1], dz = v[q][2] - v[a][2];
                         l2 = fmax(l2, dx * dx + dy * dy + dz * dz);
                     }
-                F.id2 = 1.0 / l2;
+                D.id2 = 1.0 / l2;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
-                    F.c[k] = 0.25 * ((v[0][k] + v[1][k]) + (v[2][k] + v[3][k]));
-                    F.e[0][k] = v[1][k] - v[0][k];
-                    F.e[1][k] = v[2][k] - v[0][k];
-                    F.e[2][k] = v[3][k] - v[0][k];
+                    D.c[k] = 0.25 * ((v[0][k] + v[1][k]) + (v[2][k] + v[3][k]));
+                    D.e[0][k] = v[1][k] - v[0][k];
+                    D.e[1][k] = v[2][k] - v[0][k];
+                    D.e[2][k] = v[3][k] - v[0][k];
                 }
-                const double det = F.e[0][0] * (F.e[1][1] * F.e[2][2] - F.e[1][2] * F.e[2][1]) -
-                                   F.e[0][1] * (F.e[1][0] * F.e[2][2] - F.e[1][2] * F.e[2][0]) +
-                                   F.e[0][2] * (F.e[1][0] * F.e[2][1] - F.e[1][1] * F.e[2][0]);
-                F.vol6 = fabs(det);
+                const double det = D.e[0][0] * (D.e[1][1] * D.e[2][2] - D.e[1][2] * D.e[2][1]) -
+                                   D.e[0][1] * (D.e[1][0] * D.e[2][2] - D.e[1][2] * D.e[2][0]) +
+                                   D.e[0][2] * (D.e[1][0] * D.e[2][1] - D.e[1][1] * D.e[2][0]);
+                D.vol6 = fabs(det);
             }
         }
     }
     __syncthreads();
-    const double r2b[kFarBands] = {kFarRatio[0] * kFarRatio[0], kFarRatio[1] * kFarRatio[1],
-                                   kFarRatio[2] * kFarRatio[2], kFarRatio[3] * kFarRatio[3]};
-    for (int64_t i = lane; i < N; i += 256) {
+    const int wl = lane & 63;
+    for (int64_t i0 = (int64_t)blockIdx.y * 256; i0 < N; i0 += 256 * (int64_t)gridDim.y) {
+        const bool ok = i0 + lane < N;
+        const int64_t i = ok ? i0 + lane : N - 1;
         const double x[3] = {tgt_xyz[i], tgt_xyz[N + i], tgt_xyz[2 * N + i]};
-        double acc[FCH];
 #pragma unroll
-        for (int f = 0; f < FCH; ++f) acc[f] = 0.0;
+        for (int k = 0; k < 3; ++k) s_x[k][lane] = x[k];
+#pragma unroll
+        for (int f = 0; f < FCH; ++f) s_u[f][lane] = 0.0;
+        if (lane < NC) s_cnt[lane] = 0;
+        if (lane == NC) s_next = 0;
+        __syncthreads();
+        // sort the pairs (tet, target) by class: count, then place
+        uint64_t cls = 0;  // this target's class per tet, 4 bits each
+        int at[NC];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) at[k] = 0;
 #pragma unroll 1
         for (int t = 0; t < nt; ++t) {
-            const FarTet &F = s_t[t];
-            const double dc0 = x[0] - F.c[0], dc1 = x[1] - F.c[1], dc2 = x[2] - F.c[2];
-            const double rat2 = (dc0 * dc0 + dc1 * dc1 + dc2 * dc2) * F.id2;
-            if (rat2 < r2b[0]) {
-                pair_accumulate<FCH>(x, s_g[t], s_f[t], acc);
-                continue;
-            }
-            const int band = rat2 < r2b[1] ? 0 : (rat2 < r2b[2] ? 1 : (rat2 < r2b[3] ? 2 : 3));
-            const int q0 = band == 0 ? kFarOff[0] : (band == 1 ? kFarOff[1] : (band == 2 ? kFarOff[2] : kFarOff[3]));
-            const int q1 = band == 0 ? kFarOff[1] : (band == 1 ? kFarOff[2] : (band == 2 ? kFarOff[3] : kFarOff[4]));
-            const double xv[3] = {x[0] - s_g[t].v[0][0], x[1] - s_g[t].v[0][1], x[2] - s_g[t].v[0][2]};
-            double S[3] = {0.0, 0.0, 0.0}, K[3][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-#pragma unroll 2
-            for (int q = q0; q < q1; ++q) {
-                const double l1 = rule[4 * q], l2 = rule[4 * q + 1], l3 = rule[4 * q + 2], w = rule[4 * q + 3];
-                double d[3];
+            const DirectTet &D = s_t[t];
+            const double dc0 = x[0] - D.c[0], dc1 = x[1] - D.c[1], dc2 = x[2] - D.c[2];
+            const double rat2 = (dc0 * dc0 + dc1 * dc1 + dc2 * dc2) * D.id2;
+            int c = 0;
 #pragma unroll
-                for (int k = 0; k < 3; ++k) d[k] = xv[k] - (l1 * F.e[0][k] + l2 * F.e[1][k] + l3 * F.e[2][k]);
-                const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-                const double ri = rsqrt_nr(r2);
-                const double wr = w * ri * ri * ri;
+            for (int k = 1; k < kFarRules; ++k) c += !(rat2 < kFarRatio[k] * kFarRatio[k]);
+            if (rat2 < kFarRatio[0] * kFarRatio[0]) c = kFarRules;
+            if (!ok) c = 15;
+            cls |= (uint64_t)c << (4 * t);
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const double kk = wr * d[k];
-                    S[k] += kk;
-                    K[0][k] = fma(l1, kk, K[0][k]);
-                    K[1][k] = fma(l2, kk, K[1][k]);
-                    K[2][k] = fma(l3, kk, K[2][k]);
-                }
-            }
-            // K_0 = S - K_1 - K_2 - K_3 (lambda_0 = 1 - lambda_1 - lambda_2 - lambda_3)
+            for (int k = 0; k < NC; ++k) at[k] += __popcll(__ballot(c == k));
+        }
 #pragma unroll
-            for (int f = 0; f < FCH; ++f) {
-                const double *m = s_m[t][f];
-                double v = 0.0;
+        for (int k = 0; k < NC; ++k) {
+            int base = 0;
+            if (wl == 0) base = atomicAdd(&s_cnt[k], at[k]);
+            at[k] = __builtin_amdgcn_readfirstlane(base);
+        }
+        __syncthreads();
+        int cnt[NC], start[NC + 1];
+        start[0] = 0;
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
-                    v += m[k] * (S[k] - K[0][k] - K[1][k] - K[2][k]) + m[3 + k] * K[0][k] + m[6 + k] * K[1][k] +
-                         m[9 + k] * K[2][k];
-                acc[f] = fma(F.vol6, v, acc[f]);
+        for (int k = 0; k < NC; ++k) {
+            cnt[k] = __builtin_amdgcn_readfirstlane(s_cnt[k]);
+            start[k + 1] = start[k] + cnt[k];
+            at[k] += start[k];
+        }
+#pragma unroll 1
+        for (int t = 0; t < nt; ++t) {
+            const int c = (int)(cls >> (4 * t)) & 15;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                const uint64_t mask = __ballot(c == k);
+                if (c == k) s_pair[at[k] + __popcll(mask & ((1ull << wl) - 1))] = (uint16_t)(t * 256 + lane);
+                at[k] += __popcll(mask);
             }
         }
-        const int64_t o = tgt_perm[i];
+        __syncthreads();
+        for (;;) {
+            int chunk = 0;
+            if (wl == 0) chunk = atomicAdd(&s_next, 1);
+            chunk = __builtin_amdgcn_readfirstlane(chunk);
+            int c = 0, p0 = 0, p1 = 0;
 #pragma unroll
-        for (int f = 0; f < FCH; ++f) atomicAdd(&u[(int64_t)(f0 + f) * N + o], acc[f] * kInv4Pi);
+            for (int k = 0; k < NC; ++k) {
+                const int nch = (cnt[k] + 63) / 64;
+                if (chunk >= 0 && chunk < nch) {
+                    c = k;
+                    p0 = start[k] + 64 * chunk;
+                    p1 = start[k + 1];
+                }
+                chunk -= nch;
+            }
+            if (chunk >= 0) break;
+            const bool on = p0 + wl < p1;
+            const int pr = s_pair[on ? p0 + wl : p1 - 1], t = pr >> 8, j = pr & 255;
+            const double y[3] = {s_x[0][j], s_x[1][j], s_x[2][j]};
+            double acc[FCH];
+            if (c == kFarRules) {
+#pragma unroll
+                for (int f = 0; f < FCH; ++f) acc[f] = 0.0;
+                pair_accumulate<FCH>(y, s_g[t], s_f[t], acc);
+            } else {
+                const DirectTet &D = s_t[t];
+                const double xv[3] = {y[0] - s_g[t].v[0][0], y[1] - s_g[t].v[0][1], y[2] - s_g[t].v[0][2]};
+                double e[3][3], m[10];
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) e[q][k] = D.e[q][k];
+                switch (c) {
+                case 0: far_moments<kFarPts[0]>(xv, e, rules + far_offset(0), m); break;
+                case 1: far_moments<kFarPts[1]>(xv, e, rules + far_offset(1), m); break;
+                case 2: far_moments<kFarPts[2]>(xv, e, rules + far_offset(2), m); break;
+                default: far_moments<kFarPts[3]>(xv, e, rules + far_offset(3), m); break;
+                }
+                double K[4][3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    K[0][k] = D.vol6 * fma(m[0], xv[k], -fma(m[1], e[0][k], fma(m[2], e[1][k], m[3] * e[2][k])));
+                    K[1][k] = D.vol6 * fma(m[1], xv[k], -fma(m[4], e[0][k], fma(m[5], e[1][k], m[6] * e[2][k])));
+                    K[2][k] = D.vol6 * fma(m[2], xv[k], -fma(m[5], e[0][k], fma(m[7], e[1][k], m[8] * e[2][k])));
+                    K[3][k] = D.vol6 * fma(m[3], xv[k], -fma(m[6], e[0][k], fma(m[8], e[1][k], m[9] * e[2][k])));
+                }
+#pragma unroll
+                for (int f = 0; f < FCH; ++f) {
+                    const double *M4 = s_m[t][f];
+                    double v = 0.0;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) v = fma(M4[3 * q + k], K[q][k], v);
+                    acc[f] = v;
+                }
+            }
+            if (on)
+#pragma unroll
+                for (int f = 0; f < FCH; ++f) atomicAdd(&s_u[f][j], acc[f]);
+        }
+        __syncthreads();
+        if (ok) {
+            const int64_t o = tgt_perm[i];
+#pragma unroll
+            for (int f = 0; f < FCH; ++f)
+                if (f0 + f < F) atomicAdd(&u[(int64_t)(f0 + f) * N + o], s_u[f][lane] * kInv4Pi);
+        }
+        __syncthreads();
     }
 }
 
@@ -1937,16 +2099,6 @@ __global__ __launch_bounds__(64) void k_topo_coef(const int32_t *__restrict__ ch
         const double w = q < 10 ? 2.0 * edge[(int64_t)eoff + e].il : 0.5;
         (&edge_w[(int64_t)eoff + e].B[0])[q] = q < 11 ? s_B[e][q] * w : 0.0;
     }
-}
-
-// Memory that no thread writes during the launch: uniform reads of it go to
-// the scalar unit whatever the compiler can prove about aliasing.
-template <typename T>
-using ScalarMem = T __attribute__((address_space(4)));
-template <typename T>
-__device__ __forceinline__ const ScalarMem<T> *scalar_mem(const T *p)
-{
-    return (const ScalarMem<T> *)p;
 }
 
 // Work item: up to 64 targets of one source block, one wavefront, one target
@@ -4219,25 +4371,29 @@ void run_direct(DevicePlan &dp, const double *M, int32_t F, double *u, hipStream
     }
     if (hp.n_tets == 0 || hp.n_targets == 0) return;
     for (int f = 0; f < F;) {
+        // one pass for up to 16 fields: the integrals cost more than padded fields
         const int left = F - f;
-        const int fch = left >= 32 ? 32 : (left >= 16 ? 16 : (left >= 8 ? 8 : (left >= 4 ? 4 : (left >= 2 ? 2 : 1))));
         auto go = [&](auto fc) {
             constexpr int FC = decltype(fc)::value;
             const int nblk = (int)((hp.n_tets + direct_stage(FC) - 1) / direct_stage(FC));
-            k_direct<FC><<<dim3(xcd_grid(nblk)), dim3(256), 0, st>>>(nblk, hp.n_tets, dp.tet_xyz, dp.tet_node,
-                                                                     dp.tgt_xyz, dp.tgt_perm, hp.n_targets, M,
-                                                                     hp.n_nodes, f, dp.far_rule, u);
+            // enough workgroups for five rounds of three a CU; more would only stage the tets again
+            const int64_t shares = std::min<int64_t>((hp.n_targets + 255) / 256, std::max(1, (4096 + nblk - 1) / nblk));
+            k_direct<FC><<<dim3(xcd_grid(nblk), (unsigned)shares), dim3(256), 0, st>>>(
+                nblk, hp.n_tets, dp.tet_xyz, dp.tet_node, dp.tgt_xyz, dp.tgt_perm, hp.n_targets, M, hp.n_nodes, f, F,
+                dp.far_rule, u);
+            f += FC;
         };
-        switch (fch) {
-        case 32: go(std::integral_constant<int, 32>{}); break;
-        case 16: go(std::integral_constant<int, 16>{}); break;
-        case 8: go(std::integral_constant<int, 8>{}); break;
-        case 4: go(std::integral_constant<int, 4>{}); break;
-        case 2: go(std::integral_constant<int, 2>{}); break;
-        default: go(std::integral_constant<int, 1>{}); break;
-        }
+        if (left > 8)
+            go(std::integral_constant<int, kDirectFieldsMax>{});
+        else if (left > 4)
+            go(std::integral_constant<int, 8>{});
+        else if (left > 2)
+            go(std::integral_constant<int, 4>{});
+        else if (left > 1)
+            go(std::integral_constant<int, 2>{});
+        else
+            go(std::integral_constant<int, 1>{});
         hip_check(hipGetLastError(), "k_direct launch");
-        f += fch;
     }
 }
 
@@ -4310,6 +4466,33 @@ void gauss_jacobi01(int n, double a, std::vector<double> &t, std::vector<double>
 }
 
 }  // namespace
+
+std::vector<double> far_tables()
+{
+    std::vector<double> out;
+    for (int n : kFarPts) {
+        std::vector<double> t[3], w[3];
+        for (int k = 0; k < 3; ++k) {
+            gauss_jacobi01(n, (double)k, t[k], w[k]);
+            double sum = 0.0;
+            for (double x : w[k]) sum += x;
+            for (double &x : w[k]) x /= sum * (k + 1);  // the weights sum to 1 / (k + 1)
+        }
+        for (int i = 0; i < n; ++i) {
+            const double c = t[0][i], wc = w[0][i];
+            out.insert(out.end(), {c, wc, wc * c, wc * c * c});
+        }
+        for (int i = 0; i < n; ++i) {
+            const double b = t[1][i], u = 1.0 - b, wb = w[1][i];
+            out.insert(out.end(), {b, u, wb, wb * b, wb * b * b, wb * u, wb * b * u, wb * u * u});
+        }
+        for (int i = 0; i < n; ++i) {
+            const double a = t[2][i], q = 1.0 - a, wa = w[2][i];
+            out.insert(out.end(), {a, q, wa, wa * a, wa * a * a, wa * q, wa * a * q, wa * q * q});
+        }
+    }
+    return out;
+}
 
 std::vector<double> simplex_rule(int deg, int *npts)
 {
