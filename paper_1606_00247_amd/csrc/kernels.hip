@@ -82,7 +82,7 @@ __host__ __device__ constexpr int mi_y(int m) { return kMi.v[m][1]; }
 __host__ __device__ constexpr int mi_z(int m) { return kMi.v[m][2]; }
 __constant__ BinomTable c_bin = make_binom();
 
-__device__ __forceinline__ int mi_index(int nx, int ny, int nz)
+__host__ __device__ constexpr int mi_index(int nx, int ny, int nz)
 {
     int d = nx + ny + nz, r = ny + nz;
     return d * (d + 1) * (d + 2) / 6 + r * (r + 1) / 2 + nz;
@@ -631,11 +631,14 @@ __host__ __device__ constexpr int m2l_ks(int P, int rt)
     if (d >= P) return 0;
     return (nr_of(P - d) - 1 + 3) / 4;
 }
-__host__ __device__ constexpr int m2l_kstr(int P)
+// Rows of the tile form's multipoles: row length at order p, and the place of
+// column n >= 1 (step ks = (n - 1) / 4, quarter (n - 1) % 4), grouped by the
+// wavefront that takes the step and the quarter of it that loads the column.
+__host__ __device__ constexpr int m2l_tile_row(int p) { return 16 * ((m2l_ks(p, 0) + kM2LWaves - 1) / kM2LWaves); }
+__host__ __device__ constexpr int m2l_tile_col(int i, int row)  // column at place i
 {
-    int k = 4 * m2l_ks(P, 0) + 1;  // columns 0 .. 4 KS
-    while (k % 16 != 1) ++k;       // odd row stride: spreads the 16 columns over the banks
-    return k;
+    const int g = i / (row / 16), j = i % (row / 16);
+    return 1 + 4 * (g / 4 + kM2LWaves * j) + g % 4;
 }
 // Column steps of wave W: ks = W, W + kM2LWaves, ... of every row tile.
 __host__ __device__ constexpr int m2l_wave_steps(int P, int W)
@@ -686,39 +689,129 @@ __global__ void k_to_float(const double *__restrict__ a, int64_t n, float *__res
     for (; i < n; i += (int64_t)gridDim.x * blockDim.x) b[i] = (float)a[i];
 }
 
-// Reduced scaled multipoles of the cells holding tets; one thread per
-// (cell, reduced index n = (a, b, c), c <= 1):
+// Reduced scaled multipoles of the cells holding tets, for reduced indices
+// n = (a, b, c), c <= 1:
 //   Qr_n = (-1)^|n| s_B^-|n| sum_{j >= 0} (-1)^j sum_{i <= j} C(j, i) Q_n'/n'!,
-//   n' = (a - 2i, b - 2(j - i), c + 2j).
-template <typename T>
-__global__ void k_qreduce(const double *__restrict__ Q, const int32_t *__restrict__ cell_i, int64_t C, double side,
-                          int p, int qpad, T *__restrict__ Qr)
+//   n' = (a - 2i, b - 2(j - i), c + 2j),
+// and back: Lt_m of the reduced locals (see k_m2l_mfma) times 1 / (4 pi m!).
+// Both as lists of terms (coefficient, weight) per output, made at compile time.
+constexpr int kReduceTerms = 1024, kExpandTerms = 704;
+struct ReduceTable {
+    int16_t start[kNrMax + 1], at[kReduceTerms];
+    double w[kReduceTerms];
+};
+constexpr ReduceTable make_reduce()
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int f = blockIdx.y;
-    const int ncoef = ncoef_of(p);
-    if (i >= C * qpad) return;
-    const int64_t c = i / qpad;
-    const int n = (int)(i % qpad);
-    double v = 0.0;
-    if (n < nr_of(p) && cell_i[CI_N * c + CI_TEND] > cell_i[CI_N * c + CI_TBEG]) {
-        const int a = c_red.r[n][0], b = c_red.r[n][1], cz = c_red.r[n][2], d = c_red.r[n][3];
-        const double *q = Q + ((int64_t)f * C + c) * ncoef;
-        for (int j = 0; cz + 2 * j <= d; ++j) {
-            double sj = 0.0;
-            for (int k = 0; k <= j; ++k) {
-                const int x = a - 2 * k, y = b - 2 * (j - k), z = cz + 2 * j;
+    constexpr BinomTable bin = make_binom();
+    constexpr RedTable red = make_red();
+    ReduceTable t{};
+    int k = 0;
+    for (int n = 0; n < kNrMax; ++n) {
+        const int a = red.r[n][0], b = red.r[n][1], c = red.r[n][2], d = red.r[n][3];
+        t.start[n] = (int16_t)k;
+        for (int j = 0; c + 2 * j <= d; ++j)
+            for (int i = 0; i <= j; ++i) {
+                const int x = a - 2 * i, y = b - 2 * (j - i), z = c + 2 * j;
                 if (x < 0 || y < 0) continue;
-                sj += c_bin.c[j][k] * q[mi_index(x, y, z)] * c_bin.invfact[x] * c_bin.invfact[y] * c_bin.invfact[z];
+                t.at[k] = (int16_t)mi_index(x, y, z);
+                t.w[k++] = (j & 1 ? -1.0 : 1.0) * bin.c[j][i] * bin.invfact[x] * bin.invfact[y] * bin.invfact[z];
             }
-            v += (j & 1) ? -sj : sj;
-        }
-        const double is = 1.0 / ldexp(side, -cell_i[CI_N * c + CI_LEVEL]);
-        double sp = 1.0;
-        for (int j = 0; j < d; ++j) sp *= is;
-        v *= ((d & 1) ? -sp : sp);
     }
-    Qr[((int64_t)f * C + c) * qpad + n] = (T)v;
+    t.start[kNrMax] = (int16_t)k;
+    return t;
+}
+constexpr int kNcMax = ncoef_of(kPmax);
+struct ExpandTable {
+    int16_t start[kNcMax + 1], at[kExpandTerms];
+    double w[kExpandTerms];
+};
+constexpr ExpandTable make_expand()
+{
+    constexpr BinomTable bin = make_binom();
+    ExpandTable t{};
+    int k = 0;
+    for (int m = 0; m < kNcMax; ++m) {
+        const int x = kMi.v[m][0], y = kMi.v[m][1], z = kMi.v[m][2], j = z / 2;
+        t.start[m] = (int16_t)k;
+        for (int i = 0; i <= j; ++i) {
+            t.at[k] = (int16_t)ridx(x + 2 * i, y + 2 * (j - i), z % 2);
+            t.w[k++] = (j & 1 ? -1.0 : 1.0) * bin.c[j][i] * kInv4Pi * bin.invfact[x] * bin.invfact[y] * bin.invfact[z];
+        }
+    }
+    t.start[kNcMax] = (int16_t)k;
+    return t;
+}
+__constant__ ReduceTable c_reduce = make_reduce();
+__constant__ ExpandTable c_expand = make_expand();
+
+// A workgroup takes up to kRowCells consecutive cells of a field (fewer on small
+// meshes, for 1024 workgroups): their coefficients and the terms go to LDS in whole
+// lines.  Bound by its bytes (37,449 cells, order
+// 8, in us: 95 with a thread per output walking the multi-indices in global
+// memory, now 30; the locals 57, now 24).
+constexpr int kRowCells = 16;
+__host__ __device__ constexpr size_t row_lds(int nin, int nterm, int nout)
+{
+    return sizeof(double) * (size_t)(kRowCells * (nin + kPmax + 1) + nterm) + sizeof(int16_t) * (size_t)(nterm + nout + 1);
+}
+inline int row_cells(int64_t C, int32_t F)
+{
+    return (int)std::min<int64_t>(kRowCells, std::max<int64_t>(1, C * F / 1024));
+}
+struct RowLds {
+    double *in, *scale, *w;
+    int16_t *at, *start;
+    __device__ RowLds(double *s, int nin, int nterm)
+        : in(s), scale(in + kRowCells * nin), w(scale + kRowCells * (kPmax + 1)), at((int16_t *)(w + nterm)),
+          start(at + nterm)
+    {
+    }
+    // sum of output n of cell c
+    __device__ double sum(int c, int nin, int n) const
+    {
+        double v = 0.0;
+        for (int k = start[n]; k < start[n + 1]; ++k) v = fma(w[k], in[c * nin + at[k]], v);
+        return v;
+    }
+};
+
+// (Lr, where given: the accumulators of M2L, lrs a cell, cleared here)
+template <typename T>
+__global__ __launch_bounds__(256) void k_qreduce(const double *__restrict__ Q, const int32_t *__restrict__ cell_i,
+                                                 int64_t C, double side, int p, int row, bool tiled, T *__restrict__ Qr,
+                                                 double *__restrict__ Lr, int lrs, int cells)
+{
+    extern __shared__ double s_row[];
+    const int ncoef = ncoef_of(p), nr = nr_of(p), nterm = c_reduce.start[nr], tid = threadIdx.x, f = blockIdx.y;
+    const RowLds S(s_row, ncoef, nterm);
+    const int64_t c0 = (int64_t)blockIdx.x * cells;
+    const int n_c = (int)min<int64_t>(cells, C - c0);
+    const double *q = Q + ((int64_t)f * C + c0) * ncoef;
+    for (int i = tid; i < n_c * ncoef; i += 256) S.in[i] = q[i];
+    for (int i = tid; i < nterm; i += 256) {
+        S.w[i] = c_reduce.w[i];
+        S.at[i] = c_reduce.at[i];
+    }
+    for (int i = tid; i <= nr; i += 256) S.start[i] = c_reduce.start[i];
+    if (tid < n_c) {  // (-1 / s)^d, zero for a cell without tets
+        const int32_t *ci = cell_i + CI_N * (c0 + tid);
+        const double is = -1.0 / ldexp(side, -ci[CI_LEVEL]);
+        double sp = ci[CI_TEND] > ci[CI_TBEG] ? 1.0 : 0.0;
+        for (int d = 0; d <= p; ++d, sp *= is) S.scale[tid * (kPmax + 1) + d] = sp;
+    }
+    __syncthreads();
+    T *out = Qr + ((int64_t)f * C + c0) * row;
+    for (int i = tid; i < n_c * row; i += 256) {
+        const int c = i / row, at = i - c * row, n = tiled ? m2l_tile_col(at, row) : at;
+        double v = 0.0;
+        if (n < nr) {
+            const double sp = S.scale[c * (kPmax + 1) + (int)sqrtf((float)n)];  // degree: exact, d starts at d^2
+            if (sp != 0.0) v = sp * S.sum(c, ncoef, n);
+        }
+        out[i] = (T)v;
+    }
+    if (Lr)
+        for (int i = tid; i < n_c * lrs; i += 256) Lr[((int64_t)f * C + c0) * lrs + i] = 0.0;
 }
 
 // Steps of wave W in issue order: column step ks = W, W + 4, ... (outer),
@@ -747,31 +840,6 @@ __device__ __forceinline__ void m2l_wave_index(int lane, M2LIdx<P, W> &didx)
     }
 }
 
-template <typename T, int P, int W>
-__device__ __forceinline__ void m2l_wave_mfma(typename Mfma<T>::v4 (&acc)[m2l_nrt(P)], typename Mfma<T>::v4 (&acc0)[2],
-                                              const T *s_D, const T *s_Q, const M2LIdx<P, W> &didx, int lane)
-{
-    constexpr int NRT = m2l_nrt(P), KSTR = m2l_kstr(P), KS0 = m2l_ks(P, 0);
-    const T *qcol = s_Q + (lane & 15) * KSTR + 1 + (lane >> 4);
-    int s = 0, r0 = 0;
-#pragma unroll
-    for (int ks = W; ks < KS0; ks += kM2LWaves) {
-        const T b = qcol[4 * ks];
-#pragma unroll
-        for (int rt = 0; rt < NRT; ++rt) {
-            if (ks < m2l_ks(P, rt)) {
-                const T a = s_D[didx[s++]];
-                if (rt == 0) {
-                    acc0[r0 & 1] = Mfma<T>::mma(a, b, acc0[r0 & 1]);
-                    ++r0;
-                } else {
-                    acc[rt] = Mfma<T>::mma(a, b, acc[rt]);
-                }
-            }
-        }
-    }
-}
-
 // Geometry of a tile: TPT target cells x FPT fields = 16 MFMA columns,
 // column c = t * FPT + g (target slot t, field f0 + g).
 struct M2LCols {
@@ -779,122 +847,104 @@ struct M2LCols {
     int dstr;  // row stride of the derivative tables (the plan's order; P may be lower)
 };
 
-// One workgroup of kM2LWaves wavefronts per target tile (see k_m2l_mfma).
-// Two LDS buffers: while the MFMAs of key e read buffer e&1, the operands of
-// key e+1 are loaded into registers and stored to the other buffer; one
-// barrier per key.  Thread tid stages column tid/16, coefficients
-// n = tid%16 + 16 j.
-constexpr int kM2LSeg = 128;  // M2L entries whose metadata is staged in LDS at once
-constexpr int kM2LAhead = 2;  // lookahead entries staged with a segment (matrix-core form)
+constexpr int kM2LSeg = 128;  // M2L entries whose metadata is staged in LDS at once (BF16 form)
 
+// Column steps of wavefront W (see k_m2l_mfma): KJ of them, ks = W + kM2LWaves j,
+// whose multipoles lie together in a row of Qr (m2l_tile_slot).  The wavefronts
+// share nothing until their sums meet: each gathers its A operands from its own
+// copy of the key's derivative row in LDS and loads its B operands in place, two
+// entries ahead, in one of two register sets.  (With operands staged for all four
+// by all four, a barrier per entry, the matrix cores were busy 38% of the time;
+// F = 16, order 8, 1.4 million translations: 1.53 ms, now 1.45.)
 template <typename T, int P, int W>
 __device__ __forceinline__ void m2l_tile(const int32_t *__restrict__ tile_rng, const int32_t *__restrict__ ent_key,
                                          const int32_t *__restrict__ ent_src, const int32_t *__restrict__ keys,
-                                         const T *__restrict__ Dtab, const T *__restrict__ Qr, int qpad, int64_t C,
-                                         M2LCols cols, int tile, T *s_D, T *s_Q, int32_t *s_src, int32_t *s_kk,
-                                         typename Mfma<T>::v4 (&acc)[m2l_nrt(P)])
+                                         const T *__restrict__ Dtab, const T *__restrict__ Qr, int qrow, int64_t C,
+                                         M2LCols cols, int tile, T *D, typename Mfma<T>::v4 (&acc)[m2l_nrt(P)])
 {
     using v4 = typename Mfma<T>::v4;
-    constexpr int NR = nr_of(P), ND = nd_of(P), KSTR = m2l_kstr(P), DSTR = ND + 1;
-    constexpr int NT = 64 * kM2LWaves;
-    static_assert(NT == 256, "16 columns x 16 threads");
-    constexpr int QREG = (NR + 15) / 16, DREG = (ND + NT - 1) / NT;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int tcol = tid >> 4, tn = tid & 15;
-    const int tslot = tcol / cols.fpt, field = cols.f0 + tcol % cols.fpt;
-    M2LIdx<P, W> didx;
-    m2l_wave_index<P, W>(lane, didx);
-    v4 acc0[2] = {v4{0, 0, 0, 0}, v4{0, 0, 0, 0}};
-    const int e0 = tile_rng[2 * tile], e1 = tile_rng[2 * tile + 1];
-    int qdeg[QREG];
+    constexpr int ND = nd_of(P), NRT = m2l_nrt(P), KS0 = m2l_ks(P, 0);
+    constexpr int KJ = (KS0 - W + kM2LWaves - 1) / kM2LWaves, DREG = (ND + 63) / 64;
+    if constexpr (KJ > 0) {
+        const int lane = threadIdx.x & 63, col = lane & 15, kq = lane >> 4;
+        const int tslot = col / cols.fpt, field = cols.f0 + col % cols.fpt;
+        M2LIdx<P, W> didx;
+        m2l_wave_index<P, W>(lane, didx);
+        constexpr int NS = m2l_wave_steps(P, W);
+        v4 acc0[2] = {v4{0, 0, 0, 0}, v4{0, 0, 0, 0}};
+        const int e0 = tile_rng[2 * tile], e1 = tile_rng[2 * tile + 1];
+        if (e0 >= e1) return;
+        const bool active = field < cols.F;
+        const T *qf = Qr + (int64_t)(active ? field : 0) * C * qrow + (W * 4 + kq) * (qrow / 16);
+        auto source = [&](int e) { return ent_src[(int64_t)min(e, e1 - 1) * cols.tpt + tslot]; };
+        auto key_of = [&](int e) { return ent_key[min(e, e1 - 1)]; };
+        // Loads go to in-bounds addresses unconditionally and are masked when used.
+        struct Ops {
+            T q[KJ], d[DREG];
+            int dl;
+            bool ok;
+        };
+        auto load = [&](Ops &o, int src, int key) {
+            o.ok = active && src >= 0;
+            const T *q = qf + (int64_t)(o.ok ? src : 0) * qrow;
 #pragma unroll
-    for (int j = 0; j < QREG; ++j) qdeg[j] = rdeg(tn + 16 * j);
-    // Entry metadata (key id, its level difference, the source cell of every
-    // tile slot) is staged in LDS a segment of kM2LSeg entries (plus
-    // kM2LAhead lookahead entries) at a time, so the loop issues no global
-    // load whose address depends on another global load.  The table row and
-    // multipoles of an entry are loaded two entries ahead, into one of two
-    // register sets: those of entry e + 2 are in flight while the MFMAs of
-    // entry e run and entry e + 1 is stored to LDS, so a load has two entries
-    // of matrix work to arrive in.  Loads go to clamped, in-bounds addresses
-    // unconditionally and are masked when stored (exec-masked loads make the
-    // compiler wait for every outstanding load where the branches join).
-    const bool active = field < cols.F;
-    const T *qf = Qr + (int64_t)(active ? field : 0) * C * qpad;
-    int seg = e0;
-    auto stage_seg = [&]() {
-        const int ne = min(e1 - seg, kM2LSeg + kM2LAhead);
-        for (int i = tid; i < ne * cols.tpt; i += NT) s_src[i] = ent_src[(int64_t)seg * cols.tpt + i];
-        for (int i = tid; i < ne; i += NT) {
-            const int key = ent_key[seg + i];
-            s_kk[2 * i] = key;
-            s_kk[2 * i + 1] = keys[4 * key];
-        }
-    };
-    struct Ops {
-        T q[QREG], d[DREG];
-        int dl;
-        bool ok;
-    };
-    auto fetch = [&](Ops &o, int e) {
-        const int r = e - seg;
-        const int key = s_kk[2 * r];
-        o.dl = s_kk[2 * r + 1];
-        const int src = s_src[r * cols.tpt + tslot];
+            for (int j = 0; j < KJ; ++j) o.q[j] = q[j];
 #pragma unroll
-        for (int j = 0; j < DREG; ++j) {
-            const int k = tid + NT * j;
-            o.d[j] = Dtab[(int64_t)key * cols.dstr + (k < ND ? k : ND - 1)];
-        }
-        o.ok = active && src >= 0;
-        const T *q = qf + (int64_t)(o.ok ? src : 0) * qpad;
+            for (int j = 0; j < DREG; ++j) o.d[j] = Dtab[(int64_t)key * cols.dstr + min(lane + 64 * j, ND - 1)];
+            o.dl = keys[4 * key];
+        };
+        auto stage = [&](const Ops &o) {  // a wavefront's LDS operations keep their order
 #pragma unroll
-        for (int j = 0; j < QREG; ++j) {
-            const int n = tn + 16 * j;
-            o.q[j] = q[n < NR ? n : NR - 1];
-        }
-    };
-    auto store = [&](const Ops &o, int buf) {
-        T *D = s_D + buf * DSTR;
-        T *Qb = s_Q + buf * 16 * KSTR + tcol * KSTR;
+            for (int j = 0; j < DREG; ++j)
+                if (lane + 64 * j < ND) D[lane + 64 * j] = o.d[j];
+        };
+        Ops oa, ob;
+        load(oa, source(e0), key_of(e0));
+        load(ob, source(e0 + 1), key_of(e0 + 1));
+        int src2 = source(e0 + 2), src3 = source(e0 + 3), key2 = key_of(e0 + 2), key3 = key_of(e0 + 3);
+        stage(oa);
+        auto step = [&](Ops &cur, const Ops &nxt, int e) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            T a[NS];
 #pragma unroll
-        for (int j = 0; j < DREG; ++j) {
-            const int k = tid + NT * j;
-            if (k < ND) D[k] = o.d[j];
-        }
+            for (int s = 0; s < NS; ++s) a[s] = D[didx[s]];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (e + 1 < e1) stage(nxt);
+            if (cur.dl != 0) {  // uniform over the wavefront; 2^(-dl |n|), exact
 #pragma unroll
-        for (int j = 0; j < QREG; ++j) {
-            const int n = tn + 16 * j;
-            if (n < NR) Qb[n] = o.ok ? ldexp(o.q[j], -o.dl * qdeg[j]) : (T)0;  // 2^(-dl |n|), exact
+                for (int j = 0; j < KJ; ++j) {
+                    const int deg = (int)sqrtf((float)(1 + 4 * (W + kM2LWaves * j) + kq));  // exact: degree d starts at d^2
+                    cur.q[j] = ldexp(cur.q[j], -cur.dl * deg);
+                }
+            }
+            int s = 0;
+#pragma unroll
+            for (int j = 0; j < KJ; ++j) {
+                const int ks = W + kM2LWaves * j;
+                const T b = cur.ok ? cur.q[j] : (T)0;
+#pragma unroll
+                for (int rt = 0; rt < NRT; ++rt)
+                    if (ks < m2l_ks(P, rt)) {
+                        if (rt == 0)
+                            acc0[j & 1] = Mfma<T>::mma(a[s++], b, acc0[j & 1]);
+                        else
+                            acc[rt] = Mfma<T>::mma(a[s++], b, acc[rt]);
+                    }
+            }
+            load(cur, src2, key2);
+            src2 = src3;
+            key2 = key3;
+            src3 = source(e + 4);
+            key3 = key_of(e + 4);
+        };
+        for (int e = e0; e < e1; e += 2) {
+            step(oa, ob, e);
+            if (e + 1 < e1) step(ob, oa, e + 1);
         }
-    };
-    if (e0 >= e1) return;
-    stage_seg();
-    __syncthreads();
-    Ops oa, ob;
-    fetch(oa, e0);
-    store(oa, 0);
-    if (e0 + 1 < e1) fetch(oa, e0 + 1);
-    __syncthreads();
-    // Entry e is in LDS buffer (e - e0) & 1, `cur` holds the loads of entry
-    // e + 1 and `nxt` takes those of entry e + 2.
-    auto step = [&](Ops &cur, Ops &nxt, int e) {
-        const int buf = (e - e0) & 1;
-        if (e + 2 < e1) fetch(nxt, e + 2);
-        m2l_wave_mfma<T, P, W>(acc, acc0, s_D + buf * DSTR, s_Q + buf * 16 * KSTR, didx, lane);
-        if (e + 1 < e1) store(cur, buf ^ 1);
-        __syncthreads();
-        if (e + 3 < e1 && e + 3 - seg == kM2LSeg + kM2LAhead) {  // the next fetch leaves the segment
-            seg = e + 3;
-            stage_seg();
-            __syncthreads();
-        }
-    };
-    for (int e = e0; e < e1; e += 2) {
-        step(oa, ob, e);
-        if (e + 1 < e1) step(ob, oa, e + 1);
+        acc[0] += acc0[0] + acc0[1];
     }
-    acc[0] += acc0[0] + acc0[1];
 }
 
 // ---------------------------------------------------------------------------
@@ -909,7 +959,7 @@ __device__ __forceinline__ void m2l_tile(const int32_t *__restrict__ tile_rng, c
 // distinct key serves every level, and all magnitudes are O(1) (the FP32 form
 // needs no other scaling).  The level factor splits exactly as
 // 2^(dl (|n|+|m|+1)) * 2^(-dl |n|): the first is in the key's table, the
-// second is applied to the multipoles as they are staged.  The contraction runs on the harmonic reduction
+// second is applied to the multipoles as they are used.  The contraction runs on the harmonic reduction
 // (reduced multipoles Qr, outputs Lr with m_z <= 1); the epilogue expands Lr
 // to all m by
 //   Lt_(x, y, c + 2j) = (-1)^j sum_{i <= j} C(j, i) Lr_(x + 2i, y + 2(j - i), c).
@@ -921,47 +971,41 @@ __device__ __forceinline__ void m2l_tile(const int32_t *__restrict__ tile_rng, c
 // partial sums meet in LDS.
 // ---------------------------------------------------------------------------
 template <typename T, int P>
-__global__ __launch_bounds__(64 * kM2LWaves, 2) void k_m2l_mfma(
+__global__ __launch_bounds__(64 * kM2LWaves, sizeof(T) == 4 ? 4 : 2) void k_m2l_mfma(
     const int32_t *__restrict__ tile_tgt, const int32_t *__restrict__ tile_rng, const int32_t *__restrict__ ent_key,
     const int32_t *__restrict__ ent_src, const int32_t *__restrict__ keys, const T *__restrict__ Dtab,
-    const T *__restrict__ Qr, int qpad, const int32_t *__restrict__ cell_i, double side, int64_t C, int tpt, int fpt,
+    const T *__restrict__ Qr, int qrow, const int32_t *__restrict__ cell_i, double side, int64_t C, int tpt, int fpt,
     int F, int ntiles, int dstr, int lstr, double *__restrict__ L)
 {
     using v4 = typename Mfma<T>::v4;
-    constexpr int NC = ncoef_of(P), NROW = m2l_nrows(P), ND = nd_of(P), NRT = m2l_nrt(P), KSTR = m2l_kstr(P);
-    static_assert(KSTR >= NROW, "the staging buffer doubles as the reduction buffer");
+    constexpr int NC = ncoef_of(P), NROW = m2l_nrows(P), ND = nd_of(P), NRT = m2l_nrt(P), RSTR = NROW | 1;
     static_assert(kM2LWaves == 4, "wave specialisation below");
-    static_assert(2 * sizeof(T) >= sizeof(double), "reduction buffer fits in the staging buffers");
-    __shared__ T s_D[2 * (ND + 1)];
-    __shared__ __align__(16) T s_Q[2 * 16 * KSTR];
-    __shared__ int32_t s_src[(kM2LSeg + kM2LAhead) * 16], s_kk[2 * (kM2LSeg + kM2LAhead)];
+    __shared__ T s_D[kM2LWaves][ND + 1];
+    __shared__ double red[16 * RSTR];  // the waves' sums: red[c][m], c = column
     const int tile = blockIdx.x;
     if (tile >= ntiles) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const M2LCols cols{tpt, fpt, (int)blockIdx.y * fpt, F, dstr};
-    for (int i = tid; i < 2 * 16 * KSTR; i += blockDim.x) s_Q[i] = (T)0;  // column padding stays zero
-    for (int i = tid; i < 2 * (ND + 1); i += blockDim.x) s_D[i] = (T)0;   // zero slot ND of each buffer
-    __syncthreads();
+    for (int i = tid; i < 16 * RSTR; i += blockDim.x) red[i] = 0.0;
+    T *D = s_D[wave];
+    if ((tid & 63) == 0) D[ND] = (T)0;  // the zero slot
     v4 acc[NRT];
 #pragma unroll
     for (int rt = 0; rt < NRT; ++rt) acc[rt] = v4{0, 0, 0, 0};
     switch (wave) {
-    case 0: m2l_tile<T, P, 0>(tile_rng, ent_key, ent_src, keys, Dtab, Qr, qpad, C, cols, tile, s_D, s_Q, s_src, s_kk, acc); break;
-    case 1: m2l_tile<T, P, 1>(tile_rng, ent_key, ent_src, keys, Dtab, Qr, qpad, C, cols, tile, s_D, s_Q, s_src, s_kk, acc); break;
-    case 2: m2l_tile<T, P, 2>(tile_rng, ent_key, ent_src, keys, Dtab, Qr, qpad, C, cols, tile, s_D, s_Q, s_src, s_kk, acc); break;
-    default: m2l_tile<T, P, 3>(tile_rng, ent_key, ent_src, keys, Dtab, Qr, qpad, C, cols, tile, s_D, s_Q, s_src, s_kk, acc); break;
+    case 0: m2l_tile<T, P, 0>(tile_rng, ent_key, ent_src, keys, Dtab, Qr, qrow, C, cols, tile, D, acc); break;
+    case 1: m2l_tile<T, P, 1>(tile_rng, ent_key, ent_src, keys, Dtab, Qr, qrow, C, cols, tile, D, acc); break;
+    case 2: m2l_tile<T, P, 2>(tile_rng, ent_key, ent_src, keys, Dtab, Qr, qrow, C, cols, tile, D, acc); break;
+    default: m2l_tile<T, P, 3>(tile_rng, ent_key, ent_src, keys, Dtab, Qr, qrow, C, cols, tile, D, acc); break;
     }
-    // sum the waves' partial accumulators in LDS (FP64): red[c][m], c = column
-    __syncthreads();
-    double *red = reinterpret_cast<double *>(s_Q);
-    for (int i = tid; i < 16 * KSTR; i += blockDim.x) red[i] = 0.0;
+    // sum the waves' partial accumulators in LDS (FP64)
     __syncthreads();
 #pragma unroll
     for (int rt = 0; rt < NRT; ++rt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int m = 16 * rt + Mfma<T>::row(lane, r);
-            if (m < NROW) atomicAdd(&red[(lane & 15) * KSTR + m], (double)acc[rt][r]);
+            if (m < NROW) atomicAdd(&red[(lane & 15) * RSTR + m], (double)acc[rt][r]);
         }
     __syncthreads();
     // expand to all m, then l_m(A) = Lt_m / (4 pi m! s_A^(|m|+1))
@@ -974,7 +1018,7 @@ __global__ __launch_bounds__(64 * kM2LWaves, 2) void k_m2l_mfma(
         double lt = 0.0;
         if (dm < P) {
             const int j = mz >> 1, cz = mz & 1;
-            for (int k = 0; k <= j; ++k) lt += c_bin.c[j][k] * red[c * KSTR + ridx(mx + 2 * k, my + 2 * (j - k), cz)];
+            for (int k = 0; k <= j; ++k) lt += c_bin.c[j][k] * red[c * RSTR + ridx(mx + 2 * k, my + 2 * (j - k), cz)];
             if (j & 1) lt = -lt;
         }
         const double is = 1.0 / ldexp(side, -cell_i[CI_N * A + CI_LEVEL]);
@@ -1202,29 +1246,42 @@ __global__ __launch_bounds__(64 * kM2LPWaves, 2) void k_m2l_pack(
     }
 }
 
-// L_m(A) += Lt_m(A) / (4 pi m! s_A^(|m|+1)), Lt expanded from the reduced
-// locals Lr (see k_m2l_mfma), for |m| < the order of A's level; one thread
-// per (cell, m), fields in blockIdx.y.
-__global__ void k_lr_expand(const double *__restrict__ Lr, int lrs, const int32_t *__restrict__ cell_i, double side,
-                            int64_t C, int ncoef, LevelOrders lo, double *__restrict__ L)
+// L_m(A) = Lt_m(A) / (4 pi m! s_A^(|m|+1)), Lt expanded from the reduced
+// locals Lr (see k_m2l_mfma), for |m| < the order of A's level, 0 above.
+__global__ __launch_bounds__(256) void k_lr_expand(const double *__restrict__ Lr, int lrs,
+                                                   const int32_t *__restrict__ cell_i, double side, int64_t C, int p,
+                                                   LevelOrders lo, int cells, double *__restrict__ L)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= C * ncoef) return;
-    const int64_t A = i / ncoef;
-    const int m = (int)(i - A * ncoef), f = blockIdx.y;
-    const int lev = cell_i[CI_N * A + CI_LEVEL];
-    const int mx = c_mi.v[m][0], my = c_mi.v[m][1], mz = c_mi.v[m][2], dm = c_mi.v[m][3];
-    if (dm >= lo.q[lev]) return;
-    const double *red = Lr + ((int64_t)f * C + A) * lrs;
-    const int j = mz >> 1, cz = mz & 1;
-    double lt = 0.0;
-    for (int k = 0; k <= j; ++k) lt += c_bin.c[j][k] * red[ridx(mx + 2 * k, my + 2 * (j - k), cz)];
-    if (lt == 0.0) return;
-    if (j & 1) lt = -lt;
-    const double is = 1.0 / ldexp(side, -lev);
-    double sp = is;
-    for (int k = 0; k < dm; ++k) sp *= is;
-    L[((int64_t)f * C + A) * ncoef + m] += lt * kInv4Pi * sp * c_bin.invfact[mx] * c_bin.invfact[my] * c_bin.invfact[mz];
+    extern __shared__ double s_row[];
+    // outputs below order p only: their reduced locals are the lrs = p^2 of a row
+    const int ncoef = ncoef_of(p), nm = ncoef_of(p - 1), nterm = c_expand.start[nm], tid = threadIdx.x, f = blockIdx.y;
+    const RowLds S(s_row, lrs, nterm);
+    const int64_t c0 = (int64_t)blockIdx.x * cells;
+    const int n_c = (int)min<int64_t>(cells, C - c0);
+    const double *r = Lr + ((int64_t)f * C + c0) * lrs;
+    for (int i = tid; i < n_c * lrs; i += 256) S.in[i] = r[i];
+    for (int i = tid; i < nterm; i += 256) {
+        S.w[i] = c_expand.w[i];
+        S.at[i] = c_expand.at[i];
+    }
+    for (int i = tid; i <= nm; i += 256) S.start[i] = c_expand.start[i];
+    if (tid < n_c) {
+        const int lev = cell_i[CI_N * (c0 + tid) + CI_LEVEL];
+        const double is = 1.0 / ldexp(side, -lev);
+        double sp = is;
+        for (int d = 0; d <= p; ++d, sp *= is) S.scale[tid * (kPmax + 1) + d] = d < lo.q[lev] ? sp : 0.0;
+    }
+    __syncthreads();
+    double *out = L + ((int64_t)f * C + c0) * ncoef;
+    for (int i = tid; i < n_c * ncoef; i += 256) {
+        const int c = i / ncoef, m = i - c * ncoef;
+        double v = 0.0;
+        if (m < nm) {
+            const double sp = S.scale[c * (kPmax + 1) + c_mi.v[m][3]];
+            if (sp != 0.0) v = sp * S.sum(c, lrs, m);
+        }
+        out[i] = v;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1678,7 +1735,7 @@ __device__ __forceinline__ void far_moments(const double (&x)[3], const double (
 }
 
 template <int FCH>
-__global__ __launch_bounds__(256, 3) void k_direct(int nblk, int64_t T, const double *__restrict__ tet_xyz,
+__global__ __launch_bounds__(256, FCH <= 4 ? 3 : 2) void k_direct(int nblk, int64_t T, const double *__restrict__ tet_xyz,
                                                 const int32_t *__restrict__ tet_node,
                                                 const double *__restrict__ tgt_xyz,
                                                 const int32_t *__restrict__ tgt_perm, int64_t N,
@@ -3508,7 +3565,7 @@ void launch_m2l_p(DevicePlan &dp, const DevicePlan::Tiles &tl, const T *D, const
     const HostPlan &hp = dp.hp;
     const unsigned groups = (unsigned)((F + fpt - 1) / fpt);
     k_m2l_mfma<T, P><<<dim3(tl.ntiles, groups), dim3(64 * kM2LWaves), 0, st>>>(
-        tl.tile_tgt, tl.tile_rng, tl.ent_key, tl.ent_src, dp.m2l_keys, D, Qt, dp.qpad, dp.cell_i, hp.side,
+        tl.tile_tgt, tl.tile_rng, tl.ent_key, tl.ent_src, dp.m2l_keys, D, Qt, m2l_tile_row(hp.p), dp.cell_i, hp.side,
         (int64_t)hp.cells.size(), tl.tpt, fpt, F, tl.ntiles, m2l_table_width(hp.p), dp.ncoef, dp.L);
     hip_check(hipGetLastError(), "k_m2l_mfma launch");
 }
@@ -3606,6 +3663,9 @@ int m2l_pack_fpt(int32_t F)
 // every column used; the FP32 and split-BF16 tiles are faster than their
 // packed forms, whose few matrix-core cycles per group leave the LDS
 // accumulation as the bound).
+// Longest row of reduced multipoles over the forms of M2L.
+int m2l_row_max(const DevicePlan &dp) { return std::max(dp.qpad, m2l_tile_row(dp.hp.p)); }
+
 bool m2l_packed(const DevicePlan &dp, int32_t F)
 {
     return dp.m2l_pack && m2l_fpt(F) < 16 && dp.m2l_precision == TFMM_M2L_FP64;
@@ -3636,22 +3696,27 @@ void run_m2l(DevicePlan &dp, int32_t F, hipStream_t st)
     const HostPlan &hp = dp.hp;
     const int64_t C = (int64_t)hp.cells.size();
     const int fpt = m2l_fpt(F);
+    const bool packed = m2l_packed(dp, F);  // its locals replace L, the others add to it
+    if (!packed || hp.m2l_src.empty()) fill(dp.L, (int64_t)F * C * dp.ncoef, 0.0, st);
     if (hp.m2l_src.empty()) return;
-    const int64_t nq = C * dp.qpad;
-    const dim3 qgrid((unsigned)((nq + 255) / 256), F);
+    // the row form of the multipoles is that of the translation's kernel
+    const bool tiled = !packed && dp.m2l_precision <= TFMM_M2L_FP32;
+    const int qrow = tiled ? m2l_tile_row(hp.p) : dp.qpad, lrs = m2l_nrows(hp.p);
+    const int cells = row_cells(C, F);
+    const dim3 rgrid((unsigned)((C + cells - 1) / cells), F);
+    constexpr ReduceTable rt = make_reduce();
+    const size_t rlds = row_lds(dp.ncoef, rt.start[nr_of(hp.p)], nr_of(hp.p));
     if (dp.m2l_precision != TFMM_M2L_FP64) {  // FP32 operands (FP32, BF16x3, BF16x6)
         if (!dp.m2l_Df || dp.qtf_cap < F) throw DeviceError{"M2L buffers not prepared"};
-        k_qreduce<float><<<qgrid, dim3(256), 0, st>>>(dp.Q, dp.cell_i, C, hp.side, hp.p, dp.qpad, dp.Qtf);
+        k_qreduce<float><<<rgrid, dim3(256), rlds, st>>>(dp.Q, dp.cell_i, C, hp.side, hp.p, qrow, tiled, dp.Qtf, nullptr, 0, cells);
     } else {
-        if (dp.qt_cap < F) throw DeviceError{"M2L buffers not prepared"};
-        k_qreduce<double><<<qgrid, dim3(256), 0, st>>>(dp.Q, dp.cell_i, C, hp.side, hp.p, dp.qpad, dp.Qt);
+        if (dp.qt_cap < F || (packed && dp.lr_cap < F)) throw DeviceError{"M2L buffers not prepared"};
+        k_qreduce<double><<<rgrid, dim3(256), rlds, st>>>(dp.Q, dp.cell_i, C, hp.side, hp.p, qrow, tiled, dp.Qt,
+                                                          packed ? dp.Lr : nullptr, lrs, cells);
     }
     hip_check(hipGetLastError(), "k_qreduce launch");
-    if (m2l_packed(dp, F)) {
+    if (packed) {
         const int fpt = m2l_pack_fpt(F);
-        if (dp.lr_cap < F) throw DeviceError{"M2L buffers not prepared"};
-        const int lrs = m2l_nrows(hp.p);
-        fill(dp.Lr, (int64_t)F * C * lrs, 0.0, st);
         auto go = [&](const DevicePlan::Packs &k, int p) {
             launch_m2l_pack(dp, k, fpt, F, st, p);
         };
@@ -3660,9 +3725,10 @@ void run_m2l(DevicePlan &dp, int32_t F, hipStream_t st)
         } else {
             for (size_t lv = 0; lv < dp.lvl_packs.size(); ++lv) go(dp.lvl_packs[lv], dp.lo.q[lv]);
         }
-        const int64_t n = C * dp.ncoef;
-        k_lr_expand<<<dim3((unsigned)((n + 255) / 256), (unsigned)F), dim3(256), 0, st>>>(
-            dp.Lr, lrs, dp.cell_i, hp.side, C, dp.ncoef, dp.lo, dp.L);
+        constexpr ExpandTable et = make_expand();
+        const int nm = ncoef_of(hp.p - 1);
+        k_lr_expand<<<rgrid, dim3(256), row_lds(lrs, et.start[nm], nm), st>>>(dp.Lr, lrs, dp.cell_i, hp.side, C, hp.p,
+                                                                              dp.lo, cells, dp.L);
         hip_check(hipGetLastError(), "k_lr_expand launch");
         return;
     }
@@ -4016,6 +4082,9 @@ void ensure_expansions(DevicePlan &dp, int32_t F)
     const size_t bytes = sizeof(double) * (size_t)F * dp.hp.cells.size() * dp.ncoef;
     hip_check(hipMalloc(&dp.Q, bytes), "hipMalloc Q");
     hip_check(hipMalloc(&dp.L, bytes), "hipMalloc L");
+    // an evaluation writes the multipoles of every cell that holds sources; the others' stay 0
+    fill(dp.Q, (int64_t)(bytes / sizeof(double)), 0.0, nullptr);
+    hip_check(hipStreamSynchronize(nullptr), "clear Q");
     dp.Fcap = F;
 }
 
@@ -4062,7 +4131,7 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
             if (dp.Qtf) (void)hipFree(dp.Qtf);
             dp.Qtf = nullptr;
             dp.qtf_cap = 0;
-            hip_check(hipMalloc(&dp.Qtf, sizeof(float) * (size_t)F * C * dp.qpad), "hipMalloc Qt f32");
+            hip_check(hipMalloc(&dp.Qtf, sizeof(float) * (size_t)F * C * m2l_row_max(dp)), "hipMalloc Qt f32");
             dp.qtf_cap = F;
         }
     } else if (dp.qt_cap < F) {
@@ -4070,7 +4139,7 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
         if (dp.Qt) (void)hipFree(dp.Qt - 1);
         dp.Qt = nullptr;
         dp.qt_cap = 0;
-        hip_check(hipMalloc(&dp.Qt, sizeof(double) * ((size_t)F * C * dp.qpad + 2)), "hipMalloc Qt");
+        hip_check(hipMalloc(&dp.Qt, sizeof(double) * ((size_t)F * C * m2l_row_max(dp) + 2)), "hipMalloc Qt");
         dp.Qt += 1;  // entry 1 of every row (the first that counts) on a 16-byte boundary
         dp.qt_cap = F;
     }
@@ -4189,8 +4258,6 @@ void run_evaluate(DevicePlan &dp, const double *M, int32_t F, double *u, hipStre
         hip_check(hipEventRecord(dp.ev_join, dp.side), "hipEventRecord");
     };
     if (fork) fork_p2p();
-    fill(dp.Q, (int64_t)F * C * dp.ncoef, 0.0, st);
-    fill(dp.L, (int64_t)F * C * dp.ncoef, 0.0, st);
     {
         KTimer kt(dp, KT_P2M, st);
         if (dp.n_p2m_cells > 0) with_p2m(F, p, [&](auto fc, auto nt) {
