@@ -172,10 +172,11 @@ struct DevicePlan {
     // (expansions, scaled multipoles, M2L tiles), so that captured graphs
     // are rebuilt instead of replaying on freed memory
     uint64_t schedule_gen = 0;
-    // scaled multipoles Qt_n = (-1)^|n| Q_n / (n! s^|n|): [Fcap][C][qpad] (FP64 or FP32)
+    // scaled multipoles Qt_n = (-1)^|n| Q_n / (n! s^|n|), reduced, in the row form of
+    // the evaluation's M2L (k_qreduce), and the doubles or floats they have room for
     double *Qt = nullptr;
     float *Qtf = nullptr;
-    int32_t qt_cap = 0, qtf_cap = 0;
+    int64_t qt_cap = 0, qtf_cap = 0;
     int32_t qpad = 0;
     // P2P: blocks of <= 64 tets of one source leaf with their target list
     int32_t *p2p_blk = nullptr;  // [nblk][4]: tbeg, tend, ibeg, iend into p2p_idx

@@ -775,11 +775,25 @@ struct RowLds {
     }
 };
 
-// (Lr, where given: the accumulators of M2L, lrs a cell, cleared here)
-template <typename T>
+__device__ __forceinline__ void bf16_split3(float x, __bf16 &x0, __bf16 &x1, __bf16 &x2)
+{
+    x0 = (__bf16)x;
+    const float r1 = x - (float)x0;
+    x1 = (__bf16)r1;
+    x2 = (__bf16)(r1 - (float)x1);
+}
+
+// Row forms of the reduced multipoles, each the operand order of one form of M2L:
+// by n, len a cell and field (packed form); by wavefront of the tile form, field
+// of a group of fpt and place (m2l_tile_col), len = m2l_tile_row; and split in np
+// BF16 parts by column step, part, field of a group and n, len = 32 steps.
+enum { ROW_PLAIN, ROW_TILE, ROW_BF16 };
+
+// (Lr: the accumulators of M2L, lrs a cell, cleared here)
+template <int kForm, typename T>
 __global__ __launch_bounds__(256) void k_qreduce(const double *__restrict__ Q, const int32_t *__restrict__ cell_i,
-                                                 int64_t C, double side, int p, int row, bool tiled, T *__restrict__ Qr,
-                                                 double *__restrict__ Lr, int lrs, int cells)
+                                                 int64_t C, double side, int p, int len, int fpt, int np,
+                                                 T *__restrict__ Qr, double *__restrict__ Lr, int lrs, int cells)
 {
     extern __shared__ double s_row[];
     const int ncoef = ncoef_of(p), nr = nr_of(p), nterm = c_reduce.start[nr], tid = threadIdx.x, f = blockIdx.y;
@@ -800,18 +814,28 @@ __global__ __launch_bounds__(256) void k_qreduce(const double *__restrict__ Q, c
         for (int d = 0; d <= p; ++d, sp *= is) S.scale[tid * (kPmax + 1) + d] = sp;
     }
     __syncthreads();
-    T *out = Qr + ((int64_t)f * C + c0) * row;
-    for (int i = tid; i < n_c * row; i += 256) {
-        const int c = i / row, at = i - c * row, n = tiled ? m2l_tile_col(at, row) : at;
+    const int64_t cell = (int64_t)(f / fpt) * C + c0;  // first cell, in the rows of f's group
+    for (int i = tid; i < n_c * len; i += 256) {
+        const int c = i / len, at = i - c * len;
+        const int n = kForm == ROW_TILE ? m2l_tile_col(at, len) : (kForm == ROW_BF16 ? at + 1 : at);
         double v = 0.0;
         if (n < nr) {
             const double sp = S.scale[c * (kPmax + 1) + (int)sqrtf((float)n)];  // degree: exact, d starts at d^2
             if (sp != 0.0) v = sp * S.sum(c, ncoef, n);
         }
-        out[i] = (T)v;
+        if constexpr (kForm == ROW_PLAIN) {
+            Qr[((int64_t)f * C + c0) * len + i] = (T)v;
+        } else if constexpr (kForm == ROW_TILE) {
+            const int part = len / kM2LWaves;
+            Qr[(((cell + c) * kM2LWaves + at / part) * fpt + f % fpt) * part + at % part] = (T)v;
+        } else {
+            T x[3];
+            bf16_split3((float)v, x[0], x[1], x[2]);
+            T *o = Qr + (((cell + c) * (len / 32) + at / 32) * np * fpt + f % fpt) * 32 + at % 32;
+            for (int k = 0; k < np; ++k) o[(int64_t)k * fpt * 32] = x[k];
+        }
     }
-    if (Lr)
-        for (int i = tid; i < n_c * lrs; i += 256) Lr[((int64_t)f * C + c0) * lrs + i] = 0.0;
+    for (int i = tid; i < n_c * lrs; i += 256) Lr[((int64_t)f * C + c0) * lrs + i] = 0.0;
 }
 
 // Steps of wave W in issue order: column step ks = W, W + 4, ... (outer),
@@ -847,15 +871,14 @@ struct M2LCols {
     int dstr;  // row stride of the derivative tables (the plan's order; P may be lower)
 };
 
-constexpr int kM2LSeg = 128;  // M2L entries whose metadata is staged in LDS at once (BF16 form)
-
 // Column steps of wavefront W (see k_m2l_mfma): KJ of them, ks = W + kM2LWaves j,
 // whose multipoles lie together in a row of Qr (m2l_tile_slot).  The wavefronts
 // share nothing until their sums meet: each gathers its A operands from its own
 // copy of the key's derivative row in LDS and loads its B operands in place, two
 // entries ahead, in one of two register sets.  (With operands staged for all four
 // by all four, a barrier per entry, the matrix cores were busy 38% of the time;
-// F = 16, order 8, 1.4 million translations: 1.53 ms, now 1.45.)
+// F = 16, order 8, 1.4 million translations: 1.53 ms of M2L, now 1.06
+// with rows in whole lines.)
 template <typename T, int P, int W>
 __device__ __forceinline__ void m2l_tile(const int32_t *__restrict__ tile_rng, const int32_t *__restrict__ ent_key,
                                          const int32_t *__restrict__ ent_src, const int32_t *__restrict__ keys,
@@ -875,7 +898,10 @@ __device__ __forceinline__ void m2l_tile(const int32_t *__restrict__ tile_rng, c
         const int e0 = tile_rng[2 * tile], e1 = tile_rng[2 * tile + 1];
         if (e0 >= e1) return;
         const bool active = field < cols.F;
-        const T *qf = Qr + (int64_t)(active ? field : 0) * C * qrow + (W * 4 + kq) * (qrow / 16);
+        const int part = qrow / kM2LWaves;
+        const T *qf = Qr + (((int64_t)(cols.f0 / cols.fpt) * C * kM2LWaves + W) * cols.fpt + col % cols.fpt) * part +
+                      kq * (part / 4);
+        const int64_t stride = (int64_t)qrow * cols.fpt;  // a cell and field group
         auto source = [&](int e) { return ent_src[(int64_t)min(e, e1 - 1) * cols.tpt + tslot]; };
         auto key_of = [&](int e) { return ent_key[min(e, e1 - 1)]; };
         // Loads go to in-bounds addresses unconditionally and are masked when used.
@@ -886,7 +912,7 @@ __device__ __forceinline__ void m2l_tile(const int32_t *__restrict__ tile_rng, c
         };
         auto load = [&](Ops &o, int src, int key) {
             o.ok = active && src >= 0;
-            const T *q = qf + (int64_t)(o.ok ? src : 0) * qrow;
+            const T *q = qf + max(src, 0) * stride;
 #pragma unroll
             for (int j = 0; j < KJ; ++j) o.q[j] = q[j];
 #pragma unroll
@@ -974,11 +1000,11 @@ template <typename T, int P>
 __global__ __launch_bounds__(64 * kM2LWaves, sizeof(T) == 4 ? 4 : 2) void k_m2l_mfma(
     const int32_t *__restrict__ tile_tgt, const int32_t *__restrict__ tile_rng, const int32_t *__restrict__ ent_key,
     const int32_t *__restrict__ ent_src, const int32_t *__restrict__ keys, const T *__restrict__ Dtab,
-    const T *__restrict__ Qr, int qrow, const int32_t *__restrict__ cell_i, double side, int64_t C, int tpt, int fpt,
-    int F, int ntiles, int dstr, int lstr, double *__restrict__ L)
+    const T *__restrict__ Qr, int qrow, int64_t C, int tpt, int fpt, int F, int ntiles, int dstr,
+    double *__restrict__ Lr, int lrs)
 {
     using v4 = typename Mfma<T>::v4;
-    constexpr int NC = ncoef_of(P), NROW = m2l_nrows(P), ND = nd_of(P), NRT = m2l_nrt(P), RSTR = NROW | 1;
+    constexpr int NROW = m2l_nrows(P), ND = nd_of(P), NRT = m2l_nrt(P), RSTR = NROW | 1;
     static_assert(kM2LWaves == 4, "wave specialisation below");
     __shared__ T s_D[kM2LWaves][ND + 1];
     __shared__ double red[16 * RSTR];  // the waves' sums: red[c][m], c = column
@@ -1008,24 +1034,10 @@ __global__ __launch_bounds__(64 * kM2LWaves, sizeof(T) == 4 ? 4 : 2) void k_m2l_
             if (m < NROW) atomicAdd(&red[(lane & 15) * RSTR + m], (double)acc[rt][r]);
         }
     __syncthreads();
-    // expand to all m, then l_m(A) = Lt_m / (4 pi m! s_A^(|m|+1))
-    for (int i = tid; i < 16 * NC; i += blockDim.x) {
-        const int c = i / NC, m = i - c * NC;
-        const int field = cols.f0 + c % fpt;
+    for (int i = tid; i < 16 * NROW; i += blockDim.x) {
+        const int c = i / NROW, m = i - c * NROW, field = cols.f0 + c % fpt;
         const int A = tile_tgt[tile * tpt + c / fpt];
-        if (A < 0 || field >= F) continue;
-        const int mx = c_mi.v[m][0], my = c_mi.v[m][1], mz = c_mi.v[m][2], dm = c_mi.v[m][3];
-        double lt = 0.0;
-        if (dm < P) {
-            const int j = mz >> 1, cz = mz & 1;
-            for (int k = 0; k <= j; ++k) lt += c_bin.c[j][k] * red[c * RSTR + ridx(mx + 2 * k, my + 2 * (j - k), cz)];
-            if (j & 1) lt = -lt;
-        }
-        const double is = 1.0 / ldexp(side, -cell_i[CI_N * A + CI_LEVEL]);
-        double sp = is;
-        for (int k = 0; k < dm; ++k) sp *= is;
-        atomicAdd(&L[((int64_t)field * C + A) * lstr + m],
-                  lt * kInv4Pi * sp * c_bin.invfact[mx] * c_bin.invfact[my] * c_bin.invfact[mz]);
+        if (A >= 0 && field < F) atomicAdd(&Lr[((int64_t)field * C + A) * lrs + m], red[c * RSTR + m]);
     }
 }
 
@@ -1288,7 +1300,7 @@ __global__ __launch_bounds__(256) void k_lr_expand(const double *__restrict__ Lr
 // M2L with split BF16 operands on matrix cores (v_mfma_f32_16x16x32_bf16).
 //
 // The FP32 operands of the FP32 form (derivative rows and reduced multipoles,
-// all O(1) by the level scaling) are split as they are staged into LDS,
+// all O(1) by the level scaling) are split,
 // x = x0 + x1 + x2 with x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1)
 // (each difference exact in FP32), and the product is formed from the part
 // products of total order < NP: NP = 2 takes a0 b0 + a0 b1 + a1 b0 (BF16x3),
@@ -1296,10 +1308,18 @@ __global__ __launch_bounds__(256) void k_lr_expand(const double *__restrict__ Lr
 // Operand layout: A (16 x 32): lane l holds row l%16, columns 8(l/16) + i;
 // B (32 x 16): lane l holds rows 8(l/16) + i, column l%16; result as the
 // FP32 16x16x4 form (row 4(l/16) + r, column l%16).
-// Column steps are 32 wide (n = 1 + 32 ks + ...); the (row tile, step) pairs
-// are dealt to two wavefronts in turn.
+// Column steps are 32 wide (n = 1 + 32 ks + ...).  The sums of a row tile are kept
+// in two accumulators, of the even and of the odd (step, row tile) pairs, which
+// meet in FP64.
+//
+// One wavefront per tile and G field groups of 16 columns: the derivative parts of
+// a key are gathered once for G groups from the wavefront's copy in LDS, the
+// multipoles come split and in operand order from k_qreduce, straight into the
+// registers of the entry before as its matrix steps consume them.  (With two
+// wavefronts splitting and staging both operands for one group, the LDS was busy
+// 64% of the time and the matrix cores 10%: 64 fields, order 8, 1.1 million
+// translations, BF16x3: 6.3 ms of M2L, now 2.65.)
 // ---------------------------------------------------------------------------
-constexpr int kM2LBWaves = 2;
 using bf16x8 = __bf16 __attribute__((ext_vector_type(8)));
 
 __host__ __device__ constexpr int m2lb_ks(int P, int rt)
@@ -1308,227 +1328,197 @@ __host__ __device__ constexpr int m2lb_ks(int P, int rt)
     if (d >= P) return 0;
     return (nr_of(P - d) - 1 + 31) / 32;
 }
-__host__ __device__ constexpr int m2lb_kstr(int P) { return 32 * m2lb_ks(P, 0) + 8; }  // bf16 per staged column
-// number of (rt, ks) steps of wave W: steps in order ks-major, dealt in turn
-__host__ __device__ constexpr int m2lb_wave_steps(int P, int W)
+__host__ __device__ constexpr int m2lb_steps(int P)
 {
-    int s = 0, c = 0;
-    for (int ks = 0; ks < m2lb_ks(P, 0); ++ks)
-        for (int rt = 0; rt < m2l_nrt(P); ++rt)
-            if (ks < m2lb_ks(P, rt)) {
-                if (s % kM2LBWaves == W) ++c;
-                ++s;
-            }
-    return c;
-}
-// row tile and column step of the j-th step of wave W
-__host__ __device__ constexpr int m2lb_step(int P, int W, int j, bool want_rt)
-{
-    int s = 0, c = 0;
-    for (int ks = 0; ks < m2lb_ks(P, 0); ++ks)
-        for (int rt = 0; rt < m2l_nrt(P); ++rt)
-            if (ks < m2lb_ks(P, rt)) {
-                if (s % kM2LBWaves == W) {
-                    if (c == j) return want_rt ? rt : ks;
-                    ++c;
-                }
-                ++s;
-            }
-    return 0;
+    int s = 0;
+    for (int rt = 0; rt < m2l_nrt(P); ++rt) s += m2lb_ks(P, rt);
+    return s;
 }
 
-__device__ __forceinline__ void bf16_split3(float x, __bf16 &x0, __bf16 &x1, __bf16 &x2)
-{
-    x0 = (__bf16)x;
-    const float r1 = x - (float)x0;
-    x1 = (__bf16)r1;
-    x2 = (__bf16)(r1 - (float)x1);
-}
-
-template <int P, int NP, int W>
-__device__ __forceinline__ void m2lb_tile(const int32_t *__restrict__ tile_rng, const int32_t *__restrict__ ent_key,
-                                          const int32_t *__restrict__ ent_src, const int32_t *__restrict__ keys,
-                                          const float *__restrict__ Dtab, const float *__restrict__ Qr, int qpad,
-                                          int64_t C, M2LCols cols, int tile, __bf16 *s_D, __bf16 *s_Q,
-                                          int32_t *s_src, int32_t *s_kk, Mfma<float>::v4 (&acc)[m2l_nrt(P)])
-{
-    constexpr int NR = nr_of(P), NROW = m2l_nrows(P), ND = nd_of(P), KSTR = m2lb_kstr(P), DSTR = ND + 1;
-    constexpr int NT = 64 * kM2LBWaves, NS = m2lb_wave_steps(P, W);
-    static_assert(NT % 16 == 0, "16 columns");
-    constexpr int TPC = NT / 16;  // staging threads per column
-    constexpr int QREG = (NR + TPC - 1) / TPC, DREG = (ND + NT - 1) / NT;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int tcol = tid / TPC, tn = tid % TPC;
-    const int tslot = tcol / cols.fpt, field = cols.f0 + tcol % cols.fpt;
-    // A-operand table indices of this lane, per step (the zero slot ND outside |n| + |m| <= P)
-    int didx[NS > 0 ? NS : 1][8];
-#pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        const int rt = m2lb_step(P, W, j, true), ks = m2lb_step(P, W, j, false);
-        const int m = 16 * rt + (lane & 15);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int n = 1 + 32 * ks + 8 * (lane >> 4) + i;
-            int di = ND;
-            if (m < NROW && n < NR && c_red.r[m][3] + c_red.r[n][3] <= P)
-                di = didx_of(c_red.r[m][0] + c_red.r[n][0], c_red.r[m][1] + c_red.r[n][1], c_red.r[m][2] + c_red.r[n][2]);
-            didx[j][i] = di;
-        }
-    }
-    const int e0 = tile_rng[2 * tile], e1 = tile_rng[2 * tile + 1];
-    float pq[QREG], pd[DREG];
-    int pdl = 0, qdeg[QREG];
-#pragma unroll
-    for (int j = 0; j < QREG; ++j) qdeg[j] = rdeg(tn + TPC * j);
-    // entry metadata staged in LDS by segments, loads as in m2l_tile
-    const bool active = field < cols.F;
-    const float *qf = Qr + (int64_t)(active ? field : 0) * C * qpad;
-    int seg = e0;
-    auto stage_seg = [&]() {
-        const int ne = min(e1 - seg, kM2LSeg + 1);
-        for (int i = tid; i < ne * cols.tpt; i += NT) s_src[i] = ent_src[(int64_t)seg * cols.tpt + i];
-        for (int i = tid; i < ne; i += NT) {
-            const int key = ent_key[seg + i];
-            s_kk[2 * i] = key;
-            s_kk[2 * i + 1] = keys[4 * key];
-        }
-    };
-    bool qok = false;
-    auto fetch = [&](int e) {
-        const int r = e - seg;
-        const int key = s_kk[2 * r];
-        pdl = s_kk[2 * r + 1];
-        const int src = s_src[r * cols.tpt + tslot];
-#pragma unroll
-        for (int j = 0; j < DREG; ++j) {
-            const int k = tid + NT * j;
-            pd[j] = Dtab[(int64_t)key * cols.dstr + (k < ND ? k : ND - 1)];
-        }
-        qok = active && src >= 0;
-        const float *q = qf + (int64_t)(qok ? src : 0) * qpad;
-#pragma unroll
-        for (int j = 0; j < QREG; ++j) {
-            const int n = tn + TPC * j;
-            pq[j] = q[n < NR ? n : NR - 1];
-        }
-    };
-    auto store = [&](int buf) {
-        __bf16 *D = s_D + buf * 3 * DSTR;
-#pragma unroll
-        for (int j = 0; j < DREG; ++j) {
-            const int k = tid + NT * j;
-            if (k < ND) bf16_split3(pd[j], D[k], D[DSTR + k], D[2 * DSTR + k]);
-        }
-        __bf16 *Qb = s_Q + buf * 3 * 16 * KSTR + tcol * KSTR;
-#pragma unroll
-        for (int j = 0; j < QREG; ++j) {
-            const int n = tn + TPC * j;
-            if (n >= 1 && n < NR)  // column n is stored at n - 1
-                bf16_split3(qok ? ldexpf(pq[j], -pdl * qdeg[j]) : 0.0f, Qb[n - 1], Qb[16 * KSTR + n - 1],
-                            Qb[32 * KSTR + n - 1]);
-        }
-    };
-    if (e0 >= e1) return;
-    stage_seg();
-    __syncthreads();
-    fetch(e0);
-    store(0);
-    __syncthreads();
-    for (int e = e0; e < e1; ++e) {
-        const int buf = (e - e0) & 1;
-        if (e + 1 < e1) fetch(e + 1);
-        const __bf16 *D = s_D + buf * 3 * DSTR;
-        const __bf16 *Qb = s_Q + buf * 3 * 16 * KSTR + (lane & 15) * KSTR + 8 * (lane >> 4);
-#pragma unroll
-        for (int j = 0; j < NS; ++j) {
-            const int rt = m2lb_step(P, W, j, true), ks = m2lb_step(P, W, j, false);
-            bf16x8 a[NP], b[NP];
-#pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                b[q] = *reinterpret_cast<const bf16x8 *>(Qb + q * 16 * KSTR + 32 * ks);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) a[q][i] = D[q * DSTR + didx[j][i]];
-            }
-            // smallest terms first
-            if constexpr (NP == 3) {
-                acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0], acc[rt], 0, 0, 0);
-                acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2], acc[rt], 0, 0, 0);
-                acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1], acc[rt], 0, 0, 0);
-            }
-            acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0], acc[rt], 0, 0, 0);
-            acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1], acc[rt], 0, 0, 0);
-            acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0], acc[rt], 0, 0, 0);
-        }
-        if (e + 1 < e1) store(buf ^ 1);
-        __syncthreads();
-        if (e + 1 - seg == kM2LSeg && e + 1 < e1) {
-            seg = e + 1;
-            stage_seg();
-            __syncthreads();
-        }
-    }
-}
-
-template <int P, int NP>
-__global__ __launch_bounds__(64 * kM2LBWaves, 2) void k_m2l_bf16(
+template <int P, int NP, int G>
+__global__ __launch_bounds__(64, 2) void k_m2l_bf16(
     const int32_t *__restrict__ tile_tgt, const int32_t *__restrict__ tile_rng, const int32_t *__restrict__ ent_key,
-    const int32_t *__restrict__ ent_src, const int32_t *__restrict__ keys, const float *__restrict__ Dtab,
-    const float *__restrict__ Qr, int qpad, const int32_t *__restrict__ cell_i, double side, int64_t C, int tpt, int fpt,
-    int F, int ntiles, int dstr, int lstr, double *__restrict__ L)
+    const int32_t *__restrict__ ent_src, const int32_t *__restrict__ keys, const float *__restrict__ Dtab, int dstr,
+    const __bf16 *__restrict__ Qb, int ksp, int64_t C, int tpt, int fpt, int fg0, int F, int ntiles,
+    double *__restrict__ Lr, int lrs)
 {
     using v4 = Mfma<float>::v4;
-    constexpr int NC = ncoef_of(P), NROW = m2l_nrows(P), ND = nd_of(P), NRT = m2l_nrt(P), KSTR = m2lb_kstr(P);
-    constexpr int RSTR = NROW + 1;  // reduction buffer row stride (doubles)
-    static_assert(kM2LBWaves == 2, "wave specialisation below");
-    static_assert(16 * RSTR * sizeof(double) <= 2 * 3 * 16 * KSTR * sizeof(__bf16), "reduction buffer fits");
-    __shared__ __bf16 s_D[2 * 3 * (ND + 1)];
-    __shared__ __align__(16) __bf16 s_Q[2 * 3 * 16 * KSTR];
-    __shared__ int32_t s_src[(kM2LSeg + 1) * 16], s_kk[2 * (kM2LSeg + 1)];
+    constexpr int NR = nr_of(P), NROW = m2l_nrows(P), ND = nd_of(P), NRT = m2l_nrt(P), KS = m2lb_ks(P, 0);
+    constexpr int NS = m2lb_steps(P), DW = NP == 3 ? 2 : 1, RSTR = NROW | 1, DREG = (ND + 63) / 64;
+    __shared__ uint32_t s_D[(ND + 1) * DW];  // parts 0 and 1 of an entry in a word, part 2 in the next
+    __shared__ double red[16 * RSTR];
     const int tile = blockIdx.x;
     if (tile >= ntiles) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const M2LCols cols{tpt, fpt, (int)blockIdx.y * fpt, F, dstr};
-    for (int i = tid; i < 2 * 3 * 16 * KSTR; i += blockDim.x) s_Q[i] = (__bf16)0.0f;  // padding stays zero
-    for (int i = tid; i < 2 * 3 * (ND + 1); i += blockDim.x) s_D[i] = (__bf16)0.0f;   // zero slots
-    __syncthreads();
-    v4 acc[NRT];
+    const int lane = threadIdx.x, col = lane & 15, kq = lane >> 4, tslot = col / fpt, fsub = col % fpt;
+    const int e0 = tile_rng[2 * tile], e1 = tile_rng[2 * tile + 1];
+    if (e0 >= e1) return;
+    const int fg = fg0 + (int)blockIdx.y * G;  // first field group
+    if (lane < DW) s_D[ND * DW + lane] = 0;    // the zero slot
+    // byte offsets in s_D of this lane's A operand elements, two to a register (the zero slot outside |n| + |m| <= P)
+    uint32_t at[NS][4];
+    {
+        int s = 0;
 #pragma unroll
-    for (int rt = 0; rt < NRT; ++rt) acc[rt] = v4{0, 0, 0, 0};
-    if (wave == 0)
-        m2lb_tile<P, NP, 0>(tile_rng, ent_key, ent_src, keys, Dtab, Qr, qpad, C, cols, tile, s_D, s_Q, s_src, s_kk,
-                            acc);
-    else
-        m2lb_tile<P, NP, 1>(tile_rng, ent_key, ent_src, keys, Dtab, Qr, qpad, C, cols, tile, s_D, s_Q, s_src, s_kk,
-                            acc);
-    __syncthreads();
-    double *red = reinterpret_cast<double *>(s_Q);
-    for (int i = tid; i < 16 * RSTR; i += blockDim.x) red[i] = 0.0;
-    __syncthreads();
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-    for (int rt = 0; rt < NRT; ++rt)
+            for (int rt = 0; rt < NRT; ++rt)
+                if (ks < m2lb_ks(P, rt)) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int m = 16 * rt + Mfma<float>::row(lane, r);
-            if (m < NROW) atomicAdd(&red[(lane & 15) * RSTR + m], (double)acc[rt][r]);
+                    for (int h = 0; h < 4; ++h) {
+                        uint32_t o = 0;
+#pragma unroll
+                        for (int i = 2 * h; i < 2 * h + 2; ++i) {
+                            const int m = 16 * rt + col, n = 1 + 32 * ks + 8 * kq + i;
+                            int di = ND;
+                            if (m < NROW && n < NR && c_red.r[m][3] + c_red.r[n][3] <= P)
+                                di = didx_of(c_red.r[m][0] + c_red.r[n][0], c_red.r[m][1] + c_red.r[n][1],
+                                             c_red.r[m][2] + c_red.r[n][2]);
+                            o |= (uint32_t)(di * DW * 4) << (16 * (i & 1));
+                        }
+                        at[s][h] = o;
+                    }
+                    ++s;
+                }
+    }
+    const int64_t row = (int64_t)ksp * NP * fpt * 32;  // a cell and field group
+    const __bf16 *qb = Qb + (int64_t)fg * C * row + fsub * 32 + kq * 8;
+    auto source = [&](int e) { return ent_src[(int64_t)min(e, e1 - 1) * tpt + tslot]; };
+    auto key_of = [&](int e) { return ent_key[min(e, e1 - 1)]; };
+    bf16x8 b[G][KS][NP];
+    auto load = [&](int src, int ks) {  // in-bounds unconditionally, masked when used
+        const __bf16 *q = qb + (int64_t)max(src, 0) * row + ks * NP * fpt * 32;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int k = 0; k < NP; ++k) b[g][ks][k] = *reinterpret_cast<const bf16x8 *>(q + g * C * row + k * fpt * 32);
+    };
+    float d[DREG];
+    auto fetch_row = [&](int key) {
+#pragma unroll
+        for (int j = 0; j < DREG; ++j) d[j] = Dtab[(int64_t)key * dstr + min(lane + 64 * j, ND - 1)];
+    };
+    auto stage = [&]() {  // a wavefront's LDS operations keep their order
+#pragma unroll
+        for (int j = 0; j < DREG; ++j) {
+            __bf16 x[3];
+            bf16_split3(d[j], x[0], x[1], x[2]);
+            const uint32_t lo = __builtin_bit_cast(uint16_t, x[0]) | (uint32_t)__builtin_bit_cast(uint16_t, x[1]) << 16;
+            if (lane + 64 * j < ND) {
+                s_D[(lane + 64 * j) * DW] = lo;
+                if constexpr (NP == 3) s_D[(lane + 64 * j) * DW + 1] = __builtin_bit_cast(uint16_t, x[2]);
+            }
         }
-    __syncthreads();
-    for (int i = tid; i < 16 * NC; i += blockDim.x) {
-        const int c = i / NC, m = i - c * NC;
-        const int field = cols.f0 + c % fpt;
-        const int A = tile_tgt[tile * tpt + c / fpt];
-        if (A < 0 || field >= F) continue;
-        const int mx = c_mi.v[m][0], my = c_mi.v[m][1], mz = c_mi.v[m][2], dm = c_mi.v[m][3];
-        double lt = 0.0;
-        if (dm < P) {
-            const int j = mz >> 1, cz = mz & 1;
-            for (int k = 0; k <= j; ++k) lt += c_bin.c[j][k] * red[c * RSTR + ridx(mx + 2 * k, my + 2 * (j - k), cz)];
-            if (j & 1) lt = -lt;
+    };
+    v4 acc[G][2][NRT];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int rt = 0; rt < NRT; ++rt) acc[g][0][rt] = acc[g][1][rt] = v4{0, 0, 0, 0};
+    int src = source(e0), src1 = source(e0 + 1), key = key_of(e0), key1 = key_of(e0 + 1);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) load(src, ks);
+    fetch_row(key);
+    stage();
+    for (int e = e0; e < e1; ++e) {
+        const int src2 = source(e + 2), key2 = key_of(e + 2), dl = keys[4 * key];
+        fetch_row(key1);
+        if (tpt > 1) {  // columns without a source
+            const uint32_t keep = src >= 0 ? 0xffffffffu : 0u;
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                    for (int k = 0; k < NP; ++k) {
+                        using u4 = uint32_t __attribute__((ext_vector_type(4)));
+                        b[g][ks][k] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u4, b[g][ks][k]) & keep);
+                    }
         }
-        const double is = 1.0 / ldexp(side, -cell_i[CI_N * A + CI_LEVEL]);
-        double sp = is;
-        for (int k = 0; k < dm; ++k) sp *= is;
-        atomicAdd(&L[((int64_t)field * C + A) * lstr + m],
-                  lt * kInv4Pi * sp * c_bin.invfact[mx] * c_bin.invfact[my] * c_bin.invfact[mz]);
+        if (dl != 0) {  // uniform; 2^(-dl |n|), exact
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int deg = (int)sqrtf((float)(1 + 32 * ks + 8 * kq + i));  // exact: degree d starts at d^2
+#pragma unroll
+                    for (int g = 0; g < G; ++g)
+#pragma unroll
+                        for (int k = 0; k < NP; ++k) b[g][ks][k][i] = (__bf16)ldexpf((float)b[g][ks][k][i], -dl * deg);
+                }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        int s = 0;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+            for (int rt = 0; rt < NRT; ++rt)
+                if (ks < m2lb_ks(P, rt)) {
+                    uint32_t w[8], w2[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const uint32_t *p = (const uint32_t *)((const char *)s_D + (i & 1 ? at[s][i / 2] >> 16 : at[s][i / 2] & 0xffffu));
+                        w[i] = p[0];
+                        if constexpr (NP == 3) w2[i] = p[1];
+                    }
+                    using u4 = uint32_t __attribute__((ext_vector_type(4)));
+                    bf16x8 a[NP];
+                    u4 q0, q1, q2;
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        q0[h] = __builtin_amdgcn_perm(w[2 * h + 1], w[2 * h], 0x05040100u);
+                        q1[h] = __builtin_amdgcn_perm(w[2 * h + 1], w[2 * h], 0x07060302u);
+                        if constexpr (NP == 3) q2[h] = w2[2 * h] | w2[2 * h + 1] << 16;
+                    }
+                    a[0] = __builtin_bit_cast(bf16x8, q0);
+                    a[1] = __builtin_bit_cast(bf16x8, q1);
+                    if constexpr (NP == 3) a[2] = __builtin_bit_cast(bf16x8, q2);
+                    auto mma = [&](int i, int k) {
+#pragma unroll
+                        for (int g = 0; g < G; ++g)
+                            acc[g][s & 1][rt] =
+                                __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[g][ks][k], acc[g][s & 1][rt], 0, 0, 0);
+                    };
+                    // smallest terms first
+                    if constexpr (NP == 3) {
+                        mma(2, 0);
+                        mma(0, 2);
+                        mma(1, 1);
+                    }
+                    mma(1, 0);
+                    mma(0, 1);
+                    mma(0, 0);
+                    ++s;
+                }
+            load(src1, ks);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        stage();
+        src = src1;
+        src1 = src2;
+        key = key1;
+        key1 = key2;
+    }
+    // the groups' sums, through LDS in whole rows, to Lr
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = 16 * rt + Mfma<float>::row(lane, r);
+                if (m < NROW) red[col * RSTR + m] = (double)acc[g][0][rt][r] + (double)acc[g][1][rt][r];
+            }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int i = lane; i < 16 * NROW; i += 64) {
+            const int c = i / NROW, m = i - c * NROW, field = (fg + g) * fpt + c % fpt;
+            const int A = tile_tgt[tile * tpt + c / fpt];
+            if (A >= 0 && field < F) atomicAdd(&Lr[((int64_t)field * C + A) * lrs + m], red[c * RSTR + m]);
+        }
     }
 }
 
@@ -3565,41 +3555,35 @@ void launch_m2l_p(DevicePlan &dp, const DevicePlan::Tiles &tl, const T *D, const
     const HostPlan &hp = dp.hp;
     const unsigned groups = (unsigned)((F + fpt - 1) / fpt);
     k_m2l_mfma<T, P><<<dim3(tl.ntiles, groups), dim3(64 * kM2LWaves), 0, st>>>(
-        tl.tile_tgt, tl.tile_rng, tl.ent_key, tl.ent_src, dp.m2l_keys, D, Qt, m2l_tile_row(hp.p), dp.cell_i, hp.side,
-        (int64_t)hp.cells.size(), tl.tpt, fpt, F, tl.ntiles, m2l_table_width(hp.p), dp.ncoef, dp.L);
+        tl.tile_tgt, tl.tile_rng, tl.ent_key, tl.ent_src, dp.m2l_keys, D, Qt, m2l_tile_row(hp.p),
+        (int64_t)hp.cells.size(), tl.tpt, fpt, F, tl.ntiles, m2l_table_width(hp.p), dp.Lr, m2l_nrows(hp.p));
     hip_check(hipGetLastError(), "k_m2l_mfma launch");
 }
 
-template <int P, int NP>
-void launch_m2lb_p(DevicePlan &dp, const DevicePlan::Tiles &tl, const float *D, const float *Qt, int fpt, int32_t F,
-                   hipStream_t st)
+// BF16 form: field groups two at a time, an odd last one alone; one at a time
+// above order 8, where two groups' multipoles do not fit in the registers.
+template <int NP>
+void launch_m2lb(DevicePlan &dp, const DevicePlan::Tiles &tl, int fpt, int32_t F, hipStream_t st, int p)
 {
     const HostPlan &hp = dp.hp;
-    const unsigned groups = (unsigned)((F + fpt - 1) / fpt);
-    k_m2l_bf16<P, NP><<<dim3(tl.ntiles, groups), dim3(64 * kM2LBWaves), 0, st>>>(
-        tl.tile_tgt, tl.tile_rng, tl.ent_key, tl.ent_src, dp.m2l_keys, D, Qt, dp.qpad, dp.cell_i, hp.side,
-        (int64_t)hp.cells.size(), tl.tpt, fpt, F, tl.ntiles, m2l_table_width(hp.p), dp.ncoef, dp.L);
-    hip_check(hipGetLastError(), "k_m2l_bf16 launch");
-}
-
-// (p: the order of the translation, the plan's or a level's)
-template <int NP>
-void launch_m2lb_t(DevicePlan &dp, const DevicePlan::Tiles &tl, const float *D, const float *Qt, int fpt, int32_t F,
-                   hipStream_t st, int p)
-{
-    switch (p) {
-    case 1: launch_m2lb_p<1, NP>(dp, tl, D, Qt, fpt, F, st); break;
-    case 2: launch_m2lb_p<2, NP>(dp, tl, D, Qt, fpt, F, st); break;
-    case 3: launch_m2lb_p<3, NP>(dp, tl, D, Qt, fpt, F, st); break;
-    case 4: launch_m2lb_p<4, NP>(dp, tl, D, Qt, fpt, F, st); break;
-    case 5: launch_m2lb_p<5, NP>(dp, tl, D, Qt, fpt, F, st); break;
-    case 6: launch_m2lb_p<6, NP>(dp, tl, D, Qt, fpt, F, st); break;
-    case 7: launch_m2lb_p<7, NP>(dp, tl, D, Qt, fpt, F, st); break;
-    case 8: launch_m2lb_p<8, NP>(dp, tl, D, Qt, fpt, F, st); break;
-    case 9: launch_m2lb_p<9, NP>(dp, tl, D, Qt, fpt, F, st); break;
-    case 10: launch_m2lb_p<10, NP>(dp, tl, D, Qt, fpt, F, st); break;
-    default: throw DeviceError{"unsupported expansion order"};
-    }
+    const int groups = (F + fpt - 1) / fpt, pairs = groups / 2;
+    with_order(p, [&](auto pc) {
+        constexpr int P = decltype(pc)::value;
+        auto go = [&](auto gc, int fg0, int n) {
+            constexpr int G = decltype(gc)::value;
+            k_m2l_bf16<P, NP, G><<<dim3(tl.ntiles, (unsigned)n), dim3(64), 0, st>>>(
+                tl.tile_tgt, tl.tile_rng, tl.ent_key, tl.ent_src, dp.m2l_keys, dp.m2l_Df, m2l_table_width(hp.p),
+                reinterpret_cast<const __bf16 *>(dp.Qtf), m2lb_ks(hp.p, 0), (int64_t)hp.cells.size(), tl.tpt, fpt, fg0, F,
+                tl.ntiles, dp.Lr, m2l_nrows(hp.p));
+            hip_check(hipGetLastError(), "k_m2l_bf16 launch");
+        };
+        if constexpr (P <= 8) {
+            if (pairs) go(std::integral_constant<int, 2>{}, 0, pairs);
+            if (groups & 1) go(std::integral_constant<int, 1>{}, 2 * pairs, 1);
+        } else {
+            go(std::integral_constant<int, 1>{}, 0, groups);
+        }
+    });
 }
 
 template <typename T>
@@ -3663,13 +3647,28 @@ int m2l_pack_fpt(int32_t F)
 // every column used; the FP32 and split-BF16 tiles are faster than their
 // packed forms, whose few matrix-core cycles per group leave the LDS
 // accumulation as the bound).
-// Longest row of reduced multipoles over the forms of M2L.
-int m2l_row_max(const DevicePlan &dp) { return std::max(dp.qpad, m2l_tile_row(dp.hp.p)); }
-
 bool m2l_packed(const DevicePlan &dp, int32_t F)
 {
     return dp.m2l_pack && m2l_fpt(F) < 16 && dp.m2l_precision == TFMM_M2L_FP64;
 }
+
+// Row form of the reduced multipoles of an evaluation of F fields (see k_qreduce).
+struct QRows {
+    int form, len, fpt, np;
+    int64_t count;  // numbers of all fields and cells (np parts of BF16 each)
+};
+static QRows q_rows(const DevicePlan &dp, int32_t F)
+{
+    const int64_t C = (int64_t)dp.hp.cells.size();
+    if (m2l_packed(dp, F)) return {ROW_PLAIN, dp.qpad, 1, 1, F * C * dp.qpad};
+    const int fpt = m2l_fpt(F);
+    const int64_t cells = (int64_t)((F + fpt - 1) / fpt) * fpt * C;
+    if (dp.m2l_precision <= TFMM_M2L_FP32) return {ROW_TILE, m2l_tile_row(dp.hp.p), fpt, 1, cells * m2l_tile_row(dp.hp.p)};
+    const int len = 32 * m2lb_ks(dp.hp.p, 0);
+    return {ROW_BF16, len, fpt, dp.m2l_precision == TFMM_M2L_BF16X3 ? 2 : 3, cells * len};
+}
+// elements of the buffer they take: doubles of Qt or floats of Qtf
+static int64_t q_elems(const QRows &q) { return q.form == ROW_BF16 ? (q.count * q.np + 1) / 2 : q.count; }
 int m2l_pack_slot(int fpt)
 {
     int s = 0;
@@ -3682,9 +3681,9 @@ void launch_m2l_tiles(DevicePlan &dp, const DevicePlan::Tiles &tl, int fpt, int3
 {
     if (tl.ntiles == 0) return;
     if (dp.m2l_precision == TFMM_M2L_BF16X3)
-        launch_m2lb_t<2>(dp, tl, dp.m2l_Df, dp.Qtf, fpt, F, st, p);
+        launch_m2lb<2>(dp, tl, fpt, F, st, p);
     else if (dp.m2l_precision == TFMM_M2L_BF16X6)
-        launch_m2lb_t<3>(dp, tl, dp.m2l_Df, dp.Qtf, fpt, F, st, p);
+        launch_m2lb<3>(dp, tl, fpt, F, st, p);
     else if (dp.m2l_precision == TFMM_M2L_FP32)
         launch_m2l_t<float>(dp, tl, dp.m2l_Df, dp.Qtf, fpt, F, st, p);
     else
@@ -3695,51 +3694,52 @@ void run_m2l(DevicePlan &dp, int32_t F, hipStream_t st)
 {
     const HostPlan &hp = dp.hp;
     const int64_t C = (int64_t)hp.cells.size();
-    const int fpt = m2l_fpt(F);
-    const bool packed = m2l_packed(dp, F);  // its locals replace L, the others add to it
-    if (!packed || hp.m2l_src.empty()) fill(dp.L, (int64_t)F * C * dp.ncoef, 0.0, st);
-    if (hp.m2l_src.empty()) return;
-    // the row form of the multipoles is that of the translation's kernel
-    const bool tiled = !packed && dp.m2l_precision <= TFMM_M2L_FP32;
-    const int qrow = tiled ? m2l_tile_row(hp.p) : dp.qpad, lrs = m2l_nrows(hp.p);
-    const int cells = row_cells(C, F);
+    if (hp.m2l_src.empty()) {
+        fill(dp.L, (int64_t)F * C * dp.ncoef, 0.0, st);
+        return;
+    }
+    const bool fp64 = dp.m2l_precision == TFMM_M2L_FP64;
+    const QRows q = q_rows(dp, F);
+    if (dp.lr_cap < F || (fp64 ? dp.qt_cap : dp.qtf_cap) < q_elems(q) || (!fp64 && !dp.m2l_Df))
+        throw DeviceError{"M2L buffers not prepared"};
+    const int cells = row_cells(C, F), lrs = m2l_nrows(hp.p);
     const dim3 rgrid((unsigned)((C + cells - 1) / cells), F);
     constexpr ReduceTable rt = make_reduce();
     const size_t rlds = row_lds(dp.ncoef, rt.start[nr_of(hp.p)], nr_of(hp.p));
-    if (dp.m2l_precision != TFMM_M2L_FP64) {  // FP32 operands (FP32, BF16x3, BF16x6)
-        if (!dp.m2l_Df || dp.qtf_cap < F) throw DeviceError{"M2L buffers not prepared"};
-        k_qreduce<float><<<rgrid, dim3(256), rlds, st>>>(dp.Q, dp.cell_i, C, hp.side, hp.p, qrow, tiled, dp.Qtf, nullptr, 0, cells);
-    } else {
-        if (dp.qt_cap < F || (packed && dp.lr_cap < F)) throw DeviceError{"M2L buffers not prepared"};
-        k_qreduce<double><<<rgrid, dim3(256), rlds, st>>>(dp.Q, dp.cell_i, C, hp.side, hp.p, qrow, tiled, dp.Qt,
-                                                          packed ? dp.Lr : nullptr, lrs, cells);
-    }
+    auto reduce = [&](auto form, auto *rows) {
+        k_qreduce<decltype(form)::value><<<rgrid, dim3(256), rlds, st>>>(dp.Q, dp.cell_i, C, hp.side, hp.p, q.len, q.fpt, q.np,
+                                                                         rows, dp.Lr, lrs, cells);
+    };
+    if (q.form == ROW_PLAIN)
+        reduce(std::integral_constant<int, ROW_PLAIN>{}, dp.Qt);
+    else if (q.form == ROW_BF16)
+        reduce(std::integral_constant<int, ROW_BF16>{}, reinterpret_cast<__bf16 *>(dp.Qtf));
+    else if (fp64)
+        reduce(std::integral_constant<int, ROW_TILE>{}, dp.Qt);
+    else
+        reduce(std::integral_constant<int, ROW_TILE>{}, dp.Qtf);
     hip_check(hipGetLastError(), "k_qreduce launch");
-    if (packed) {
+    // with per-level orders, one launch per target level at that level's order
+    // (the source multipoles already hold no terms above their own level's)
+    if (q.form == ROW_PLAIN) {
         const int fpt = m2l_pack_fpt(F);
-        auto go = [&](const DevicePlan::Packs &k, int p) {
-            launch_m2l_pack(dp, k, fpt, F, st, p);
-        };
+        auto go = [&](const DevicePlan::Packs &k, int p) { launch_m2l_pack(dp, k, fpt, F, st, p); };
         if (!dp.level_orders) {
             go(dp.m2l_packs[m2l_pack_slot(fpt)], hp.p);
         } else {
             for (size_t lv = 0; lv < dp.lvl_packs.size(); ++lv) go(dp.lvl_packs[lv], dp.lo.q[lv]);
         }
-        constexpr ExpandTable et = make_expand();
-        const int nm = ncoef_of(hp.p - 1);
-        k_lr_expand<<<rgrid, dim3(256), row_lds(lrs, et.start[nm], nm), st>>>(dp.Lr, lrs, dp.cell_i, hp.side, C, hp.p,
-                                                                              dp.lo, cells, dp.L);
-        hip_check(hipGetLastError(), "k_lr_expand launch");
-        return;
+    } else if (!dp.level_orders) {
+        launch_m2l_tiles(dp, ensure_m2l_tiles(dp, 16 / q.fpt), q.fpt, F, st, hp.p);
+    } else {
+        const std::vector<DevicePlan::Tiles> &lt = ensure_m2l_level_tiles(dp, 16 / q.fpt);
+        for (size_t lv = 0; lv < lt.size(); ++lv) launch_m2l_tiles(dp, lt[lv], q.fpt, F, st, dp.lo.q[lv]);
     }
-    if (!dp.level_orders) {
-        launch_m2l_tiles(dp, ensure_m2l_tiles(dp, 16 / fpt), fpt, F, st, hp.p);
-        return;
-    }
-    // per-level orders: one launch per target level at that level's order
-    // (the source multipoles already hold no terms above their own level's)
-    const std::vector<DevicePlan::Tiles> &lt = ensure_m2l_level_tiles(dp, 16 / fpt);
-    for (size_t lv = 0; lv < lt.size(); ++lv) launch_m2l_tiles(dp, lt[lv], fpt, F, st, dp.lo.q[lv]);
+    constexpr ExpandTable et = make_expand();
+    const int nm = ncoef_of(hp.p - 1);
+    k_lr_expand<<<rgrid, dim3(256), row_lds(lrs, et.start[nm], nm), st>>>(dp.Lr, lrs, dp.cell_i, hp.side, C, hp.p, dp.lo,
+                                                                          cells, dp.L);
+    hip_check(hipGetLastError(), "k_lr_expand launch");
 }
 
 }  // namespace
@@ -4038,14 +4038,6 @@ static void ensure_m2l_packs(DevicePlan &dp, int32_t F)
             for (int lv = 0; lv <= hp.depth; ++lv) build_packs(dp, fpt, F, dp.lo.q[lv], lv, dp.lvl_packs[lv]);
         }
     }
-    if (dp.lr_cap < F) {
-        ++dp.schedule_gen;
-        if (dp.Lr) (void)hipFree(dp.Lr);
-        dp.Lr = nullptr;
-        dp.lr_cap = 0;
-        hip_check(hipMalloc(&dp.Lr, sizeof(double) * (size_t)F * hp.cells.size() * m2l_nrows(hp.p)), "hipMalloc Lr");
-        dp.lr_cap = F;
-    }
 }
 
 void collect_timing(DevicePlan &dp)
@@ -4116,6 +4108,15 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
         ensure_m2l_tiles(dp, 16 / m2l_fpt(F));
         if (dp.level_orders) ensure_m2l_level_tiles(dp, 16 / m2l_fpt(F));
     }
+    if (dp.lr_cap < F) {
+        ++dp.schedule_gen;
+        if (dp.Lr) (void)hipFree(dp.Lr);
+        dp.Lr = nullptr;
+        dp.lr_cap = 0;
+        hip_check(hipMalloc(&dp.Lr, sizeof(double) * (size_t)F * C * m2l_nrows(dp.hp.p)), "hipMalloc Lr");
+        dp.lr_cap = F;
+    }
+    const QRows q = q_rows(dp, F);
     if (dp.m2l_precision != TFMM_M2L_FP64) {
         if (!dp.m2l_Df) {
             ++dp.schedule_gen;
@@ -4126,22 +4127,22 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
             hip_check(hipGetLastError(), "k_to_float launch");
             hip_check(hipDeviceSynchronize(), "k_to_float");
         }
-        if (dp.qtf_cap < F) {
+        if (dp.qtf_cap < q_elems(q)) {
             ++dp.schedule_gen;
             if (dp.Qtf) (void)hipFree(dp.Qtf);
             dp.Qtf = nullptr;
             dp.qtf_cap = 0;
-            hip_check(hipMalloc(&dp.Qtf, sizeof(float) * (size_t)F * C * m2l_row_max(dp)), "hipMalloc Qt f32");
-            dp.qtf_cap = F;
+            hip_check(hipMalloc(&dp.Qtf, sizeof(float) * (size_t)q_elems(q)), "hipMalloc Qt f32");
+            dp.qtf_cap = q_elems(q);
         }
-    } else if (dp.qt_cap < F) {
+    } else if (dp.qt_cap < q_elems(q)) {
         ++dp.schedule_gen;
         if (dp.Qt) (void)hipFree(dp.Qt - 1);
         dp.Qt = nullptr;
         dp.qt_cap = 0;
-        hip_check(hipMalloc(&dp.Qt, sizeof(double) * ((size_t)F * C * m2l_row_max(dp) + 2)), "hipMalloc Qt");
-        dp.Qt += 1;  // entry 1 of every row (the first that counts) on a 16-byte boundary
-        dp.qt_cap = F;
+        hip_check(hipMalloc(&dp.Qt, sizeof(double) * (size_t)(q_elems(q) + 2)), "hipMalloc Qt");
+        dp.Qt += 1;  // entry 1 of every plain row (the first that counts) on a 16-byte boundary
+        dp.qt_cap = q_elems(q);
     }
 }
 
