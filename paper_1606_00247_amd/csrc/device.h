@@ -196,6 +196,8 @@ struct DevicePlan {
     // ([near_rows][fields of the pass], near_w_cap doubles)
     NearTet *near_tet = nullptr;
     int64_t near_rows = 0, near_w_cap = 0;
+    double *u_tree = nullptr;  // sums in the octree's order [u_cap][n_targets] (near_in_order)
+    int32_t u_cap = 0;
     double *near_w = nullptr;
     int64_t topo_evals[3] = {0, 0, 0};  // (target, node / edge / face) evaluations per one-field evaluation
     bool p2p_topo = true;  // single-field near field over shared entities
