@@ -495,46 +495,61 @@ void build_m2l_packs(const HostPlan &hp, int nb, int tpg, int max_grp, M2LPacks 
     }
     std::vector<std::array<int32_t, 2>> rng;  // items: group range
     std::vector<int32_t> iblk, lev;
-    std::vector<std::array<int32_t, 3>> trip;  // key, slot, source
+    // A block's pairs by key, then by slot class (slot mod tpg), then slot: the
+    // pairs of a key are dealt round-robin over its ceil(n / tpg) groups, so that a
+    // group's slots differ mod tpg wherever the class counts allow (its accumulator
+    // rows then fall in different LDS banks).  The slots are taken in that order
+    // and dealt to their keys' ranges (a counting sort).
+    const size_t nkeys = hp.m2l_keys.size() / 4;
+    std::vector<int32_t> at(nkeys + 1), used;
+    std::vector<std::array<int32_t, 2>> pair;  // slot, source
     for (auto &kv : lvl) {
         std::sort(kv.second.begin(), kv.second.end());
         const auto &v = kv.second;
         for (size_t b0 = 0; b0 < v.size(); b0 += (size_t)nb) {
             const int32_t blk = (int32_t)(out.blk_cells.size() / nb);
-            const size_t b1 = std::min(v.size(), b0 + (size_t)nb);
-            trip.clear();
-            for (size_t i = b0; i < b0 + (size_t)nb; ++i) {
-                const int32_t a = i < b1 ? v[i].second : -1;
+            const int n_slot = (int)(std::min(v.size(), b0 + (size_t)nb) - b0);
+            used.clear();
+            for (int i = 0; i < nb; ++i) {
+                const int32_t a = i < n_slot ? v[b0 + i].second : -1;
                 out.blk_cells.push_back(a);
                 if (a < 0) continue;
                 for (int32_t j = hp.m2l_ptr[a]; j < hp.m2l_ptr[a + 1]; ++j)
-                    trip.push_back({hp.m2l_pair_key[j], (int32_t)(i - b0), hp.m2l_src[j]});
+                    if (at[hp.m2l_pair_key[j]]++ == 0) used.push_back(hp.m2l_pair_key[j]);
             }
-            // by key, then by slot class (slot mod tpg), then slot: the pairs
-            // of a key are dealt round-robin over its ceil(n / tpg) groups, so
-            // that a group's slots differ mod tpg wherever the class counts
-            // allow (its accumulator rows then fall in different LDS banks)
-            std::sort(trip.begin(), trip.end(), [tpg](const std::array<int32_t, 3> &x, const std::array<int32_t, 3> &y) {
-                if (x[0] != y[0]) return x[0] < y[0];
-                if (x[1] % tpg != y[1] % tpg) return x[1] % tpg < y[1] % tpg;
-                return x[1] < y[1];
-            });
-            const int32_t g0 = (int32_t)out.grp_key.size();
-            for (size_t i = 0; i < trip.size();) {
-                const int32_t k = trip[i][0];
-                size_t j = i;
-                while (j < trip.size() && trip[j][0] == k) ++j;
-                const size_t n = j - i, G = (n + (size_t)tpg - 1) / (size_t)tpg;
-                for (size_t g = 0; g < G; ++g) {
-                    out.grp_key.push_back(k);
-                    for (int q = 0; q < tpg; ++q) {
-                        const size_t e = g + (size_t)q * G;  // round-robin deal
-                        const bool ok = e < n;
-                        out.grp_src.push_back(ok ? trip[i + e][2] : -1);
-                        out.grp_slot.push_back(ok ? (uint8_t)trip[i + e][1] : (uint8_t)0);
-                    }
+            std::sort(used.begin(), used.end());
+            int32_t total = 0;
+            size_t groups = 0;
+            for (int32_t k : used) {
+                const int32_t n = at[k];
+                groups += ((size_t)n + tpg - 1) / tpg;
+                at[k] = total;
+                total += n;
+            }
+            pair.resize((size_t)total);
+            for (int c = 0; c < tpg; ++c)
+                for (int i = c; i < n_slot; i += tpg) {
+                    const int32_t a = v[b0 + i].second;
+                    for (int32_t j = hp.m2l_ptr[a]; j < hp.m2l_ptr[a + 1]; ++j)
+                        pair[at[hp.m2l_pair_key[j]]++] = {i, hp.m2l_src[j]};
                 }
-                i = j;
+            // at[k]: end of key k's range
+            const int32_t g0 = (int32_t)out.grp_key.size();
+            out.grp_key.resize((size_t)g0 + groups);
+            out.grp_src.resize(((size_t)g0 + groups) * tpg, -1);
+            out.grp_slot.resize(((size_t)g0 + groups) * tpg, 0);
+            size_t g = (size_t)g0;
+            int32_t beg = 0;
+            for (int32_t k : used) {
+                const int32_t n = at[k] - beg, G = (n + tpg - 1) / tpg;
+                for (int32_t e = 0; e < n; ++e) {  // pair e: group e % G, place e / G
+                    const size_t o = (g + e % G) * tpg + e / G;
+                    out.grp_src[o] = pair[beg + e][1];
+                    out.grp_slot[o] = (uint8_t)pair[beg + e][0];
+                }
+                for (int32_t e = 0; e < G; ++e) out.grp_key[g++] = k;
+                beg = at[k];
+                at[k] = 0;
             }
             const int32_t g1 = (int32_t)out.grp_key.size();
             if (out.grp_key.size() > (size_t)INT32_MAX / 16) throw PlanError{TFMM_ENOTSUP, "too many M2L groups"};
