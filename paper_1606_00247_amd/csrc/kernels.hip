@@ -1331,13 +1331,15 @@ __global__ __launch_bounds__(256) void k_lr_expand(const double *__restrict__ Lr
 // in two accumulators, of the even and of the odd (step, row tile) pairs, which
 // meet in FP64.
 //
-// One wavefront per tile and G field groups of 16 columns: the derivative parts of
-// a key are gathered once for G groups from the wavefront's copy in LDS, the
-// multipoles come split and in operand order from k_qreduce, straight into the
-// registers of the entry before as its matrix steps consume them.  (With two
+// One wavefront per tile of 16 columns: the derivative parts of a key are gathered
+// from the wavefront's copy in LDS, the multipoles come split and in operand order
+// from k_qreduce, straight into the registers of the entry before as its matrix
+// steps consume them.  (With two
 // wavefronts splitting and staging both operands for one group, the LDS was busy
 // 64% of the time and the matrix cores 10%: 64 fields, order 8, 1.1 million
-// translations, BF16x3: 6.3 ms of M2L, now 2.65.)
+// translations, BF16x3: 6.3 ms of M2L, now 2.41.)  Bound by the multipoles, of which
+// half come from beyond the L2; two field groups a wavefront, with half the gathers,
+// keep twice as many of them in use at a time and take 2.64 ms.
 // ---------------------------------------------------------------------------
 using bf16x8 = __bf16 __attribute__((ext_vector_type(8)));
 
@@ -1354,14 +1356,15 @@ __host__ __device__ constexpr int m2lb_steps(int P)
     return s;
 }
 
-template <int P, int NP, int G>
-__global__ __launch_bounds__(64, 2) void k_m2l_bf16(
+template <int P, int NP>
+__global__ __launch_bounds__(64, P <= 8 ? 3 : 2) void k_m2l_bf16(
     const int32_t *__restrict__ tile_tgt, const int32_t *__restrict__ tile_rng, const int32_t *__restrict__ ent_key,
     const int32_t *__restrict__ ent_src, const int32_t *__restrict__ keys, const float *__restrict__ Dtab, int dstr,
-    const __bf16 *__restrict__ Qb, int ksp, int64_t C, int tpt, int fpt, int fg0, int F, int ntiles,
+    const __bf16 *__restrict__ Qb, int ksp, int64_t C, int tpt, int fpt, int F, int ntiles,
     double *__restrict__ Lr, int lrs)
 {
     using v4 = Mfma<float>::v4;
+    using u4 = uint32_t __attribute__((ext_vector_type(4)));
     constexpr int NR = nr_of(P), NROW = m2l_nrows(P), ND = nd_of(P), NRT = m2l_nrt(P), KS = m2lb_ks(P, 0);
     constexpr int NS = m2lb_steps(P), DW = NP == 3 ? 2 : 1, RSTR = NROW | 1, DREG = (ND + 63) / 64;
     __shared__ uint32_t s_D[(ND + 1) * DW];  // parts 0 and 1 of an entry in a word, part 2 in the next
@@ -1371,7 +1374,7 @@ __global__ __launch_bounds__(64, 2) void k_m2l_bf16(
     const int lane = threadIdx.x, col = lane & 15, kq = lane >> 4, tslot = col / fpt, fsub = col % fpt;
     const int e0 = tile_rng[2 * tile], e1 = tile_rng[2 * tile + 1];
     if (e0 >= e1) return;
-    const int fg = fg0 + (int)blockIdx.y * G;  // first field group
+    const int fg = (int)blockIdx.y;            // field group
     if (lane < DW) s_D[ND * DW + lane] = 0;    // the zero slot
     // byte offsets in s_D of this lane's A operand elements, two to a register (the zero slot outside |n| + |m| <= P)
     uint32_t at[NS][4];
@@ -1403,13 +1406,11 @@ __global__ __launch_bounds__(64, 2) void k_m2l_bf16(
     const __bf16 *qb = Qb + (int64_t)fg * C * row + fsub * 32 + kq * 8;
     auto source = [&](int e) { return ent_src[(int64_t)min(e, e1 - 1) * tpt + tslot]; };
     auto key_of = [&](int e) { return ent_key[min(e, e1 - 1)]; };
-    bf16x8 b[G][KS][NP];
+    bf16x8 b[KS][NP];
     auto load = [&](int src, int ks) {  // in-bounds unconditionally, masked when used
         const __bf16 *q = qb + (int64_t)max(src, 0) * row + ks * NP * fpt * 32;
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int k = 0; k < NP; ++k) b[g][ks][k] = *reinterpret_cast<const bf16x8 *>(q + g * C * row + k * fpt * 32);
+        for (int k = 0; k < NP; ++k) b[ks][k] = *reinterpret_cast<const bf16x8 *>(q + k * fpt * 32);
     };
     float d[DREG];
     auto fetch_row = [&](int key) {
@@ -1428,11 +1429,9 @@ __global__ __launch_bounds__(64, 2) void k_m2l_bf16(
             }
         }
     };
-    v4 acc[G][2][NRT];
+    v4 acc[2][NRT];
 #pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int rt = 0; rt < NRT; ++rt) acc[g][0][rt] = acc[g][1][rt] = v4{0, 0, 0, 0};
+    for (int rt = 0; rt < NRT; ++rt) acc[0][rt] = acc[1][rt] = v4{0, 0, 0, 0};
     int src = source(e0), src1 = source(e0 + 1), key = key_of(e0), key1 = key_of(e0 + 1);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) load(src, ks);
@@ -1444,14 +1443,9 @@ __global__ __launch_bounds__(64, 2) void k_m2l_bf16(
         if (tpt > 1) {  // columns without a source
             const uint32_t keep = src >= 0 ? 0xffffffffu : 0u;
 #pragma unroll
-            for (int g = 0; g < G; ++g)
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                    for (int k = 0; k < NP; ++k) {
-                        using u4 = uint32_t __attribute__((ext_vector_type(4)));
-                        b[g][ks][k] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u4, b[g][ks][k]) & keep);
-                    }
+                for (int k = 0; k < NP; ++k) b[ks][k] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u4, b[ks][k]) & keep);
         }
         if (dl != 0) {  // uniform; 2^(-dl |n|), exact
 #pragma unroll
@@ -1460,9 +1454,7 @@ __global__ __launch_bounds__(64, 2) void k_m2l_bf16(
                 for (int i = 0; i < 8; ++i) {
                     const int deg = (int)sqrtf((float)(1 + 32 * ks + 8 * kq + i));  // exact: degree d starts at d^2
 #pragma unroll
-                    for (int g = 0; g < G; ++g)
-#pragma unroll
-                        for (int k = 0; k < NP; ++k) b[g][ks][k][i] = (__bf16)ldexpf((float)b[g][ks][k][i], -dl * deg);
+                    for (int k = 0; k < NP; ++k) b[ks][k][i] = (__bf16)ldexpf((float)b[ks][k][i], -dl * deg);
                 }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1480,7 +1472,6 @@ __global__ __launch_bounds__(64, 2) void k_m2l_bf16(
                         w[i] = p[0];
                         if constexpr (NP == 3) w2[i] = p[1];
                     }
-                    using u4 = uint32_t __attribute__((ext_vector_type(4)));
                     bf16x8 a[NP];
                     u4 q0, q1, q2;
 #pragma unroll
@@ -1493,10 +1484,7 @@ __global__ __launch_bounds__(64, 2) void k_m2l_bf16(
                     a[1] = __builtin_bit_cast(bf16x8, q1);
                     if constexpr (NP == 3) a[2] = __builtin_bit_cast(bf16x8, q2);
                     auto mma = [&](int i, int k) {
-#pragma unroll
-                        for (int g = 0; g < G; ++g)
-                            acc[g][s & 1][rt] =
-                                __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[g][ks][k], acc[g][s & 1][rt], 0, 0, 0);
+                        acc[s & 1][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[ks][k], acc[s & 1][rt], 0, 0, 0);
                     };
                     // smallest terms first
                     if constexpr (NP == 3) {
@@ -1519,25 +1507,20 @@ __global__ __launch_bounds__(64, 2) void k_m2l_bf16(
         key = key1;
         key1 = key2;
     }
-    // the groups' sums, through LDS in whole rows, to Lr
+    // the sums, through LDS in whole rows, to Lr
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+    for (int rt = 0; rt < NRT; ++rt)
 #pragma unroll
-        for (int rt = 0; rt < NRT; ++rt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = 16 * rt + Mfma<float>::row(lane, r);
-                if (m < NROW) red[col * RSTR + m] = (double)acc[g][0][rt][r] + (double)acc[g][1][rt][r];
-            }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        for (int i = lane; i < 16 * NROW; i += 64) {
-            const int c = i / NROW, m = i - c * NROW, field = (fg + g) * fpt + c % fpt;
-            const int A = tile_tgt[tile * tpt + c / fpt];
-            if (A >= 0 && field < F) atomicAdd(&Lr[((int64_t)field * C + A) * lrs + m], red[c * RSTR + m]);
+        for (int r = 0; r < 4; ++r) {
+            const int m = 16 * rt + Mfma<float>::row(lane, r);
+            if (m < NROW) red[col * RSTR + m] = (double)acc[0][rt][r] + (double)acc[1][rt][r];
         }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int i = lane; i < 16 * NROW; i += 64) {
+        const int c = i / NROW, m = i - c * NROW, field = fg * fpt + c % fpt;
+        const int A = tile_tgt[tile * tpt + c / fpt];
+        if (A >= 0 && field < F) atomicAdd(&Lr[((int64_t)field * C + A) * lrs + m], red[c * RSTR + m]);
     }
 }
 
@@ -3602,30 +3585,18 @@ void launch_m2l_p(DevicePlan &dp, const DevicePlan::Tiles &tl, const T *D, const
     hip_check(hipGetLastError(), "k_m2l_mfma launch");
 }
 
-// BF16 form: field groups two at a time, an odd last one alone; one at a time
-// above order 8, where two groups' multipoles do not fit in the registers.
 template <int NP>
 void launch_m2lb(DevicePlan &dp, const DevicePlan::Tiles &tl, int fpt, int32_t F, hipStream_t st, int p)
 {
     const HostPlan &hp = dp.hp;
-    const int groups = (F + fpt - 1) / fpt, pairs = groups / 2;
     with_order(p, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
-        auto go = [&](auto gc, int fg0, int n) {
-            constexpr int G = decltype(gc)::value;
-            k_m2l_bf16<P, NP, G><<<dim3(tl.ntiles, (unsigned)n), dim3(64), 0, st>>>(
-                tl.tile_tgt, tl.tile_rng, tl.ent_key, tl.ent_src, dp.m2l_keys, dp.m2l_Df, m2l_table_width(hp.p),
-                reinterpret_cast<const __bf16 *>(dp.Qtf), m2lb_ks(hp.p, 0), (int64_t)hp.cells.size(), tl.tpt, fpt, fg0, F,
-                tl.ntiles, dp.Lr, m2l_nrows(hp.p));
-            hip_check(hipGetLastError(), "k_m2l_bf16 launch");
-        };
-        if constexpr (P <= 8) {
-            if (pairs) go(std::integral_constant<int, 2>{}, 0, pairs);
-            if (groups & 1) go(std::integral_constant<int, 1>{}, 2 * pairs, 1);
-        } else {
-            go(std::integral_constant<int, 1>{}, 0, groups);
-        }
+        k_m2l_bf16<P, NP><<<dim3(tl.ntiles, (unsigned)((F + fpt - 1) / fpt)), dim3(64), 0, st>>>(
+            tl.tile_tgt, tl.tile_rng, tl.ent_key, tl.ent_src, dp.m2l_keys, dp.m2l_Df, m2l_table_width(hp.p),
+            reinterpret_cast<const __bf16 *>(dp.Qtf), m2lb_ks(hp.p, 0), (int64_t)hp.cells.size(), tl.tpt, fpt, F, tl.ntiles,
+            dp.Lr, m2l_nrows(hp.p));
     });
+    hip_check(hipGetLastError(), "k_m2l_bf16 launch");
 }
 
 template <typename T>
