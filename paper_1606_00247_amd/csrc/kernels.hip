@@ -4,13 +4,13 @@
 //         geometric moments (exact quadrature, once per plan) and affine M
 //   m2m   binomial shift of child multipoles to the parent centre
 //   m2l   multipole -> local translation of the Cartesian Taylor expansion on
-//         FP64 matrix cores, target cells in tiles sharing translation keys
+//         the matrix cores, translations packed by key or target cells in tiles
 //   l2l   binomial shift of a local expansion to the child centres
 //   l2p   evaluation of the local expansion at the targets (adds into u)
 //   p2p   exact near-field tet-to-target potential (Sec. 2.1), source-major:
-//         one workgroup per block of <= 64 tets of a source leaf, the tets'
-//         geometry and field coefficients staged in LDS, every lane a target,
-//         atomically accumulated into u
+//         one wavefront per chunk of a source leaf's tets and 64 targets, the
+//         tets' (one field: their shared nodes', edges' and faces') data read
+//         through the scalar unit, atomically accumulated into u
 //
 // Multi-indices |n| <= p are stored in graded order: degree ascending, within
 // a degree n_x descending, then n_y descending.  idx(n) = d(d+1)(d+2)/6 +
@@ -361,6 +361,24 @@ __global__ __launch_bounds__(kP2MThreads, FC == 1 ? 4 : (NT <= 3 ? 3 : 2)) void 
     }
     // kept to the order of the leaf's level (the rest stays zero)
     const int nkeep = ncoef_of(lo.q[cell_i[CI_N * cell + CI_LEVEL]]);
+    // the terms of coefficient n: weights and places in U, found once for all fields
+    double nv[3];
+    int at[3][4];
+    auto terms = [&](int n) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            int b[3] = {c_mi.v[n][0], c_mi.v[n][1], c_mi.v[n][2]};
+            const bool on = b[k] > 0 && n < nkeep;
+            nv[k] = on ? (double)b[k] : 0.0;
+            if (on) --b[k];
+            const int row = 64 * NT;
+            at[k][0] = k * row + (on ? mi_index(b[0], b[1], b[2]) : 0);
+            at[k][1] = (3 + 3 * k) * row + (on ? mi_index(b[0] + 1, b[1], b[2]) : 0);
+            at[k][2] = (4 + 3 * k) * row + (on ? mi_index(b[0], b[1] + 1, b[2]) : 0);
+            at[k][3] = (5 + 3 * k) * row + (on ? mi_index(b[0], b[1], b[2] + 1) : 0);
+        }
+    };
+    terms(min(tid, ncoef - 1));
 #pragma unroll
     for (int f = 0; f < FC; ++f) {
         if (f0 + f >= F) break;
@@ -372,20 +390,14 @@ __global__ __launch_bounds__(kP2MThreads, FC == 1 ? 4 : (NT <= 3 ? 3 : 2)) void 
                 s_U[(4 * (g - 3 * f) + kq) * 64 * NT + 16 * (wave + 4 * j) + col] = acc[g >> 2][j][g & 3];
         __syncthreads();
         for (int n = tid; n < ncoef; n += kP2MThreads) {
-            const int nv[3] = {c_mi.v[n][0], c_mi.v[n][1], c_mi.v[n][2]};
+            if (n != tid) terms(n);  // only above order 9
             double q = 0.0;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                if (nv[k] == 0 || n >= nkeep) continue;
-                int b[3] = {nv[0], nv[1], nv[2]};
-                --b[k];
-                const double *U = s_U + (3 + 3 * k) * 64 * NT;
-                q += nv[k] * (s_U[k * 64 * NT + mi_index(b[0], b[1], b[2])] + U[mi_index(b[0] + 1, b[1], b[2])] +
-                              U[64 * NT + mi_index(b[0], b[1] + 1, b[2])] +
-                              U[2 * 64 * NT + mi_index(b[0], b[1], b[2] + 1)]);
-            }
+            for (int k = 0; k < 3; ++k)
+                if (nv[k] != 0.0) q += nv[k] * (s_U[at[k][0]] + s_U[at[k][1]] + s_U[at[k][2]] + s_U[at[k][3]]);
             Q[((int64_t)(f0 + f) * C + cell) * ncoef + n] = q;
         }
+        if (ncoef > kP2MThreads) terms(tid);
     }
 }
 
