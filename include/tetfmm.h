@@ -180,8 +180,8 @@ int tfmm_evaluate(tfmm_plan plan, const double *M, int32_t F, double *u, void *h
  * targets and all tets, in FP64.  Pairs within 3 tet diameters (longest edge)
  * of the tet's centroid take the closed form; farther pairs, where the closed
  * form cancels, a collapsed Gauss-Jacobi rule of degree 13, 11, 9 or 7 by
- * distance band (3-6, 6-12, 12-24, >= 24 diameters; rule error below ~1e-14
- * of the pair's size).  Point-dipole plans sum the dipole potentials.  Same
+ * distance band (3-5, 5-9, 9-24, >= 24 diameters; rule error at most 3e-14 of
+ * the pair's size, below 1e-14 beyond 3.5).  Point-dipole plans sum the dipole potentials.  Same
  * arguments and errors as tfmm_evaluate.
  */
 int tfmm_direct(tfmm_plan plan, const double *M, int32_t F, double *u, void *hip_stream);
@@ -412,8 +412,8 @@ int tfmm_plan_autotune(tfmm_plan plan, void *hip_stream);
  * one; one field takes it only beside the surrogate's band), and
  * the M2L form for fewer than 16 fields with FP64 or FP32 translations
  * (m2l_packed 1: the translations of each key are packed 16 columns at a
- * time inside blocks of target cells, m2l_groups_per_item (16..4096) such
- * groups per workgroup item; 0: target tiles run through their keys).
+ * time inside blocks of target cells, at most m2l_groups_per_item (16..4096)
+ * such groups per workgroup item; 0: target tiles run through their keys).
  * Every choice computes the same contraction (sums in another order); the
  * point is to run a given schedule (for instance the one a benchmark timed)
  * under test.  Builds the M2L work lists of the new schedule for one field

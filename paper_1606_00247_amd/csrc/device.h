@@ -159,7 +159,7 @@ struct DevicePlan {
     Packs m2l_packs[4];  // fpt = 1, 2, 4, 8
     std::vector<Packs> lvl_packs;
     bool m2l_pack = true;  // schedule knob: the packed form where it applies
-    int m2l_max_grp = 256;  // groups per packed work item
+    int m2l_max_grp = 1024;  // groups per packed work item, at most (see build_packs)
     double *Lr = nullptr;
     int32_t lr_cap = 0;
     int m2l_precision = 0;  // TFMM_M2L_*

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kMomThreads) void k_tet_moments(const int32_t *__re
 // wavefronts.  The shifts by e_k and e_d are taken once per leaf, on U in LDS.
 // Bound: the moments' bytes (507 MB on the 40^3 cube, one field: 105 us at the
 // rate of a large copy).  One field there 416 -> 239 us, on a film of 387k tets
-// (17 a leaf) 1.23 -> 0.44 ms, 16 fields on a 26^3 cube 0.60 -> 0.33 ms, against
+// (17 a leaf) 1.23 -> 0.44 ms, 16 fields on a 26^3 cube 0.60 -> 0.29 ms, against
 // one coefficient a thread with its 12 gathers a tet from LDS; the rest is the
 // field values of a leaf, formed before its contraction can start.
 // ---------------------------------------------------------------------------
@@ -1203,7 +1203,7 @@ __global__ __launch_bounds__(64 * kM2LPWaves, 2) void k_m2l_pack(
         row(key);
         stage();
         // A operand, gathered at each change of key where it fits in registers
-        // (to order 8; with a gather per group the LDS bounds: 40^3 cube 2.09, now 1.99 ms)
+        // (to order 8; with a gather per group the LDS bounds: 40^3 cube, items of 256 groups, 2.09 and 1.99 ms)
         double a[kKeep ? NS : 1];
         auto gather = [&]() {
             if constexpr (kKeep) {
@@ -4009,7 +4009,9 @@ static void build_packs(DevicePlan &dp, int fpt, int32_t F, int p, int only_leve
     // are two rounds of the chip's workgroups; 48 groups, six a wavefront, are the
     // least that carry an item's clearing and summing up.  (M2L of an 8^3 cube, 6,400
     // groups: 64 us in items of 256, 36 in items of 48.  A batch of 170,000 groups:
-    // .37 ms in items of 256, .45 in items of 166.)
+    // .37 ms in items of 256, .45 in items of 166.  The 40^3 cube, 1.2 million groups:
+    // 1.98 ms in items of 256, 1.69 in items of 1024; the 16,000 sums of a block are
+    // added to memory once an item.)
     const int64_t groups = (int64_t)dp.hp.m2l_src.size() * fpt / 16 * ((F + fpt - 1) / fpt);
     const int cut = (int)std::min<int64_t>(dp.m2l_max_grp, std::max<int64_t>(48, groups / 512));
     M2LPacks h;
@@ -4230,7 +4232,7 @@ void autotune(DevicePlan &dp, hipStream_t st)
         dp.m2l_max_ent = best_ent;
         dp.m2l_pack = true;
         if (m2l_packed(dp, 1)) {
-            for (int grp : {256, 512}) {
+            for (int grp : {512, 1024}) {
                 dp.m2l_max_grp = grp;
                 const float t = time_config(dp, M, u, st);
                 if (t < best) best = t, best_grp = grp, best_pack = true;
