@@ -180,8 +180,10 @@ int tfmm_evaluate(tfmm_plan plan, const double *M, int32_t F, double *u, void *h
  * targets and all tets, in FP64.  Pairs within 3 tet diameters (longest edge)
  * of the tet's centroid take the closed form; farther pairs, where the closed
  * form cancels, a collapsed Gauss-Jacobi rule of degree 13, 11, 9 or 7 by
- * distance band (3-5, 5-9, 9-24, >= 24 diameters; rule error at most 3e-14 of
- * the pair's size, below 1e-14 beyond 3.5).  Point-dipole plans sum the dipole potentials.  Same
+ * distance band (3-6, 6-12, 12-24, >= 24 diameters; the rule's error is, over
+ * all nodal M and shapes of tets, at most 7e-14 of the pair's size
+ * |M| V / (4 pi d^2) at 3 diameters, 8e-15 at 3.5, 2.3e-15 from 4 to 24 and
+ * 2.3e-14 at 24).  Point-dipole plans sum the dipole potentials.  Same
  * arguments and errors as tfmm_evaluate.
  */
 int tfmm_direct(tfmm_plan plan, const double *M, int32_t F, double *u, void *hip_stream);

@@ -19,12 +19,14 @@ inline int m2l_table_width(int p) { return 1 + 3 * p * (p + 1) / 2; }
 // Far pairs of the direct sum (targets at least kFarRatio[0] longest edges
 // from a tet's centroid) are integrated by collapsed Gauss-Jacobi rules of
 // kFarPts[i]^3 points from kFarRatio[i] longest edges on.  A rule's error falls
-// as (0.3 diameters / distance)^(2 n); relative to |M| V / d^2 it is, at most over
-// tet shapes from needles to flat and over directions, 2.7e-14 at 3 (7^3 points),
-// 6.7e-15 at 5 (6^3), 8.5e-15 at 9 (5^3) and 8.2e-15 at 24 (4^3).
+// as distance^(-2 n); relative to |M| V / d^2 it is, at most over all nodal M
+// with |M_i| <= |M|, tet shapes from needles to flat and directions (the worst is
+// a needle of 1:1000 seen along its axis), 7.0e-14 at 3 (7^3 points), 2.2e-15 at
+// 6 (6^3), 1.7e-15 at 12 (5^3) and 2.3e-14 at 24 (4^3).  (6^3 from 5 and 5^3 from
+// 9 would be 1.8e-14 and 2.3e-14 there.)
 constexpr int kFarRules = 4;
 constexpr int kFarPts[kFarRules] = {7, 6, 5, 4};
-constexpr double kFarRatio[kFarRules] = {3.0, 5.0, 9.0, 24.0};
+constexpr double kFarRatio[kFarRules] = {3.0, 6.0, 12.0, 24.0};
 // One-dimensional nodes and weight products of a rule of n^3 points: n rows of
 // FarC (weight 1), then n rows of FarB (weight 1 - t), then n of FarA ((1 - t)^2).
 struct FarC {

@@ -1668,13 +1668,13 @@ __global__ __launch_bounds__(p2p_threads(FCH, WIDE), 2) void k_p2p(const int32_t
 // Bound by FP64 issue: 15 slots a point (2 for the squared distance, 4 for the
 // hardware estimate of its root's reciprocal, 6 to refine and cube it, 3 for the
 // moments) and 20 for each row of points.  10,368 tets, 2,197 targets, 2 fields:
-// 15.8 ms with a rule per lane and 40 slots a point, now 3.2; 5 fields: 31.8 in
-// two passes, now 3.4.
+// 15.8 ms with a rule per lane and 40 slots a point, now 3.5; 5 fields: 31.8 in
+// two passes, now 4.0.
 //
 // A workgroup stages DT consecutive tets in LDS and takes 256 targets at a time:
 // the pairs are sorted by class (rule, or closed form) and its wavefronts take 64
 // pairs of one class after another, the most points first, so that no lane waits
-// for another's larger rule (5,700 slots a pair with the wavefront's largest, 4,000
+// for another's larger rule (5,900 slots a pair with the wavefront's largest, 4,400
 // sorted) and the loops stay uniform.  The sums are kept in LDS and added to u once
 // a target and workgroup.
 // ---------------------------------------------------------------------------
