@@ -4306,11 +4306,18 @@ void run_evaluate(DevicePlan &dp, const double *M, int32_t F, double *u, hipStre
         KTimer kt(dp, KT_P2M, st);
         if (dp.n_p2m_cells > 0) with_p2m(F, p, [&](auto fc, auto nt) {
             constexpr int FC = decltype(fc)::value, NT = decltype(nt)::value;
-            k_p2m<FC, NT><<<dim3(xcd_grid(dp.n_p2m_cells * ((F + FC - 1) / FC))), dim3(kP2MThreads),
-                            sizeof(double) * 12 * 64 * NT, st>>>(
-                dp.p2m_cells, dp.cell_i, dp.cell_c, C, dp.tet_xyz, dp.tet_node, hp.n_tets, dp.tet_mom, M, hp.n_nodes, F,
-                p, dp.n_p2m_cells, hp.points ? 1 : 0, dp.lo, dp.Q);
-            hip_check(hipGetLastError(), "k_p2m launch");
+            // a grid holds fewer than 2^32 threads: many fields in several launches
+            constexpr int64_t kItems = (1ll << 32) / kP2MThreads / 2;
+            const int32_t per = (int32_t)std::min<int64_t>(std::max<int64_t>(1, kItems / dp.n_p2m_cells) * FC, F);
+            for (int32_t f = 0; f < F; f += per) {
+                const int32_t n = std::min(per, F - f);
+                k_p2m<FC, NT><<<dim3(xcd_grid(dp.n_p2m_cells * ((n + FC - 1) / FC))), dim3(kP2MThreads),
+                                sizeof(double) * 12 * 64 * NT, st>>>(
+                    dp.p2m_cells, dp.cell_i, dp.cell_c, C, dp.tet_xyz, dp.tet_node, hp.n_tets, dp.tet_mom,
+                    M + (int64_t)f * hp.n_nodes * 3, hp.n_nodes, n, p, dp.n_p2m_cells, hp.points ? 1 : 0, dp.lo,
+                    dp.Q + (int64_t)f * C * dp.ncoef);
+                hip_check(hipGetLastError(), "k_p2m launch");
+            }
         });
     }
     {
