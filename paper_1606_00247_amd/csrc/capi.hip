@@ -287,6 +287,10 @@ void upload_plan(DevicePlan &dp)
             }
         }
         dp.n_topo_ch = (int32_t)(tp.ch_i.size() / 8);
+        // The forms from corner distances multiply two denominators of the third power
+        // of a length, so they keep to scales that leave its sixth power in range;
+        // others take the per-tet form, whose powers end at the fourth.
+        dp.p2p_topo = hp.side > 0x1p-100 && hp.side < 0x1p130;
         // one-field work items: 64 targets of one block each
         std::vector<int32_t> items;
         for (size_t k = 0; k + 3 < tp.blk.size(); k += 4)

@@ -202,7 +202,7 @@ struct DevicePlan {
     int32_t u_cap = 0;
     double *near_w = nullptr;
     int64_t topo_evals[3] = {0, 0, 0};  // (target, node / edge / face) evaluations per one-field evaluation
-    bool p2p_topo = true;  // single-field near field over shared entities
+    bool p2p_topo = true;  // near field from corner distances, where the mesh's scale allows
     // stored near-field operator (optional, built by store_near): per cell
     // [C][2] column and value offsets (-1: no block), padded column counts,
     // node columns and the coefficient blocks [nt][3][ncols] of the target

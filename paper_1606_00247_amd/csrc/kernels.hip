@@ -4121,7 +4121,7 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
         hip_check(hipEventCreateWithFlags(&dp.ev_join, hipEventDisableTiming), "hipEventCreate");
     }
     ensure_expansions(dp, F);
-    if (F > 1 && !dp.near_stored && dp.sur_mode == TFMM_SUR_OFF && dp.near_w_cap < dp.near_rows * near_pass(F)) {
+    if (F > 1 && !dp.near_stored && dp.sur_mode == TFMM_SUR_OFF && dp.p2p_topo && dp.near_w_cap < dp.near_rows * near_pass(F)) {
         ++dp.schedule_gen;  // a captured graph may hold the old weights
         if (dp.near_w) (void)hipFree(dp.near_w);
         dp.near_w = nullptr;
