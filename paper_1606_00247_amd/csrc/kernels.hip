@@ -3900,7 +3900,7 @@ void build_near_tets(DevicePlan &dp, const uint32_t *corner, const uint8_t *skin
 {
     if (dp.n_topo_ch == 0) return;
     // tets outside every block (leaves without near targets) keep row -1
-    (void)hipMemset(dp.near_tet, 0xff, sizeof(NearTet) * (size_t)dp.hp.n_tets);
+    hip_check(hipMemset(dp.near_tet, 0xff, sizeof(NearTet) * (size_t)dp.hp.n_tets), "hipMemset near-field tets");
     k_tet_static<<<dim3((unsigned)dp.n_topo_ch), dim3(64)>>>(dp.topo_ch_i, dp.topo_ch_c, dp.n_topo_ch, dp.tet_xyz,
                                                              dp.hp.n_tets, skin, row, corner, dp.near_tet);
     hip_check(hipGetLastError(), "k_tet_static launch");
