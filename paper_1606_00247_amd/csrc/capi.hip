@@ -112,7 +112,7 @@ T *dev_upload(const std::vector<T> &h, int64_t &bytes)
 
 namespace tfmm {
 
-// A device list needed only while the plan is uploaded.
+// A device list needed only while another is made.
 template <typename E>
 struct ScratchList {
     E *d;
@@ -317,16 +317,8 @@ void upload_plan(DevicePlan &dp)
             int64_t tmp = 0;
             ScratchList ab{dev_upload(tp.ed_ab, tmp)}, pqr{dev_upload(tp.fc_pqr, tmp)};
             build_topo_records(dp, ab.d, pqr.d);
-            std::vector<int64_t> row((size_t)T);
-            for (int64_t t = 0; t < T; ++t) {
-                row[t] = dp.near_rows;
-                dp.near_rows += 1 + 3 * __builtin_popcount(tp.skin[t]);
-            }
-            room(dp.near_tet, (size_t)T);
-            ScratchList corner{dev_upload(tp.corner, tmp)};
-            ScratchList skin{dev_upload(tp.skin, tmp)};
-            ScratchList rows{dev_upload(row, tmp)};
-            build_near_tets(dp, corner.d, skin.d, rows.d);
+            dp.near_corner.swap(tp.corner);
+            dp.near_skin.swap(tp.skin);
         }
     }
     {
@@ -351,6 +343,29 @@ void upload_plan(DevicePlan &dp)
         B += (int64_t)mb;
         build_tet_moments(dp);
     }
+}
+
+void ensure_near_tets(DevicePlan &dp)
+{
+    if (dp.near_tet || dp.near_skin.empty()) return;
+    const size_t T = dp.near_skin.size();
+    std::vector<int64_t> row(T);
+    int64_t rows = 0, tmp = 0;
+    for (size_t t = 0; t < T; ++t) {
+        row[t] = rows;
+        rows += 1 + 3 * __builtin_popcount(dp.near_skin[t]);
+    }
+    ScratchList corner{dev_upload(dp.near_corner, tmp)};
+    ScratchList skin{dev_upload(dp.near_skin, tmp)};
+    ScratchList first{dev_upload(row, tmp)};
+    ScratchList<NearTet> tet{nullptr};
+    hip_check(hipMalloc(&tet.d, T * sizeof(NearTet)), "hipMalloc near-field tets");
+    build_near_tets(dp, corner.d, skin.d, first.d, tet.d);
+    dp.near_rows = rows;
+    std::swap(dp.near_tet, tet.d);
+    dp.device_bytes += (int64_t)(T * sizeof(NearTet));
+    std::vector<uint32_t>().swap(dp.near_corner);
+    std::vector<uint8_t>().swap(dp.near_skin);
 }
 
 void free_plan(DevicePlan &dp)

@@ -86,7 +86,7 @@ struct TopoFaceW {
 };
 
 // Geometry of a tet for the near field of several fields (see k_p2p_fields),
-// relative to its chunk's centroid; once per plan (k_tet_static).
+// relative to its chunk's centroid; once per plan, on demand (k_tet_static).
 struct NearTet {
     uint32_t corner;   // chunk-local node indices, a byte each
     uint32_t skin;     // faces on the chunk's boundary (bit k: opposite corner k)
@@ -194,8 +194,11 @@ struct DevicePlan {
     TopoEdgeW *topo_edge_w = nullptr;
     TopoFaceW *topo_face_w = nullptr;
     int32_t n_topo_ch = 0, n_topo_items = 0;
-    // several fields: the tets' geometry, and the field weights of one pass
+    // several fields: the tets' geometry (ensure_near_tets; until then its chunk-local
+    // corners and boundary faces on the host), and the field weights of one pass
     // ([near_rows][fields of the pass], near_w_cap doubles)
+    std::vector<uint32_t> near_corner;
+    std::vector<uint8_t> near_skin;
     NearTet *near_tet = nullptr;
     int64_t near_rows = 0, near_w_cap = 0;
     double *u_tree = nullptr;  // sums in the octree's order [u_cap][n_targets] (near_in_order)
@@ -282,9 +285,12 @@ void build_tet_moments(DevicePlan &dp);
 // Geometry of the entity records (after the chunks are uploaded): edges' and
 // faces' chunk-local corners ab [ne][2], pqr [nf][3] (device).
 void build_topo_records(DevicePlan &dp, const int32_t *ab, const int32_t *pqr);
-// Geometry of the tets (after the chunks are uploaded): chunk-local corners,
+// Geometry of the tets (after the chunks are uploaded) from chunk-local corners,
 // boundary faces and first weight row of every tet (device, [T] each).
-void build_near_tets(DevicePlan &dp, const uint32_t *corner, const uint8_t *skin, const int64_t *row);
+void build_near_tets(const DevicePlan &dp, const uint32_t *corner, const uint8_t *skin, const int64_t *row, NearTet *tet);
+// dp.near_tet, near_rows: formed by the first evaluation of several fields that
+// integrates its near field (others need none of it, over 500 bytes a tet).
+void ensure_near_tets(DevicePlan &dp);
 // Fill the M2L derivative tables (after the keys are uploaded).
 void build_m2l_table(DevicePlan &dp);
 // Tiles of tpt target cells (16, 8, 4, 2 or 1), built and uploaded once.

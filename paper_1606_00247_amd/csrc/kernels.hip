@@ -3896,13 +3896,13 @@ void build_topo_records(DevicePlan &dp, const int32_t *ab, const int32_t *pqr)
     hip_check(hipDeviceSynchronize(), "k_topo_static");
 }
 
-void build_near_tets(DevicePlan &dp, const uint32_t *corner, const uint8_t *skin, const int64_t *row)
+void build_near_tets(const DevicePlan &dp, const uint32_t *corner, const uint8_t *skin, const int64_t *row, NearTet *tet)
 {
     if (dp.n_topo_ch == 0) return;
     // tets outside every block (leaves without near targets) keep row -1
-    hip_check(hipMemset(dp.near_tet, 0xff, sizeof(NearTet) * (size_t)dp.hp.n_tets), "hipMemset near-field tets");
+    hip_check(hipMemset(tet, 0xff, sizeof(NearTet) * (size_t)dp.hp.n_tets), "hipMemset near-field tets");
     k_tet_static<<<dim3((unsigned)dp.n_topo_ch), dim3(64)>>>(dp.topo_ch_i, dp.topo_ch_c, dp.n_topo_ch, dp.tet_xyz,
-                                                             dp.hp.n_tets, skin, row, corner, dp.near_tet);
+                                                             dp.hp.n_tets, skin, row, corner, tet);
     hip_check(hipGetLastError(), "k_tet_static launch");
     hip_check(hipDeviceSynchronize(), "k_tet_static");
 }
@@ -4121,7 +4121,9 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
         hip_check(hipEventCreateWithFlags(&dp.ev_join, hipEventDisableTiming), "hipEventCreate");
     }
     ensure_expansions(dp, F);
-    if (F > 1 && !dp.near_stored && dp.sur_mode == TFMM_SUR_OFF && dp.p2p_topo && dp.near_w_cap < dp.near_rows * near_pass(F)) {
+    const bool several = F > 1 && !dp.near_stored && dp.sur_mode == TFMM_SUR_OFF && dp.p2p_topo;
+    if (several) ensure_near_tets(dp);
+    if (several && dp.near_w_cap < dp.near_rows * near_pass(F)) {
         ++dp.schedule_gen;  // a captured graph may hold the old weights
         if (dp.near_w) (void)hipFree(dp.near_w);
         dp.near_w = nullptr;
