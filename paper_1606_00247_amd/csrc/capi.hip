@@ -551,9 +551,7 @@ int tfmm_plan_stats(tfmm_plan plan, tfmm_stats *out)
     out->n_p2p = (int64_t)hp.p2p_a.size();
     out->n_p2p_pairs = hp.n_p2p_pairs;
     out->ncoef = plan->dp.ncoef;
-    out->device_bytes = plan->dp.device_bytes +
-                        (int64_t)(sizeof(double) * (size_t)plan->dp.Fcap * hp.cells.size() *
-                                  (2 * (size_t)plan->dp.ncoef + (size_t)plan->dp.qpad));
+    out->device_bytes = plan->dp.device_bytes + tfmm::evaluation_bytes(plan->dp);
     out->setup_seconds = hp.setup_seconds;
     out->near_nnz = plan->dp.near_nnz;
     out->near_bytes = plan->dp.near_bytes;

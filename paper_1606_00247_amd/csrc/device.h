@@ -280,6 +280,9 @@ std::vector<int32_t> xcd_dispatch_items(int n);
 void upload_plan(DevicePlan &dp);
 void free_plan(DevicePlan &dp);
 void ensure_expansions(DevicePlan &dp, int32_t F);
+// Device bytes of the buffers that grow with the evaluations asked for (all that
+// dp.device_bytes does not count).
+int64_t evaluation_bytes(const DevicePlan &dp);
 // Geometric moments of the tets (after the rule and cells are uploaded).
 void build_tet_moments(DevicePlan &dp);
 // Geometry of the entity records (after the chunks are uploaded): edges' and

@@ -4107,6 +4107,16 @@ void ensure_expansions(DevicePlan &dp, int32_t F)
     dp.Fcap = F;
 }
 
+int64_t evaluation_bytes(const DevicePlan &dp)
+{
+    const int64_t C = (int64_t)dp.hp.cells.size(), nd = (int64_t)dp.n_m2l_keys * nd_of(dp.hp.p);
+    const int64_t doubles = 2 * dp.Fcap * C * dp.ncoef                 // Q, L
+                            + dp.lr_cap * C * m2l_nrows(dp.hp.p)       // Lr
+                            + (dp.Qt ? dp.qt_cap + 2 : 0)              // Qt
+                            + dp.near_w_cap + dp.u_cap * dp.hp.n_targets;
+    return (int64_t)sizeof(double) * doubles + (int64_t)sizeof(float) * (dp.qtf_cap + (dp.m2l_Df ? nd : 0));
+}
+
 void prepare_evaluate(DevicePlan &dp, int32_t F)
 {
     const int64_t C = (int64_t)dp.hp.cells.size();
