@@ -360,10 +360,19 @@ void ensure_near_tets(DevicePlan &dp)
     ScratchList first{dev_upload(row, tmp)};
     ScratchList<NearTet> tet{nullptr};
     hip_check(hipMalloc(&tet.d, T * sizeof(NearTet)), "hipMalloc near-field tets");
-    build_near_tets(dp, corner.d, skin.d, first.d, tet.d);
+    ScratchList<uint32_t> marks{nullptr};
+    hip_check(hipMalloc(&marks.d, dp.n_topo_ch * sizeof(uint32_t)), "hipMalloc near-field chunks");
+    const int32_t n_flat = build_near_tets(dp, corner.d, skin.d, first.d, tet.d, marks.d);
+    ScratchList<NearFlat> flat{nullptr};
+    if (n_flat > 0) {
+        hip_check(hipMalloc(&flat.d, n_flat * sizeof(NearFlat)), "hipMalloc near-field flat tets");
+        build_near_flat(dp, tet.d, flat.d);
+    }
     dp.near_rows = rows;
     std::swap(dp.near_tet, tet.d);
-    dp.device_bytes += (int64_t)(T * sizeof(NearTet));
+    std::swap(dp.near_flat, flat.d);
+    std::swap(dp.ch_flat, marks.d);
+    dp.device_bytes += (int64_t)(T * sizeof(NearTet) + n_flat * sizeof(NearFlat) + dp.n_topo_ch * sizeof(uint32_t));
     std::vector<uint32_t>().swap(dp.near_corner);
     std::vector<uint8_t>().swap(dp.near_skin);
 }
@@ -380,7 +389,7 @@ void free_plan(DevicePlan &dp)
     void *ptrs[] = {dp.tet_xyz, dp.tet_node, dp.tet_perm, dp.tgt_xyz, dp.tgt_perm, dp.tgt_leaf, dp.cell_c, dp.cell_i,
                     dp.p2m_cells, dp.m2m_cells, dp.l2l_cells, dp.p2p_blk, dp.p2p_idx, dp.quad, dp.far_rule, dp.node_lump, dp.tet_mom, dp.Q,
                     dp.L, dp.Qt ? dp.Qt - 1 : nullptr, dp.Qtf, dp.m2l_keys, dp.m2l_D, dp.m2l_Df, dp.sur_w, dp.sur_wb, dp.band_pairs, dp.band_rule, dp.topo_item,
-                    dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_inc, dp.topo_edge, dp.topo_face, dp.topo_edge_w, dp.topo_face_w, dp.near_tet, dp.near_w, dp.u_tree,
+                    dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.topo_inc, dp.topo_edge, dp.topo_face, dp.topo_edge_w, dp.topo_face_w, dp.near_tet, dp.near_flat, dp.ch_flat, dp.near_w, dp.u_tree,
                     dp.near_off, dp.near_nc, dp.near_cols, dp.near_val, dp.near_items};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);

@@ -90,6 +90,7 @@ struct TopoFaceW {
 struct NearTet {
     uint32_t corner;   // chunk-local node indices, a byte each
     uint32_t skin;     // faces on the chunk's boundary (bit k: opposite corner k)
+    int32_t flat, pad; // record of a flat tet (NearFlat), -1 if it is not
     int64_t row;       // first row of field weights: the tet's, then three per skin face
     double c[3];       // centroid
     double lam[3][3];  // gradients of barycentric coordinates 1..3
@@ -100,6 +101,18 @@ struct NearTet {
     double il2[6];     // 1 / l2
     double C[4][2][3]; // -(E_i . E_e) / (8 (2 A_k)^2): face k, its corners 1 and 2, its edges (opposite corner 0, 1, 2)
     double L[6];       // edge lengths
+};
+
+// A tet with faces at a dihedral angle whose sine is below kFlatSine.  The
+// barycentric coordinates of its faces' feet (see k_p2p_fields) are of the size
+// distance / width, those of the tet, of which they are a difference, of the size
+// distance / thickness; they are formed from their own gradients in the faces'
+// planes.  Relative to the sum of a pair's terms, targets one to three sizes away,
+// worst of 900: thickness 1/20 of the width 4 roundings by the difference, 0.6 by
+// the gradients, 1/300 84 and 0.7, 1/1000 (a side of 1/1000) 316 and 0.5.
+constexpr double kFlatSine = 1.0 / 16.0;
+struct NearFlat {
+    double f[4][2][4];  // face k, its corners 1 and 2: value at the tet's centroid, gradient
 };
 
 struct DevicePlan {
@@ -200,6 +213,8 @@ struct DevicePlan {
     std::vector<uint32_t> near_corner;
     std::vector<uint8_t> near_skin;
     NearTet *near_tet = nullptr;
+    NearFlat *near_flat = nullptr;
+    uint32_t *ch_flat = nullptr;  // per chunk, its flat tets (a bit each)
     int64_t near_rows = 0, near_w_cap = 0;
     double *u_tree = nullptr;  // sums in the octree's order [u_cap][n_targets] (near_in_order)
     int32_t u_cap = 0;
@@ -289,9 +304,12 @@ void build_tet_moments(DevicePlan &dp);
 // faces' chunk-local corners ab [ne][2], pqr [nf][3] (device).
 void build_topo_records(DevicePlan &dp, const int32_t *ab, const int32_t *pqr);
 // Geometry of the tets (after the chunks are uploaded) from chunk-local corners,
-// boundary faces and first weight row of every tet (device, [T] each).
-void build_near_tets(const DevicePlan &dp, const uint32_t *corner, const uint8_t *skin, const int64_t *row, NearTet *tet);
-// dp.near_tet, near_rows: formed by the first evaluation of several fields that
+// boundary faces and first weight row of every tet (device, [T] each); returns the
+// number of flat tets, whose records build_near_flat forms, and marks them in ch_flat.
+int32_t build_near_tets(const DevicePlan &dp, const uint32_t *corner, const uint8_t *skin, const int64_t *row, NearTet *tet,
+                        uint32_t *ch_flat);
+void build_near_flat(const DevicePlan &dp, const NearTet *tet, NearFlat *flat);
+// dp.near_tet, near_flat, near_rows: formed by the first evaluation of several fields that
 // integrates its near field (others need none of it, over 500 bytes a tet).
 void ensure_near_tets(DevicePlan &dp);
 // Fill the M2L derivative tables (after the keys are uploaded).

@@ -2511,7 +2511,8 @@ constexpr int kNearFieldsMax = 16;  // fields of one pass
 __global__ __launch_bounds__(64) void k_tet_static(const int32_t *__restrict__ ch_i, const double *__restrict__ ch_c,
                                                    int nch, const double *__restrict__ tet_xyz, int64_t T,
                                                    const uint8_t *__restrict__ skin, const int64_t *__restrict__ row,
-                                                   const uint32_t *__restrict__ corner, NearTet *__restrict__ out)
+                                                   const uint32_t *__restrict__ corner, NearTet *__restrict__ out,
+                                                   uint32_t *__restrict__ ch_flat, int32_t *__restrict__ n_flat)
 {
     const int ch = blockIdx.x;
     if (ch >= nch || (int)threadIdx.x >= ch_i[8 * ch + 1]) return;
@@ -2552,6 +2553,16 @@ __global__ __launch_bounds__(64) void k_tet_static(const int32_t *__restrict__ c
         K.L[i] = sqrt(d2);
         K.G[i] = g * iv;
     }
+    // sine of the angle between faces a and b: 6V L / (2 A_a 2 A_b), L the other two corners' edge
+    bool flat = false;
+    for (int i = 0; i < 6; ++i) {
+        const double *p = N[kEa[i]], *q = N[kEb[i]];
+        flat = flat || v6 * K.L[5 - i] < kFlatSine * sqrt((p[0] * p[0] + p[1] * p[1] + p[2] * p[2]) *
+                                                          (q[0] * q[0] + q[1] * q[1] + q[2] * q[2]));
+    }
+    K.flat = flat ? atomicAdd(n_flat, 1) : -1;
+    const uint64_t all = __ballot(flat);
+    if (threadIdx.x == 0) ch_flat[ch] = (uint32_t)all;
     for (int f = 0; f < 4; ++f) {
         const int *c = kFv[f];
         const double a2 = N[f][0] * N[f][0] + N[f][1] * N[f][1] + N[f][2] * N[f][2];
@@ -2562,6 +2573,40 @@ __global__ __launch_bounds__(64) void k_tet_static(const int32_t *__restrict__ c
                 for (int k = 0; k < 3; ++k) d += (q[k] - p[k]) * (s[k] - r[k]);
                 K.C[f][i - 1][j] = -d / (8.0 * a2);
             }
+    }
+}
+
+// The flat tets' records, one lane per tet of a chunk (as k_tet_static).
+__global__ __launch_bounds__(64) void k_flat_static(const int32_t *__restrict__ ch_i, const double *__restrict__ ch_c,
+                                                    int nch, const double *__restrict__ tet_xyz, int64_t T,
+                                                    const NearTet *__restrict__ tet, NearFlat *__restrict__ out)
+{
+    const int ch = blockIdx.x;
+    if (ch >= nch || (int)threadIdx.x >= ch_i[8 * ch + 1]) return;
+    const int64_t t = ch_i[8 * ch] + (int64_t)threadIdx.x;
+    if (tet[t].flat < 0) return;
+    NearFlat &K = out[tet[t].flat];
+    double v[4][3], cen[3];
+    for (int c = 0; c < 4; ++c)
+        for (int k = 0; k < 3; ++k) v[c][k] = tet_xyz[(int64_t)(3 * c + k) * T + t] - ch_c[3 * ch + k];
+    for (int k = 0; k < 3; ++k) cen[k] = 0.25 * ((v[0][k] + v[1][k]) + (v[2][k] + v[3][k]));  // as in k_tet_static
+    for (int f = 0; f < 4; ++f) {
+        const double *v0 = v[kFv[f][0]];
+        double e[2][3], n[3];  // corners 1 and 2 from corner 0, and the normal
+        for (int j = 0; j < 2; ++j)
+            for (int k = 0; k < 3; ++k) e[j][k] = v[kFv[f][j + 1]][k] - v0[k];
+        for (int k = 0; k < 3; ++k) n[k] = e[0][(k + 1) % 3] * e[1][(k + 2) % 3] - e[0][(k + 2) % 3] * e[1][(k + 1) % 3];
+        const double i2 = 1.0 / (n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
+        for (int j = 0; j < 2; ++j) {  // gradients e_2 x n / n^2 and n x e_1 / n^2
+            const double *p = j ? n : e[1], *q = j ? e[0] : n;
+            double at = 0.0;
+            for (int k = 0; k < 3; ++k) {
+                const double g = (p[(k + 1) % 3] * q[(k + 2) % 3] - p[(k + 2) % 3] * q[(k + 1) % 3]) * i2;
+                K.f[f][j][1 + k] = g;
+                at += g * (cen[k] - v0[k]);
+            }
+            K.f[f][j][0] = at;
+        }
     }
 }
 
@@ -2673,14 +2718,15 @@ __device__ __forceinline__ void atan_poly(double (&q)[4], const double (&z)[4])
 // 0.57; 64 on an 18^3 cube: 9.9 -> 4.6.  32 fields a pass leave two wavefronts
 // a SIMD and a quarter of the rate.  Four wavefronts a workgroup: the kernel
 // alone takes the same, but the expansion kernels beside it find room sooner
-// (whole evaluation 4.71 -> 4.43 ms at 16 fields).
+// (whole evaluation 4.71 -> 4.43 ms at 16 fields).  kFlat: for meshes that hold
+// flat tets (see NearFlat); all of it in one form is 0.5 to 0.8% slower on others.
 constexpr int kFieldWaves = 4;
 
-template <int FC>
+template <int FC, bool kFlat>
 __global__ __launch_bounds__(64 * kFieldWaves, 3) void k_p2p_fields(
     const int32_t *__restrict__ item, int nitems, const int32_t *__restrict__ ch_i, const double *__restrict__ ch_c,
-    const double *__restrict__ nw, const NearTet *__restrict__ tet, const double *__restrict__ W,
-    const int32_t *__restrict__ idx, const double *__restrict__ tgt_xyz, const int32_t *__restrict__ tgt_perm,
+    const double *__restrict__ nw, const NearTet *__restrict__ tet, const NearFlat *__restrict__ flat,
+    const uint32_t *__restrict__ ch_flat, const double *__restrict__ W, const int32_t *__restrict__ idx, const double *__restrict__ tgt_xyz, const int32_t *__restrict__ tgt_perm,
     int64_t N, int f0, int F, double *__restrict__ u)
 {
     __shared__ double s_R[kFieldWaves][kTopoNodes][64];
@@ -2736,10 +2782,15 @@ __global__ __launch_bounds__(64 * kFieldWaves, 3) void k_p2p_fields(
             }
             lam[0] = 0.25 - off;
         };
+        // Barycentric coordinates on face k of its foot, mu as above.
+        auto foot_of = [&](const ScalarMem<NearTet> &K, const double (&lam)[4], int k, double mu, double (&foot)[3]) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) foot[j] = fma(-K.G[kEdgeOf[kFv[k][j]][k]], mu, lam[kFv[k][j]]);
+        };
         // Adds tet K to the sums of all fields: F' of its edges, half solid
-        // angles of its faces, g' of an edge on demand.
+        // angles of its faces, the feet of its faces and g' of an edge on demand.
         auto add = [&](const ScalarMem<NearTet> &K, const double (&lam)[4], const double (&Fe)[6],
-                       const double (&at)[4], auto &&edge_g) {
+                       const double (&at)[4], auto &&foot_at, auto &&edge_g) {
             const ScalarMem<double> *wr = scalar_mem(W) + K.row * FC, *w0 = wr;
             const uint32_t skin = K.skin;
             double vol = 0.0;
@@ -2748,11 +2799,9 @@ __global__ __launch_bounds__(64 * kFieldWaves, 3) void k_p2p_fields(
                 const int *c = kFv[k];
                 const double mu = K.kap[k] * lam[k];
                 double foot[3], I = -mu * at[k];
+                foot_at(k, mu, foot);
 #pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    foot[j] = fma(-K.G[kEdgeOf[c[j]][k]], mu, lam[c[j]]);
-                    I = fma(foot[j], Fe[kEdgeOf[c[(j + 1) % 3]][c[(j + 2) % 3]]], I);
-                }
+                for (int j = 0; j < 3; ++j) I = fma(foot[j], Fe[kEdgeOf[c[(j + 1) % 3]][c[(j + 2) % 3]]], I);
                 vol = fma(lam[k], I, vol);
                 if (!(skin >> k & 1)) continue;
                 wr += 3 * FC;
@@ -2788,9 +2837,12 @@ __global__ __launch_bounds__(64 * kFieldWaves, 3) void k_p2p_fields(
             const double D = Rc[kEb[e]] - Rc[kEa[e]], S = Rc[kEa[e]] + Rc[kEb[e]], t2 = D * (D * K.il2[e]);
             return fma(fma(S, S, -K.l2[e]) * (1.0 - t2), Fe[e], fma(t2, S, S));
         };
-        uint32_t near = 0;  // tets with a target of this wavefront too close, taken after the others
+        // flat tets, and those with a target of this wavefront too close, are taken after the others
+        const uint32_t flats = kFlat ? ch_flat[ch] : 0;
+        uint32_t near = flats;
 #pragma unroll 1
         for (int j = 0; j < nt; ++j) {
+            if (kFlat && flats >> j & 1) continue;
             const ScalarMem<NearTet> &K = *scalar_mem(tet + tb + j);
             const uint32_t cn = K.corner;
             double Rc[4];
@@ -2834,7 +2886,8 @@ __global__ __launch_bounds__(64 * kFieldWaves, 3) void k_p2p_fields(
             }
             double Fe[6], at[4];
             series(z, iv, iv, tn, tn, Fe, at);
-            add(K, lam, Fe, at, [&](int e) { return far_g(K, Rc, Fe, e); });
+            add(K, lam, Fe, at, [&](int k, double mu, double (&foot)[3]) { foot_of(K, lam, k, mu, foot); },
+                [&](int e) { return far_g(K, Rc, Fe, e); });
         }
         // the shifted forms (see k_p2p_topo), or closer still the branch-free
         // forms of the pair formula
@@ -2930,7 +2983,24 @@ __global__ __launch_bounds__(64 * kFieldWaves, 3) void k_p2p_fields(
                                                                        dt(i0, i2) * Rc[i1] + dt(i1, i2) * Rc[i0]);
                 }
             }
-            add(K, lam, Fe, at, [&](int e) { return gp[e]; });
+            const int32_t fl = kFlat ? K.flat : -1;
+            add(K, lam, Fe, at,
+                [&](int k, double mu, double (&foot)[3]) {
+                    if (fl < 0) {
+                        foot_of(K, lam, k, mu, foot);
+                        return;
+                    }
+                    const ScalarMem<NearFlat> &P = *scalar_mem(flat + fl);
+                    foot[0] = 1.0;
+#pragma unroll
+                    for (int j = 1; j < 3; ++j) {
+                        foot[j] = P.f[k][j - 1][0];
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) foot[j] = fma(P.f[k][j - 1][1 + q], y[q] - K.c[q], foot[j]);
+                        foot[0] -= foot[j];
+                    }
+                },
+                [&](int e) { return gp[e]; });
         }
     }
     asm volatile("" ::"v"(seen));
@@ -3481,9 +3551,10 @@ void run_p2p_fields(DevicePlan &dp, const double *M, int32_t F, double *u, const
                 constexpr int FC = decltype(c)::value;
                 k_near_weights<FC><<<dim3((unsigned)((hp.n_tets * FC + 255) / 256)), dim3(256), 0, st>>>(
                     dp.near_tet, hp.n_tets, dp.tet_xyz, dp.tet_node, M, hp.n_nodes, f, F, dp.near_w);
-                k_p2p_fields<FC><<<dim3(xcd_grid((dp.n_topo_items + kFieldWaves - 1) / kFieldWaves)), dim3(64 * kFieldWaves), 0, st>>>(
-                    dp.topo_item, dp.n_topo_items, dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.near_tet, dp.near_w,
-                    dp.p2p_idx, dp.tgt_xyz, perm, hp.n_targets, f, F, u);
+                const auto kernel = dp.near_flat ? k_p2p_fields<FC, true> : k_p2p_fields<FC, false>;
+                kernel<<<dim3(xcd_grid((dp.n_topo_items + kFieldWaves - 1) / kFieldWaves)), dim3(64 * kFieldWaves), 0, st>>>(
+                    dp.topo_item, dp.n_topo_items, dp.topo_ch_i, dp.topo_ch_c, dp.topo_w, dp.near_tet, dp.near_flat,
+                    dp.ch_flat, dp.near_w, dp.p2p_idx, dp.tgt_xyz, perm, hp.n_targets, f, F, u);
             });
             hip_check(hipGetLastError(), "k_p2p_fields launch");
         }
@@ -3896,15 +3967,32 @@ void build_topo_records(DevicePlan &dp, const int32_t *ab, const int32_t *pqr)
     hip_check(hipDeviceSynchronize(), "k_topo_static");
 }
 
-void build_near_tets(const DevicePlan &dp, const uint32_t *corner, const uint8_t *skin, const int64_t *row, NearTet *tet)
+int32_t build_near_tets(const DevicePlan &dp, const uint32_t *corner, const uint8_t *skin, const int64_t *row, NearTet *tet,
+                        uint32_t *ch_flat)
 {
-    if (dp.n_topo_ch == 0) return;
+    if (dp.n_topo_ch == 0) return 0;
     // tets outside every block (leaves without near targets) keep row -1
     hip_check(hipMemset(tet, 0xff, sizeof(NearTet) * (size_t)dp.hp.n_tets), "hipMemset near-field tets");
-    k_tet_static<<<dim3((unsigned)dp.n_topo_ch), dim3(64)>>>(dp.topo_ch_i, dp.topo_ch_c, dp.n_topo_ch, dp.tet_xyz,
-                                                             dp.hp.n_tets, skin, row, corner, tet);
-    hip_check(hipGetLastError(), "k_tet_static launch");
-    hip_check(hipDeviceSynchronize(), "k_tet_static");
+    int32_t *count = nullptr, n = 0;
+    hip_check(hipMalloc(&count, sizeof(n)), "hipMalloc flat tets");
+    hipError_t e = hipMemcpy(count, &n, sizeof(n), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        k_tet_static<<<dim3((unsigned)dp.n_topo_ch), dim3(64)>>>(dp.topo_ch_i, dp.topo_ch_c, dp.n_topo_ch, dp.tet_xyz,
+                                                                 dp.hp.n_tets, skin, row, corner, tet, ch_flat, count);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipMemcpy(&n, count, sizeof(n), hipMemcpyDeviceToHost);
+    (void)hipFree(count);
+    hip_check(e, "k_tet_static");
+    return n;
+}
+
+void build_near_flat(const DevicePlan &dp, const NearTet *tet, NearFlat *flat)
+{
+    k_flat_static<<<dim3((unsigned)dp.n_topo_ch), dim3(64)>>>(dp.topo_ch_i, dp.topo_ch_c, dp.n_topo_ch, dp.tet_xyz,
+                                                              dp.hp.n_tets, tet, flat);
+    hip_check(hipGetLastError(), "k_flat_static launch");
+    hip_check(hipDeviceSynchronize(), "k_flat_static");
 }
 
 void build_m2l_table(DevicePlan &dp)
