@@ -626,15 +626,17 @@ int64_t tfmm_plan_lists(tfmm_plan plan, int32_t kind, int32_t *out)
     }
     if (kind == 3) {  // the pairs as the packed form (one field, the plan's order) schedules them
         tfmm::M2LPacks pk;
+        std::vector<int32_t> item;
         try {
-            tfmm::build_m2l_packs(hp, tfmm::m2l_pack_slots(hp.p), 16, plan->dp.m2l_max_grp, pk);
+            tfmm::build_m2l_packs(hp, tfmm::m2l_pack_slots(hp.p), 16, pk);
+            item = tfmm::m2l_pack_items(pk.blk_grp, tfmm::m2l_pack_cut(pk.npairs, 1, 1, plan->dp.m2l_max_grp));
         } catch (const tfmm::PlanError &e) {
             return set_error(e.code, e.msg);
         }
         int64_t k = 0;
-        for (size_t i = 0; 3 * i < pk.item.size(); ++i) {
-            const int32_t blk = pk.item[3 * i];
-            for (int32_t g = pk.item[3 * i + 1]; g < pk.item[3 * i + 2]; ++g)
+        for (size_t i = 0; 3 * i < item.size(); ++i) {
+            const int32_t blk = item[3 * i];
+            for (int32_t g = item[3 * i + 1]; g < item[3 * i + 2]; ++g)
                 for (int s = 0; s < pk.tpg; ++s) {
                     const int32_t b = pk.grp_src[(size_t)g * pk.tpg + s];
                     if (b < 0) continue;

@@ -162,19 +162,27 @@ struct DevicePlan {
     // M2L packed by key in blocks of target cells (FP64 translations of fewer
     // than 16 fields): per field width fpt = 1, 2, 4, 8 (built on
     // demand), and per level when the levels have their own orders; the
-    // reduced locals Lr [F][C][lrs] they accumulate into
+    // reduced locals Lr [F][C][lrs] they accumulate into.  The groups serve all
+    // evaluations of a width; their cut into work items depends on the number of
+    // fields (m2l_pack_cut), so a list keeps the items of every cut asked for (at
+    // most one a pass count, fifteen, of one schedule).
     struct Packs {
+        struct Items {
+            int cut = 0;
+            int32_t *item = nullptr, n = 0;
+        };
         int nb = 0, tpg = 0, max_grp = 0, p = 0;
-        int32_t *blk_cells = nullptr, *item = nullptr, *grp_key = nullptr, *grp_src = nullptr;
+        int32_t *blk_cells = nullptr, *grp_key = nullptr, *grp_src = nullptr;
         uint8_t *grp_slot = nullptr;
-        int32_t nitems = 0;
+        std::vector<int32_t> blk_grp;
+        std::vector<Items> items;
         int64_t ngrp = 0, npairs = 0;
         int64_t bytes = 0;
     };
     Packs m2l_packs[4];  // fpt = 1, 2, 4, 8
     std::vector<Packs> lvl_packs;
     bool m2l_pack = true;  // schedule knob: the packed form where it applies
-    int m2l_max_grp = 1024;  // groups per packed work item, at most (see build_packs)
+    int m2l_max_grp = 1024;  // groups per packed work item, at most (see m2l_pack_cut)
     double *Lr = nullptr;
     int32_t lr_cap = 0;
     int m2l_precision = 0;  // TFMM_M2L_*

@@ -3701,18 +3701,34 @@ void launch_m2l_t(DevicePlan &dp, const DevicePlan::Tiles &tl, const T *D, const
     }
 }
 
+int pack_cut(const DevicePlan &dp, const DevicePlan::Packs &k, int32_t F)
+{
+    return m2l_pack_cut((int64_t)dp.hp.m2l_src.size(), 16 / k.tpg, F, dp.m2l_max_grp);
+}
+
+// The work items of list k for F fields, null if they were not made.
+const DevicePlan::Packs::Items *pack_items(const DevicePlan &dp, const DevicePlan::Packs &k, int32_t F)
+{
+    const int cut = pack_cut(dp, k, F);
+    for (const auto &it : k.items)
+        if (it.cut == cut) return &it;
+    return nullptr;
+}
+
 // The translations of one pack list at order p (the plan's or a level's).
 void launch_m2l_pack(DevicePlan &dp, const DevicePlan::Packs &k, int fpt, int32_t F, hipStream_t st, int p)
 {
     const HostPlan &hp = dp.hp;
-    if (k.nitems == 0) return;
+    const DevicePlan::Packs::Items *it = pack_items(dp, k, F);
+    if (!it) throw DeviceError{"M2L work items not prepared"};
+    if (it->n == 0) return;
     if (k.nb * fpt != m2l_pack_slots(p) || k.tpg * fpt != 16 || k.p != p)
         throw DeviceError{"M2L packs do not match the translation order"};
     const unsigned groups = (unsigned)((F + fpt - 1) / fpt);
     with_order(p, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
-        k_m2l_pack<P><<<dim3((unsigned)k.nitems, groups), dim3(64 * kM2LPWaves), 0, st>>>(
-            k.item, k.nitems, k.blk_cells, k.nb, k.tpg, k.grp_key, k.grp_src, k.grp_slot, dp.m2l_keys, dp.m2l_D,
+        k_m2l_pack<P><<<dim3((unsigned)it->n, groups), dim3(64 * kM2LPWaves), 0, st>>>(
+            it->item, it->n, k.blk_cells, k.nb, k.tpg, k.grp_key, k.grp_src, k.grp_slot, dp.m2l_keys, dp.m2l_D,
             m2l_table_width(hp.p), dp.Qt, dp.qpad, (int64_t)hp.cells.size(), fpt, F, dp.Lr, m2l_nrows(hp.p));
     });
     hip_check(hipGetLastError(), "k_m2l_pack launch");
@@ -4069,9 +4085,21 @@ const std::vector<DevicePlan::Tiles> &ensure_m2l_level_tiles(DevicePlan &dp, int
     return dp.lvl_tiles;
 }
 
+static void free_pack_items(DevicePlan &dp, DevicePlan::Packs &k)
+{
+    for (auto &it : k.items) {
+        if (it.item) (void)hipFree(it.item);
+        const int64_t b = (int64_t)(3 * sizeof(int32_t)) * it.n;
+        k.bytes -= b;
+        dp.device_bytes -= b;
+    }
+    k.items.clear();
+}
+
 static void free_packs(DevicePlan &dp, DevicePlan::Packs &k)
 {
-    void *q[] = {k.blk_cells, k.item, k.grp_key, k.grp_src, k.grp_slot};
+    free_pack_items(dp, k);
+    void *q[] = {k.blk_cells, k.grp_key, k.grp_src, k.grp_slot};
     for (void *x : q)
         if (x) (void)hipFree(x);
     dp.device_bytes -= k.bytes;
@@ -4090,42 +4118,54 @@ void free_m2l_packs(DevicePlan &dp)
     if (any) ++dp.schedule_gen;  // a captured graph may hold them
 }
 
-// Packs of fpt fields for translations of order p (all levels, or one).
-static void build_packs(DevicePlan &dp, int fpt, int32_t F, int p, int only_level, DevicePlan::Packs &k)
+template <typename E>
+static void upload_pack_list(DevicePlan &dp, DevicePlan::Packs &k, const std::vector<E> &v, E *&d)
 {
-    // Work items of at most m2l_max_grp groups, fewer on small meshes: 512 items
-    // are two rounds of the chip's workgroups; 48 groups, six a wavefront, are the
-    // least that carry an item's clearing and summing up.  (M2L of an 8^3 cube, 6,400
-    // groups: 64 us in items of 256, 36 in items of 48.  A batch of 170,000 groups:
-    // .37 ms in items of 256, .45 in items of 166.  The 40^3 cube, 1.2 million groups:
-    // 1.98 ms in items of 256, 1.69 in items of 1024; the 16,000 sums of a block are
-    // added to memory once an item.)
-    const int64_t groups = (int64_t)dp.hp.m2l_src.size() * fpt / 16 * ((F + fpt - 1) / fpt);
-    const int cut = (int)std::min<int64_t>(dp.m2l_max_grp, std::max<int64_t>(48, groups / 512));
+    const size_t b = sizeof(E) * std::max<size_t>(v.size(), 1);
+    hip_check(hipMalloc(&d, b), "hipMalloc M2L packs");
+    k.bytes += (int64_t)b;
+    dp.device_bytes += (int64_t)b;
+    if (!v.empty()) hip_check(hipMemcpy(d, v.data(), sizeof(E) * v.size(), hipMemcpyHostToDevice), "hipMemcpy M2L packs");
+}
+
+// Packs of fpt fields for translations of order p (all levels, or one).
+static void build_packs(DevicePlan &dp, int fpt, int p, int only_level, DevicePlan::Packs &k)
+{
     M2LPacks h;
-    build_m2l_packs(dp.hp, m2l_pack_slots(p) / fpt, 16 / fpt, cut, h, only_level);
-    auto up = [&](const auto &v, auto *&d) {
-        using E = typename std::decay_t<decltype(v)>::value_type;
-        const size_t b = sizeof(E) * std::max<size_t>(v.size(), 1);
-        hip_check(hipMalloc(&d, b), "hipMalloc M2L packs");
-        k.bytes += (int64_t)b;
-        dp.device_bytes += (int64_t)b;
-        if (!v.empty())
-            hip_check(hipMemcpy(d, v.data(), sizeof(E) * v.size(), hipMemcpyHostToDevice), "hipMemcpy M2L packs");
-    };
-    up(h.blk_cells, k.blk_cells);
-    up(h.item, k.item);
-    up(h.grp_key, k.grp_key);
-    up(h.grp_src, k.grp_src);
-    up(h.grp_slot, k.grp_slot);
+    build_m2l_packs(dp.hp, m2l_pack_slots(p) / fpt, 16 / fpt, h, only_level);
+    upload_pack_list(dp, k, h.blk_cells, k.blk_cells);
+    upload_pack_list(dp, k, h.grp_key, k.grp_key);
+    upload_pack_list(dp, k, h.grp_src, k.grp_src);
+    upload_pack_list(dp, k, h.grp_slot, k.grp_slot);
+    k.blk_grp.swap(h.blk_grp);
     k.nb = h.nb;
     k.tpg = h.tpg;
-    k.max_grp = dp.m2l_max_grp;
     k.p = p;
-    k.nitems = (int32_t)(h.item.size() / 3);
     k.ngrp = (int64_t)h.grp_key.size();
-    k.npairs = 0;
-    for (int32_t s : h.grp_src) k.npairs += s >= 0;
+    k.npairs = h.npairs;
+}
+
+// The work items of list k for F fields; those of another schedule's cap are freed.
+static void ensure_pack_items(DevicePlan &dp, DevicePlan::Packs &k, int32_t F)
+{
+    if (k.max_grp != dp.m2l_max_grp) {
+        if (!k.items.empty()) ++dp.schedule_gen;  // a captured graph may hold them
+        free_pack_items(dp, k);
+        k.max_grp = dp.m2l_max_grp;
+    }
+    if (pack_items(dp, k, F)) return;
+    const int cut = pack_cut(dp, k, F);
+    const std::vector<int32_t> h = m2l_pack_items(k.blk_grp, cut);
+    k.items.push_back({0, nullptr, 0});
+    DevicePlan::Packs::Items &it = k.items.back();
+    if (!h.empty()) {
+        hip_check(hipMalloc(&it.item, sizeof(int32_t) * h.size()), "hipMalloc M2L work items");
+        it.n = (int32_t)(h.size() / 3);
+        k.bytes += (int64_t)(sizeof(int32_t) * h.size());
+        dp.device_bytes += (int64_t)(sizeof(int32_t) * h.size());
+        hip_check(hipMemcpy(it.item, h.data(), sizeof(int32_t) * h.size(), hipMemcpyHostToDevice), "hipMemcpy M2L work items");
+    }
+    it.cut = cut;  // last: found only when complete
 }
 
 static void ensure_m2l_packs(DevicePlan &dp, int32_t F)
@@ -4135,23 +4175,25 @@ static void ensure_m2l_packs(DevicePlan &dp, int32_t F)
     const int fpt = m2l_pack_fpt(F);
     if (!dp.level_orders) {
         DevicePlan::Packs &k = dp.m2l_packs[m2l_pack_slot(fpt)];
-        if (k.nb == 0 || k.max_grp != dp.m2l_max_grp || k.p != hp.p) {
+        if (k.nb == 0 || k.p != hp.p) {
             ++dp.schedule_gen;
             free_packs(dp, k);
-            build_packs(dp, fpt, F, hp.p, -1, k);
+            build_packs(dp, fpt, hp.p, -1, k);
         }
+        ensure_pack_items(dp, k, F);
     } else {
         bool ok = dp.lvl_packs.size() == (size_t)hp.depth + 1;
         for (size_t lv = 0; ok && lv < dp.lvl_packs.size(); ++lv) {
             const DevicePlan::Packs &k = dp.lvl_packs[lv];
-            ok = k.tpg * fpt == 16 && k.max_grp == dp.m2l_max_grp && k.p == dp.lo.q[lv];
+            ok = k.tpg * fpt == 16 && k.p == dp.lo.q[lv];
         }
         if (!ok) {
             ++dp.schedule_gen;
             for (auto &k : dp.lvl_packs) free_packs(dp, k);
             dp.lvl_packs.assign((size_t)hp.depth + 1, DevicePlan::Packs{});
-            for (int lv = 0; lv <= hp.depth; ++lv) build_packs(dp, fpt, F, dp.lo.q[lv], lv, dp.lvl_packs[lv]);
+            for (int lv = 0; lv <= hp.depth; ++lv) build_packs(dp, fpt, dp.lo.q[lv], lv, dp.lvl_packs[lv]);
         }
+        for (auto &k : dp.lvl_packs) ensure_pack_items(dp, k, F);
     }
 }
 

@@ -478,9 +478,9 @@ void build_m2l_tiles(const HostPlan &hp, int tpt, int max_ent, M2LTiles &out, in
     }
 }
 
-void build_m2l_packs(const HostPlan &hp, int nb, int tpg, int max_grp, M2LPacks &out, int only_level)
+void build_m2l_packs(const HostPlan &hp, int nb, int tpg, M2LPacks &out, int only_level)
 {
-    if (nb < 1 || nb > 256 || tpg < 1 || max_grp < 1) throw PlanError{TFMM_EINVAL, "bad M2L pack shape"};
+    if (nb < 1 || nb > 256 || tpg < 1) throw PlanError{TFMM_EINVAL, "bad M2L pack shape"};
     out = M2LPacks{};
     out.nb = nb;
     out.tpg = tpg;
@@ -493,8 +493,6 @@ void build_m2l_packs(const HostPlan &hp, int nb, int tpg, int max_grp, M2LPacks 
         if (only_level >= 0 && c.level != only_level) continue;
         lvl[c.level].push_back({morton((uint32_t)c.ix, (uint32_t)c.iy, (uint32_t)c.iz), (int32_t)a});
     }
-    std::vector<std::array<int32_t, 2>> rng;  // items: group range
-    std::vector<int32_t> iblk, lev;
     // A block's pairs by key, then by slot class (slot mod tpg), then slot: the
     // pairs of a key are dealt round-robin over its ceil(n / tpg) groups, so that a
     // group's slots differ mod tpg wherever the class counts allow (its accumulator
@@ -507,7 +505,6 @@ void build_m2l_packs(const HostPlan &hp, int nb, int tpg, int max_grp, M2LPacks 
         std::sort(kv.second.begin(), kv.second.end());
         const auto &v = kv.second;
         for (size_t b0 = 0; b0 < v.size(); b0 += (size_t)nb) {
-            const int32_t blk = (int32_t)(out.blk_cells.size() / nb);
             const int n_slot = (int)(std::min(v.size(), b0 + (size_t)nb) - b0);
             used.clear();
             for (int i = 0; i < nb; ++i) {
@@ -551,22 +548,48 @@ void build_m2l_packs(const HostPlan &hp, int nb, int tpg, int max_grp, M2LPacks 
                 beg = at[k];
                 at[k] = 0;
             }
-            const int32_t g1 = (int32_t)out.grp_key.size();
             if (out.grp_key.size() > (size_t)INT32_MAX / 16) throw PlanError{TFMM_ENOTSUP, "too many M2L groups"};
-            // runs of about equal size, none above max_grp
-            const int32_t n = g1 - g0, parts = (n + max_grp - 1) / std::max(max_grp, 1);
-            for (int32_t p = 0; p < parts; ++p) {
-                rng.push_back({g0 + (int32_t)((int64_t)n * p / parts), g0 + (int32_t)((int64_t)n * (p + 1) / parts)});
-                iblk.push_back(blk);
-                lev.push_back(kv.first);
-            }
+            out.npairs += total;
+            out.blk_grp.push_back(kv.first);
+            out.blk_grp.push_back((int32_t)out.grp_key.size());
         }
     }
-    for (int32_t i : xcd_dispatch_order(rng, lev)) {
-        out.item.push_back(i >= 0 ? iblk[i] : 0);
-        out.item.push_back(i >= 0 ? rng[i][0] : 0);
-        out.item.push_back(i >= 0 ? rng[i][1] : 0);
+}
+
+int m2l_pack_cut(int64_t npairs, int fpt, int32_t F, int max_grp)
+{
+    // Fewer groups an item on small meshes: 512 items are two rounds of the chip's
+    // workgroups; 48 groups, six a wavefront, are the least that carry an item's
+    // clearing and summing up.  (M2L of an 8^3 cube, 6,400 groups: 64 us in items of
+    // 256, 36 in items of 48.  A batch of 170,000 groups: .37 ms in items of 256, .45
+    // in items of 166.  The 40^3 cube, 1.2 million groups: 1.98 ms in items of 256,
+    // 1.69 in items of 1024; the 16,000 sums of a block are added to memory once an
+    // item.)
+    const int64_t groups = npairs * fpt / 16 * ((F + fpt - 1) / fpt);
+    return (int)std::min<int64_t>(max_grp, std::max<int64_t>(48, groups / 512));
+}
+
+std::vector<int32_t> m2l_pack_items(const std::vector<int32_t> &blk_grp, int cut)
+{
+    std::vector<std::array<int32_t, 2>> rng;  // items: group range
+    std::vector<int32_t> iblk, lev, out;
+    int32_t g0 = 0;
+    for (size_t b = 0; 2 * b < blk_grp.size(); ++b) {
+        // runs of about equal size, none above cut
+        const int32_t n = blk_grp[2 * b + 1] - g0, parts = (n + cut - 1) / cut;
+        for (int32_t p = 0; p < parts; ++p) {
+            rng.push_back({g0 + (int32_t)((int64_t)n * p / parts), g0 + (int32_t)((int64_t)n * (p + 1) / parts)});
+            iblk.push_back((int32_t)b);
+            lev.push_back(blk_grp[2 * b]);
+        }
+        g0 += n;
     }
+    for (int32_t i : xcd_dispatch_order(rng, lev)) {
+        out.push_back(i >= 0 ? iblk[i] : 0);
+        out.push_back(i >= 0 ? rng[i][0] : 0);
+        out.push_back(i >= 0 ? rng[i][1] : 0);
+    }
+    return out;
 }
 
 

@@ -85,19 +85,25 @@ struct M2LTiles {
 // in Morton order; its translations are sorted by key, and the pairs of one
 // key are packed into groups of tpg = 16 / fpt (target slot, source cell)
 // pairs, so that every matrix-core column of a group carries a translation
-// except in the last group of each key.  A work item is a run of at most
-// max_grp groups of one block; items are ordered for the XCDs as the tiles.
+// except in the last group of each key.
 struct M2LPacks {
     int nb = 0, tpg = 0;
+    int64_t npairs = 0;
     std::vector<int32_t> blk_cells;  // [nblk][nb] target cells (-1: empty slot)
-    std::vector<int32_t> item;       // [nitems][3] block, group begin, group end
+    std::vector<int32_t> blk_grp;    // [nblk][2] level, group end (it begins where the block before ends)
     std::vector<int32_t> grp_key;    // [ngrp]
     std::vector<int32_t> grp_src;    // [ngrp][tpg] source cell (-1: empty)
     std::vector<uint8_t> grp_slot;   // [ngrp][tpg] target slot in the block
 };
 // LDS accumulator slots (target cell x field) of one block at order p.
 constexpr int m2l_pack_slots(int p) { return p <= 8 ? 256 : 128; }
-void build_m2l_packs(const HostPlan &hp, int nb, int tpg, int max_grp, M2LPacks &out, int only_level = -1);
+void build_m2l_packs(const HostPlan &hp, int nb, int tpg, M2LPacks &out, int only_level = -1);
+// Groups per work item of a list of npairs translations, fpt fields a group, for an
+// evaluation of F fields; max_grp: the schedule's cap.
+int m2l_pack_cut(int64_t npairs, int fpt, int32_t F, int max_grp);
+// Work items [nitems][3] (block, group begin, group end): runs of at most cut groups
+// of one block, ordered for the XCDs as the tiles.
+std::vector<int32_t> m2l_pack_items(const std::vector<int32_t> &blk_grp, int cut);
 
 // Mesh entities of the near-field source blocks.  Each P2P block (<= 64 tets
 // of one leaf, [tbeg, tend) in octree order) is cut into chunks of at most
