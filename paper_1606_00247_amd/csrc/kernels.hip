@@ -3703,7 +3703,7 @@ void launch_m2l_t(DevicePlan &dp, const DevicePlan::Tiles &tl, const T *D, const
 
 int pack_cut(const DevicePlan &dp, const DevicePlan::Packs &k, int32_t F)
 {
-    return m2l_pack_cut((int64_t)dp.hp.m2l_src.size(), 16 / k.tpg, F, dp.m2l_max_grp);
+    return m2l_pack_cut(k.npairs, 16 / k.tpg, F, dp.m2l_max_grp);
 }
 
 // The work items of list k for F fields, null if they were not made.

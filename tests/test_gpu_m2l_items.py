@@ -45,3 +45,22 @@ def test_field_counts_in_turn(torch_dev):
     assert held[0] == held[1] == held[2]
     for v in u[1:]:
         assert np.abs(v - u[0]).max() <= 1e-13 * np.abs(u[0]).max()
+
+
+def test_level_lists_cut_by_their_own_translations(torch_dev):
+    """With orders per level every level's list is cut by the translations of
+    that level: where none has enough for more than 48 groups an item, the
+    largest cap and a cap of 48 give the same items."""
+    T, nodes, plan = _plan(10)
+    pairs = T.tfmm_plan_lists(plan, "m2l")[:, 0]
+    level, total = np.bincount(pairs).max(), len(pairs)
+    F = [f for f in range(1, 16, 2) if level * f // 16 // 512 <= 48 and total * f // 16 // 512 >= 50]
+    assert F, (level, total)
+    T.tfmm_plan_set_level_orders(plan, [4] * T.tfmm_plan_stats(plan)["depth"] + [3])
+    held = []
+    for cap in (4096, 48):
+        T.tfmm_plan_set_schedule(plan, 256, 0, 1, cap)
+        print("level lists", cap, F[0], flush=True)
+        _evaluate(torch_dev, T, plan, nodes, F[0])
+        held.append(T.tfmm_plan_stats(plan)["device_bytes"])
+    assert held[0] == held[1]
