@@ -4374,8 +4374,17 @@ void autotune(DevicePlan &dp, hipStream_t st)
         dp.m2l_max_ent = best_ent;
         dp.m2l_pack = true;
         if (m2l_packed(dp, 1)) {
-            for (int grp : {512, 1024}) {
+            std::vector<std::vector<int>> tried;  // caps with the same cuts are one schedule, the plan's own first
+            for (int grp : {best_grp, 1024, 512}) {
                 dp.m2l_max_grp = grp;
+                prepare_evaluate(dp, 1);
+                std::vector<int> cuts;
+                if (dp.level_orders)
+                    for (const auto &k : dp.lvl_packs) cuts.push_back(pack_cut(dp, k, 1));
+                else
+                    cuts.push_back(pack_cut(dp, dp.m2l_packs[0], 1));
+                if (std::find(tried.begin(), tried.end(), cuts) != tried.end()) continue;
+                tried.push_back(cuts);
                 const float t = time_config(dp, M, u, st);
                 if (t < best) best = t, best_grp = grp, best_pack = true;
             }

@@ -64,3 +64,14 @@ def test_level_lists_cut_by_their_own_translations(torch_dev):
         _evaluate(torch_dev, T, plan, nodes, F[0])
         held.append(T.tfmm_plan_stats(plan)["device_bytes"])
     assert held[0] == held[1]
+
+
+def test_autotune_leaves_equal_schedules_alone(torch_dev):
+    """On a small mesh every cap gives the same items: tuning times them once
+    and keeps the plan's cap."""
+    for _ in range(6):
+        T, nodes, plan = _plan(5, 3, 16)
+        cap = T.tfmm_plan_stats(plan)["m2l_groups_per_item"]
+        T.tfmm_plan_autotune(plan)
+        assert T.tfmm_plan_stats(plan)["m2l_groups_per_item"] == cap
+        T.tfmm_plan_destroy(plan)
