@@ -291,8 +291,9 @@ def tfmm_plan_autotune(plan, stream=None):
     _check(_load().tfmm_plan_autotune(plan.handle, _stream_handle(stream, dev)))
 
 
-def tfmm_plan_set_schedule(plan, m2l_keys_per_item, p2p_wide, m2l_packed=1, m2l_groups_per_item=256):
-    """Set the schedule knobs tfmm_plan_autotune picks (same results, other launch shapes)."""
+def tfmm_plan_set_schedule(plan, m2l_keys_per_item, p2p_wide, m2l_packed=1, m2l_groups_per_item=1024):
+    """Set the schedule knobs tfmm_plan_autotune picks (same results, other launch shapes);
+    those left out take a new plan's values."""
     _check(_load().tfmm_plan_set_schedule(plan.handle, int(m2l_keys_per_item), int(p2p_wide), int(m2l_packed),
                                           int(m2l_groups_per_item)))
 

@@ -1,0 +1,17 @@
+"""Setting one schedule knob leaves the M2L item size at the plan's default."""
+import pytest
+
+import meshgen
+
+pytestmark = pytest.mark.gpu
+
+
+def test_item_size_stays():
+    import paper_1606_00247_amd as T
+
+    nodes, tets = meshgen.box_mesh(4, seed=1)
+    plan = T.tfmm_plan_create(nodes, tets, p=3, leaf_size=16, theta=0.5)
+    size = T.tfmm_plan_stats(plan)["m2l_groups_per_item"]
+    T.tfmm_plan_set_schedule(plan, 512, 0)
+    st = T.tfmm_plan_stats(plan)
+    assert (st["m2l_keys_per_item"], st["m2l_groups_per_item"]) == (512, size)
