@@ -80,7 +80,6 @@ constexpr MiTable kMi = make_mi();
 __host__ __device__ constexpr int mi_x(int m) { return kMi.v[m][0]; }
 __host__ __device__ constexpr int mi_y(int m) { return kMi.v[m][1]; }
 __host__ __device__ constexpr int mi_z(int m) { return kMi.v[m][2]; }
-__constant__ BinomTable c_bin = make_binom();
 
 __host__ __device__ constexpr int mi_index(int nx, int ny, int nz)
 {
