@@ -245,7 +245,6 @@ struct DevicePlan {
     // quadrature rule for the moments: [nq][4] = lambda1, lambda2, lambda3, weight
     double *quad = nullptr;
     int32_t nq = 0;
-    // far-pair rules of the direct sum (degrees 11, 9, 7 concatenated, rows as quad)
     double *far_rule = nullptr;  // tables of the direct sum's far rules (far_offset)
     // lumped node volumes (sum of V_T / 4 over the tets of a node), built on
     // the first nodal-field request

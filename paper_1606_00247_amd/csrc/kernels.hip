@@ -8,9 +8,10 @@
 //   l2l   binomial shift of a local expansion to the child centres
 //   l2p   evaluation of the local expansion at the targets (adds into u)
 //   p2p   exact near-field tet-to-target potential (Sec. 2.1), source-major:
-//         one wavefront per chunk of a source leaf's tets and 64 targets, the
-//         tets' (one field: their shared nodes', edges' and faces') data read
-//         through the scalar unit, atomically accumulated into u
+//         one wavefront per 64 targets and block of up to 64 tets of a source
+//         leaf, taken chunk by chunk, the tets' (one field: their shared nodes',
+//         edges' and faces') data read through the scalar unit, atomically
+//         accumulated into u
 //
 // Multi-indices |n| <= p are stored in graded order: degree ascending, within
 // a degree n_x descending, then n_y descending.  idx(n) = d(d+1)(d+2)/6 +
@@ -883,7 +884,7 @@ struct M2LCols {
 };
 
 // Column steps of wavefront W (see k_m2l_mfma): KJ of them, ks = W + kM2LWaves j,
-// whose multipoles lie together in a row of Qr (m2l_tile_slot).  The wavefronts
+// whose multipoles lie together in a row of Qr (m2l_tile_col).  The wavefronts
 // share nothing until their sums meet: each gathers its A operands from its own
 // copy of the key's derivative row in LDS and loads its B operands in place, two
 // entries ahead, in one of two register sets.  (With operands staged for all four
@@ -1348,9 +1349,10 @@ __global__ __launch_bounds__(256) void k_lr_expand(const double *__restrict__ Lr
 // steps consume them.  (With two
 // wavefronts splitting and staging both operands for one group, the LDS was busy
 // 64% of the time and the matrix cores 10%: 64 fields, order 8, 1.1 million
-// translations, BF16x3: 6.3 ms of M2L, now 2.41.)  Bound by the multipoles, of which
-// half come from beyond the L2; two field groups a wavefront, with half the gathers,
-// keep twice as many of them in use at a time and take 2.64 ms.
+// translations, BF16x3: 6.3 ms of M2L, now 2.41.)  Bound by the multipoles: 42% of
+// the lines read, 12.6 GB, come from beyond the L2, at 6.4 TB/s; the matrix cores are
+// busy 0.26 of the time, the vector unit 0.53.  Two field groups a wavefront, with
+// half the gathers, keep twice as many multipoles in use at a time and take 2.64 ms.
 // ---------------------------------------------------------------------------
 using bf16x8 = __bf16 __attribute__((ext_vector_type(8)));
 
@@ -2184,7 +2186,8 @@ __global__ __launch_bounds__(64) void k_topo_coef(const int32_t *__restrict__ ch
 // second loop.  The block's target list is ordered by distance, so that few
 // wavefronts hold such targets.
 // Bound: FP64 issue, about 45 slots a (target, edge) and 43 a (target, face);
-// the vector unit is busy 0.77 of the time.  40^3 cube (160M pairs, 11.7 tets a
+// the vector unit is busy 0.86 of the time on the 40^3 cube, 0.91 on the sphere
+// below.  40^3 cube (160M pairs, 11.7 tets a
 // block): 4.05 -> 2.1 ms against the form with difference vectors, cross
 // products and branch-free selects; 14.2 -> 11.0 ms on 853M pairs of a sphere
 // with 45 tets a block.  4 wavefronts a SIMD without spills beat 5 with 13
@@ -2711,9 +2714,10 @@ __device__ __forceinline__ void atan_poly(double (&q)[4], const double (&z)[4])
 // tets of a chunk are taken one at a time, all edges and faces of a tet side
 // by side, those with a close target in a second loop.  Bound: FP64 issue, about
 // 390 slots a (target, tet) pair and 6 more a field (the whole pair formula in
-// every lane took 935 and 27); the vector unit is busy 0.63 of the time, the
-// rest is waiting for the scalar reads of geometry and weights.  16 fields on
-// a 26^3 cube (81M pairs): 4.8 -> 2.0 ms; 5 fields on a 21^3 cube: 1.77 ->
+// every lane took 935 and 27); the vector unit is busy 0.70 of the time (16
+// fields on a 26^3 cube; 0.55 on an 18^3 cube, where the last wavefronts leave
+// the chip half empty), the rest is waiting for the scalar reads of geometry and
+// weights.  16 fields on a 26^3 cube (81M pairs): 4.8 -> 2.0 ms; 5 fields on a 21^3 cube: 1.77 ->
 // 0.57; 64 on an 18^3 cube: 9.9 -> 4.6.  32 fields a pass leave two wavefronts
 // a SIMD and a quarter of the rate.  Four wavefronts a workgroup: the kernel
 // alone takes the same, but the expansion kernels beside it find room sooner
@@ -3563,10 +3567,11 @@ void run_p2p_fields(DevicePlan &dp, const double *M, int32_t F, double *u, const
 
 // Whether an evaluation keeps its sums in the octree's order (dp.u_tree) and puts
 // them in the caller's order at the end: the near field of several fields, whose
-// adds (a field and target of every work item) then fall in shared lines.  64
-// fields, 35,000 tets: near field 4.4 ms in the caller's order, 3.3 in the tree's,
-// the last step 6 us; 16 fields, 105,000 tets: 2.05 and 2.00 ms; 5 fields, 56,000
-// tets: .555 and .558 ms, where the adds are too few to pay for the step.
+// adds (a field and target of every work item) then fall in shared lines.  Whole
+// evaluations, caller's order and tree's, us: a 12^3 cube with 5 fields 346 and 349,
+// 7 381 and 378, 8 412 and 404, 16 530 and 492; a 21^3 cube with 6 fields 1,693 and
+// 1,701, 8 2,006 and 1,999, 16 3,127 and 3,057; with fewer fields the adds are too
+// few to pay for the last step.
 constexpr int kInOrderFields = 8;
 bool near_in_order(const DevicePlan &dp, int32_t F)
 {
@@ -3743,8 +3748,10 @@ int m2l_fpt(int32_t F)
 }
 
 // Field width of the packed form for F fields: the width whose passes carry the
-// fewest padded fields, the widest among equals.  (5 fields on a 21^3 cube: two
-// passes of 4 take 1.37 ms, five of 1 1.01.)
+// fewest padded fields, the widest among equals.  Whole evaluations, this width and
+// the largest power of two below F, us: a 12^3 cube with 3 fields 294 and 311, 7 380
+// and 402, 9 433 and 495, 13 492 and 526; a 21^3 cube with 3 fields 1,169 and 1,298,
+// 7 1,975 and 1,943, 9 2,408 and 2,966, 13 2,951 and 3,118.
 int m2l_pack_fpt(int32_t F)
 {
     int best = 1;

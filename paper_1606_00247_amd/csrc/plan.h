@@ -115,7 +115,6 @@ std::vector<int32_t> m2l_pack_items(const std::vector<int32_t> &blk_grp, int cut
 // and 4 faces (face k opposite corner k).  Edges and faces come in pairs, the
 // last listed twice where their number is odd.  The entities' geometry is
 // formed from these on the device.
-// (even numbers of edges and faces: see the pairs above)
 constexpr int kTopoTets = 16, kTopoNodes = 16, kTopoEdges = 48, kTopoFaces = 40;
 struct NearTopo {
     std::vector<int32_t> blk;     // [nblk][4]: chunk begin, chunk end, target begin, target end
