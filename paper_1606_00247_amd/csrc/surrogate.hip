@@ -656,10 +656,14 @@ __global__ __launch_bounds__(64, 3) void k_band_eval(const int32_t *__restrict__
             for (int j = 0; j < kOut; ++j) coef[j] = fma(g, (double)s_y[lane * NPL + j], coef[j]);
         }
     }
-    // contraction with every field, one sum per run of equal targets
+    // contraction with every field, one sum per run of equal targets (a target may
+    // come in several runs of a wavefront, of different blocks: a run is known by
+    // its first lane, not by its target)
     const int key = valid ? s : -1 - lane;
-    const int knext = __shfl_down(key, 1);
+    const int knext = __shfl_down(key, 1), kprev = __shfl_up(key, 1);
     const bool tail = valid && (lane == 63 || knext != key);
+    const uint64_t heads = __ballot(lane == 0 || kprev != key);
+    const int head = 63 - __clzll(heads & ((2ull << lane) - 1));
     const int64_t o = tgt_perm[s];
 #pragma unroll 1
     for (int f = 0; f < F; ++f) {
@@ -673,8 +677,7 @@ __global__ __launch_bounds__(64, 3) void k_band_eval(const int32_t *__restrict__
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const double vo = __shfl_up(val, d);
-            const int ko = __shfl_up(key, d);
-            if (lane >= d && ko == key) val += vo;
+            if (lane - d >= head) val += vo;
         }
         if (tail) atomicAdd(&u[(int64_t)f * N + o], val);
     }
