@@ -135,6 +135,46 @@ static int cell_ring(const Cell &a, const Cell &b)
     return (int)std::min(kRings - 1.0, 4.0 * (g0 * g0 + g1 * g1 + g2 * g2) / (s * s));
 }
 
+std::vector<int32_t> near_targets(const HostPlan &hp, bool by_distance, std::vector<int32_t> *blk)
+{
+    const int64_t C = (int64_t)hp.cells.size();
+    std::vector<int32_t> cnt(C + 1, 0);
+    for (size_t i = 0; i < hp.p2p_b.size(); ++i) cnt[hp.p2p_b[i] + 1]++;
+    for (int64_t c = 0; c < C; ++c) cnt[c + 1] += cnt[c];
+    std::vector<int32_t> tl(hp.p2p_a.size());
+    {
+        std::vector<int32_t> fillp(cnt.begin(), cnt.end() - 1);
+        for (size_t i = 0; i < hp.p2p_b.size(); ++i) tl[fillp[hp.p2p_b[i]]++] = hp.p2p_a[i];
+    }
+    std::vector<int32_t> idx, by_ring;
+    std::vector<int8_t> ring;
+    for (int64_t b = 0; b < C; ++b) {
+        if (cnt[b + 1] == cnt[b]) continue;
+        const int64_t ib = (int64_t)idx.size();
+        int32_t at[kRings + 1] = {0};
+        ring.clear();
+        for (int32_t j = cnt[b]; j < cnt[b + 1]; ++j) {
+            ring.push_back((int8_t)(by_distance ? cell_ring(hp.cells[tl[j]], hp.cells[b]) : 0));
+            ++at[ring.back() + 1];
+        }
+        for (int r = 0; r < kRings; ++r) at[r + 1] += at[r];
+        by_ring.resize(ring.size());
+        for (size_t j = 0; j < ring.size(); ++j) by_ring[at[ring[j]]++] = tl[cnt[b] + j];
+        for (const int32_t a : by_ring)
+            for (int32_t s = hp.cells[a].xbeg; s < hp.cells[a].xend; ++s) idx.push_back(s);
+        const int64_t ie = (int64_t)idx.size();
+        if (ie > INT32_MAX) throw PlanError{TFMM_ENOTSUP, "near-field target list exceeds 2^31 entries"};
+        const Cell &Bc = hp.cells[b];
+        for (int32_t t = Bc.tbeg; blk && t < Bc.tend; t += 64) {
+            blk->push_back(t);
+            blk->push_back(std::min(Bc.tend, t + 64));
+            blk->push_back((int32_t)ib);
+            blk->push_back((int32_t)ie);
+        }
+    }
+    return idx;
+}
+
 void upload_plan(DevicePlan &dp)
 {
     const HostPlan &hp = dp.hp;
@@ -214,43 +254,8 @@ void upload_plan(DevicePlan &dp)
     }
     {
         // P2P: source leaves with their target-leaf lists, cut into blocks of <= 64 tets
-        std::vector<int32_t> cnt(C + 1, 0);
-        for (size_t i = 0; i < hp.p2p_b.size(); ++i) cnt[hp.p2p_b[i] + 1]++;
-        for (int64_t c = 0; c < C; ++c) cnt[c + 1] += cnt[c];
-        std::vector<int32_t> tl(hp.p2p_a.size());
-        {
-            std::vector<int32_t> fillp(cnt.begin(), cnt.end() - 1);
-            for (size_t i = 0; i < hp.p2p_b.size(); ++i) tl[fillp[hp.p2p_b[i]]++] = hp.p2p_a[i];
-        }
-        std::vector<int32_t> blk, idx, by_ring;
-        std::vector<int8_t> ring;
-        for (int64_t b = 0; b < C; ++b) {
-            if (cnt[b + 1] == cnt[b]) continue;
-            const int64_t ib = (int64_t)idx.size();
-            // target leaves by distance: the wavefronts of the nearest take the
-            // near field's closer forms, the others hardly ever do (point
-            // sources have one form and keep the octree's order)
-            int32_t at[kRings + 1] = {0};
-            ring.clear();
-            for (int32_t j = cnt[b]; j < cnt[b + 1]; ++j) {
-                ring.push_back((int8_t)(hp.points ? 0 : cell_ring(hp.cells[tl[j]], hp.cells[b])));
-                ++at[ring.back() + 1];
-            }
-            for (int r = 0; r < kRings; ++r) at[r + 1] += at[r];
-            by_ring.resize(ring.size());
-            for (size_t j = 0; j < ring.size(); ++j) by_ring[at[ring[j]]++] = tl[cnt[b] + j];
-            for (const int32_t a : by_ring)
-                for (int32_t s = hp.cells[a].xbeg; s < hp.cells[a].xend; ++s) idx.push_back(s);
-            const int64_t ie = (int64_t)idx.size();
-            if (ie > INT32_MAX) throw PlanError{TFMM_ENOTSUP, "near-field target list exceeds 2^31 entries"};
-            const Cell &Bc = hp.cells[b];
-            for (int32_t t = Bc.tbeg; t < Bc.tend; t += 64) {
-                blk.push_back(t);
-                blk.push_back(std::min(Bc.tend, t + 64));
-                blk.push_back((int32_t)ib);
-                blk.push_back((int32_t)ie);
-            }
-        }
+        std::vector<int32_t> blk;
+        const std::vector<int32_t> idx = near_targets(hp, !hp.points, &blk);
         // shared mesh entities of the source blocks (single-field near field)
         NearTopo tp;
         if (!hp.points) build_near_topology(hp, blk, tp);  // point sources have no mesh entities

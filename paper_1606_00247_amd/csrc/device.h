@@ -301,6 +301,12 @@ std::vector<int32_t> xcd_dispatch_items(int n);
 // Allocate and upload; hp must be built.  Throws DeviceError.
 void upload_plan(DevicePlan &dp);
 void free_plan(DevicePlan &dp);
+// The target lists of the source leaves, one after the other, and the leaves' blocks
+// [n][4] (tets begin, end, list begin, end).  By distance: the nearest target leaves
+// first, whose wavefronts take the near field's closer forms (the others hardly ever
+// do); point sources have one form, and the surrogate's pairs, which seeded samples
+// are drawn from by their number, keep the octree's order.
+std::vector<int32_t> near_targets(const HostPlan &hp, bool by_distance, std::vector<int32_t> *blk);
 void ensure_expansions(DevicePlan &dp, int32_t F);
 // Device bytes of the buffers that grow with the evaluations asked for (all that
 // dp.device_bytes does not count).

@@ -822,10 +822,15 @@ void build_band_list(DevicePlan &dp, hipStream_t st)
     const int nblk = dp.n_p2p_blk;
     std::vector<int64_t> cnt((size_t)std::max(nblk, 1), 0), off((size_t)std::max(nblk, 1) + 1, 0);
     int64_t *dcnt = nullptr;
+    int32_t *idx = nullptr;
     hip_check(hipMalloc(&dcnt, sizeof(int64_t) * (cnt.size() + 1)), "hipMalloc band counts");
     try {
+        const std::vector<int32_t> list = near_targets(hp, false, nullptr);
         if (nblk > 0) {
-            k_band_count<<<nblk, kBandThreads, 0, st>>>(dp.p2p_blk, nblk, hp.n_tets, dp.tet_xyz, dp.p2p_idx, dp.tgt_xyz,
+            hip_check(hipMalloc(&idx, sizeof(int32_t) * list.size()), "hipMalloc band targets");
+            hip_check(hipMemcpyAsync(idx, list.data(), sizeof(int32_t) * list.size(), hipMemcpyHostToDevice, st),
+                      "hipMemcpy band targets");
+            k_band_count<<<nblk, kBandThreads, 0, st>>>(dp.p2p_blk, nblk, hp.n_tets, dp.tet_xyz, idx, dp.tgt_xyz,
                                                         hp.n_targets, dcnt);
             hip_check(hipGetLastError(), "k_band_count launch");
             hip_check(hipMemcpyAsync(cnt.data(), dcnt, sizeof(int64_t) * nblk, hipMemcpyDeviceToHost, st),
@@ -846,7 +851,7 @@ void build_band_list(DevicePlan &dp, hipStream_t st)
         if (nblk > 0 && n > 0) {
             hip_check(hipMemcpyAsync(dcnt, off.data(), sizeof(int64_t) * nblk, hipMemcpyHostToDevice, st),
                       "hipMemcpy band offsets");
-            k_band_fill<<<nblk, kBandThreads, 0, st>>>(dp.p2p_blk, nblk, hp.n_tets, dp.tet_xyz, dp.p2p_idx, dp.tgt_xyz,
+            k_band_fill<<<nblk, kBandThreads, 0, st>>>(dp.p2p_blk, nblk, hp.n_tets, dp.tet_xyz, idx, dp.tgt_xyz,
                                                        hp.n_targets, dcnt, dp.band_pairs);
             hip_check(hipGetLastError(), "k_band_fill launch");
         }
@@ -859,9 +864,11 @@ void build_band_list(DevicePlan &dp, hipStream_t st)
         hip_check(hipStreamSynchronize(st), "band list");
     } catch (...) {
         (void)hipFree(dcnt);
+        (void)hipFree(idx);
         throw;
     }
     (void)hipFree(dcnt);
+    (void)hipFree(idx);
     dp.band_built = true;
     ++dp.schedule_gen;
 }

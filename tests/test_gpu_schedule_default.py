@@ -6,7 +6,15 @@ import meshgen
 pytestmark = pytest.mark.gpu
 
 
-def test_item_size_stays():
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    return torch, torch.device("cuda:0")
+
+
+def test_item_size_stays(torch_dev):
     import paper_1606_00247_amd as T
 
     nodes, tets = meshgen.box_mesh(4, seed=1)
