@@ -797,8 +797,25 @@ void build_near_topology(const HostPlan &hp, const std::vector<int32_t> &blk, Ne
             edges.clear();
             faces.clear();
             int32_t t = s;
+            double lo[3], hi[3], size = 0.0;  // the chunk's box and the extent of its smallest tet
             for (; t < te && t - s < kTopoTets; ++t) {
                 const int32_t *v = &hp.tet_nodes[4 * (size_t)t];
+                double tl[3], th[3], own = 0.0, all = 0.0;
+                for (int k = 0; k < 3; ++k) {
+                    tl[k] = th[k] = hp.nodes[3 * (size_t)v[0] + k];
+                    for (int c = 1; c < 4; ++c) {
+                        tl[k] = std::min(tl[k], hp.nodes[3 * (size_t)v[c] + k]);
+                        th[k] = std::max(th[k], hp.nodes[3 * (size_t)v[c] + k]);
+                    }
+                    own = std::max(own, th[k] - tl[k]);
+                    if (t > s) {
+                        tl[k] = std::min(tl[k], lo[k]);
+                        th[k] = std::max(th[k], hi[k]);
+                    }
+                    all = std::max(all, th[k] - tl[k]);
+                }
+                if (t > s) own = std::min(own, size);
+                if (t > s && all > kTopoSpan * own) break;
                 // entities this tet would add
                 std::vector<int32_t> nn, ne, nf;
                 for (int c = 0; c < 4; ++c)
@@ -815,6 +832,11 @@ void build_near_topology(const HostPlan &hp, const std::vector<int32_t> &blk, Ne
                 if (nodes.size() + nn.size() > (size_t)kTopoNodes || (edges.size() + ne.size()) / 2 > (size_t)kTopoEdges ||
                     (faces.size() + nf.size()) / 3 > (size_t)kTopoFaces)
                     break;
+                for (int k = 0; k < 3; ++k) {
+                    lo[k] = tl[k];
+                    hi[k] = th[k];
+                }
+                size = own;
                 nodes.insert(nodes.end(), nn.begin(), nn.end());
                 edges.insert(edges.end(), ne.begin(), ne.end());
                 faces.insert(faces.end(), nf.begin(), nf.end());

@@ -114,7 +114,11 @@ std::vector<int32_t> m2l_pack_items(const std::vector<int32_t> &blk_grp, int cut
 // indices of its 6 edges (corner pairs (0,1),(0,2),(0,3),(1,2),(1,3),(2,3))
 // and 4 faces (face k opposite corner k).  Edges and faces come in pairs, the
 // last listed twice where their number is odd.  The entities' geometry is
-// formed from these on the device.
+// formed from these on the device.  A chunk ends before a tet that would make it
+// wider than kTopoSpan times its smallest tet: positions are relative to the
+// chunk's centroid, and tets of bodies far apart in one leaf would lose the digits
+// between the gap and their size (connected tets of one leaf span some 4 to 8).
+constexpr double kTopoSpan = 32.0;
 constexpr int kTopoTets = 16, kTopoNodes = 16, kTopoEdges = 48, kTopoFaces = 40;
 struct NearTopo {
     std::vector<int32_t> blk;     // [nblk][4]: chunk begin, chunk end, target begin, target end
