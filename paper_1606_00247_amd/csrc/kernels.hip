@@ -2346,9 +2346,12 @@ __global__ __launch_bounds__(64, 4) void k_p2p_topo(const int32_t *__restrict__ 
                     const double cx0 = da[1] * db[2] - da[2] * db[1], cx1 = da[2] * db[0] - da[0] * db[2],
                                  cx2 = da[0] * db[1] - da[1] * db[0];
                     const double r0sq = (cx0 * cx0 + cx1 * cx1 + cx2 * cx2) * (E.il * E.il);
-                    const double f = edge_log<false, true>(Ra, Rb, la, lb, r0sq);
+                    const bool far = kEdgeMid * S >= E.L;
+                    const double f = edge_log_mixed(far, S, E.L, Ra, Rb, la, lb, r0sq);
+                    const double t = (Rb - Ra) * E.il, t2 = t * t, SL = S * E.L;
                     F = 0.5 * f;
-                    g = 2.0 * (r0sq * f + lb * Rb - la * Ra);
+                    g = far ? fma(fma(S, S, -E.l2) * (1.0 - t2), F, fma(t2, SL, SL))
+                            : 2.0 * (r0sq * f + lb * Rb - la * Ra);
                 }
                 const ScalarMem<TopoEdgeW> &W = W0[e];
                 double bq = W.B[1] * m[0];
@@ -2974,9 +2977,11 @@ __global__ __launch_bounds__(64 * kFieldWaves, 3) void k_p2p_fields(
                                  c1 = d[p][2] * d[q][0] - d[p][0] * d[q][2],
                                  c2 = d[p][0] * d[q][1] - d[p][1] * d[q][0];
                     const double r0sq = (c0 * c0 + c1 * c1 + c2 * c2) * il2;
-                    const double f = edge_log<false, true>(Rc[p], Rc[q], la, lb, r0sq);
+                    const double S = Rc[p] + Rc[q];
+                    const bool far = kEdgeMid * S >= K.L[e];
+                    const double f = edge_log_mixed(far, S, K.L[e], Rc[p], Rc[q], la, lb, r0sq);
                     Fe[e] = 0.5 * f * il;
-                    gp[e] = 2.0 * il * (r0sq * f + lb * Rc[q] - la * Rc[p]);
+                    gp[e] = far ? far_g(K, Rc, Fe, e) : 2.0 * il * (r0sq * f + lb * Rc[q] - la * Rc[p]);
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
