@@ -3792,6 +3792,14 @@ static QRows q_rows(const DevicePlan &dp, int32_t F)
 }
 // elements of the buffer they take: doubles of Qt or floats of Qtf
 static int64_t q_elems(const QRows &q) { return q.form == ROW_BF16 ? (q.count * q.np + 1) / 2 : q.count; }
+// elements that any form of up to F fields takes in Qt (fp64) or Qtf
+static int64_t q_room(const DevicePlan &dp, int32_t F, bool fp64)
+{
+    const int fpt = m2l_fpt(F);
+    const int64_t C = (int64_t)dp.hp.cells.size(), cells = (int64_t)((F + fpt - 1) / fpt) * fpt * C;
+    const int64_t tile = cells * m2l_tile_row(dp.hp.p);
+    return std::max<int64_t>(tile, fp64 ? F * C * dp.qpad : (cells * 32 * m2lb_ks(dp.hp.p, 0) * 3 + 1) / 2);
+}
 int m2l_pack_slot(int fpt)
 {
     int s = 0;
@@ -4272,24 +4280,28 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
         hip_check(hipEventCreateWithFlags(&dp.ev_join, hipEventDisableTiming), "hipEventCreate");
     }
     ensure_expansions(dp, F);
+    // Every buffer is made for the most fields yet and for every form of them, so that
+    // one in use is only ever replaced where the expansions are, on more fields: a
+    // graph that a caller captured stays good through other settings of the plan.
+    const int32_t most = dp.Fcap;
     const bool several = F > 1 && !dp.near_stored && dp.sur_mode == TFMM_SUR_OFF && dp.p2p_topo;
     if (several) ensure_near_tets(dp);
-    if (several && dp.near_w_cap < dp.near_rows * near_pass(F)) {
+    if (several && dp.near_w_cap < dp.near_rows * near_pass(most)) {
         ++dp.schedule_gen;  // a captured graph may hold the old weights
         if (dp.near_w) (void)hipFree(dp.near_w);
         dp.near_w = nullptr;
         dp.near_w_cap = 0;
-        hip_check(hipMalloc(&dp.near_w, sizeof(double) * (size_t)(dp.near_rows * near_pass(F))), "hipMalloc near weights");
-        dp.near_w_cap = dp.near_rows * near_pass(F);
+        hip_check(hipMalloc(&dp.near_w, sizeof(double) * (size_t)(dp.near_rows * near_pass(most))), "hipMalloc near weights");
+        dp.near_w_cap = dp.near_rows * near_pass(most);
     }
-    if (near_in_order(dp, F) && dp.u_cap < F) {
+    if (near_in_order(dp, F) && dp.u_cap < most) {
         ++dp.schedule_gen;  // a captured graph may hold the old potentials
         if (dp.u_tree) (void)hipFree(dp.u_tree);
         dp.u_tree = nullptr;
         dp.u_cap = 0;
-        hip_check(hipMalloc(&dp.u_tree, sizeof(double) * (size_t)F * std::max<int64_t>(1, dp.hp.n_targets)),
+        hip_check(hipMalloc(&dp.u_tree, sizeof(double) * (size_t)most * std::max<int64_t>(1, dp.hp.n_targets)),
                   "hipMalloc potentials");
-        dp.u_cap = F;
+        dp.u_cap = most;
     }
     if (m2l_packed(dp, F)) {
         ensure_m2l_packs(dp, F);
@@ -4297,16 +4309,17 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
         ensure_m2l_tiles(dp, 16 / m2l_fpt(F));
         if (dp.level_orders) ensure_m2l_level_tiles(dp, 16 / m2l_fpt(F));
     }
-    if (dp.lr_cap < F) {
+    if (dp.lr_cap < most) {
         ++dp.schedule_gen;
         if (dp.Lr) (void)hipFree(dp.Lr);
         dp.Lr = nullptr;
         dp.lr_cap = 0;
-        hip_check(hipMalloc(&dp.Lr, sizeof(double) * (size_t)F * C * m2l_nrows(dp.hp.p)), "hipMalloc Lr");
-        dp.lr_cap = F;
+        hip_check(hipMalloc(&dp.Lr, sizeof(double) * (size_t)most * C * m2l_nrows(dp.hp.p)), "hipMalloc Lr");
+        dp.lr_cap = most;
     }
-    const QRows q = q_rows(dp, F);
-    if (dp.m2l_precision != TFMM_M2L_FP64) {
+    const bool fp64 = dp.m2l_precision == TFMM_M2L_FP64;
+    const int64_t room = q_room(dp, most, fp64);
+    if (!fp64) {
         if (!dp.m2l_Df) {
             ++dp.schedule_gen;
             const int64_t n = (int64_t)dp.n_m2l_keys * nd_of(dp.hp.p);
@@ -4316,22 +4329,22 @@ void prepare_evaluate(DevicePlan &dp, int32_t F)
             hip_check(hipGetLastError(), "k_to_float launch");
             hip_check(hipDeviceSynchronize(), "k_to_float");
         }
-        if (dp.qtf_cap < q_elems(q)) {
+        if (dp.qtf_cap < room) {
             ++dp.schedule_gen;
             if (dp.Qtf) (void)hipFree(dp.Qtf);
             dp.Qtf = nullptr;
             dp.qtf_cap = 0;
-            hip_check(hipMalloc(&dp.Qtf, sizeof(float) * (size_t)q_elems(q)), "hipMalloc Qt f32");
-            dp.qtf_cap = q_elems(q);
+            hip_check(hipMalloc(&dp.Qtf, sizeof(float) * (size_t)room), "hipMalloc Qt f32");
+            dp.qtf_cap = room;
         }
-    } else if (dp.qt_cap < q_elems(q)) {
+    } else if (dp.qt_cap < room) {
         ++dp.schedule_gen;
         if (dp.Qt) (void)hipFree(dp.Qt - 1);
         dp.Qt = nullptr;
         dp.qt_cap = 0;
-        hip_check(hipMalloc(&dp.Qt, sizeof(double) * (size_t)(q_elems(q) + 2)), "hipMalloc Qt");
+        hip_check(hipMalloc(&dp.Qt, sizeof(double) * (size_t)(room + 2)), "hipMalloc Qt");
         dp.Qt += 1;  // entry 1 of every plain row (the first that counts) on a 16-byte boundary
-        dp.qt_cap = q_elems(q);
+        dp.qt_cap = room;
     }
 }
 
