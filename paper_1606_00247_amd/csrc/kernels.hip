@@ -1672,7 +1672,8 @@ __global__ __launch_bounds__(p2p_threads(FCH, WIDE), 2) void k_p2p(const int32_t
 // 15.8 ms with a rule per lane and 40 slots a point, now 3.5; 5 fields: 31.8 in
 // two passes, now 4.0.
 //
-// A workgroup stages DT consecutive tets in LDS and takes 256 targets at a time:
+// A workgroup stages 16 consecutive tets in LDS (four times 4 with 16 fields, whose
+// coefficients take the room) and takes 256 targets at a time:
 // the pairs are sorted by class (rule, or closed form) and its wavefronts take 64
 // pairs of one class after another, the most points first, so that no lane waits
 // for another's larger rule (5,900 slots a pair with the wavefront's largest, 4,400
@@ -1687,6 +1688,9 @@ struct DirectTet {
 };
 constexpr int kDirectFieldsMax = 16;
 __host__ __device__ constexpr int direct_stage(int FCH) { return FCH >= 16 ? 4 : 16; }
+// Tets of a workgroup: the fewer, the more sums are added to u one by one, each with
+// a rounding of u (24,576 tets: 2.9e-15 of the result with 4, 1.4e-15 with 16).
+constexpr int kDirectTets = 16;
 
 // Moments m = (A_0, A_1, A_2, A_3, A_11, A_12, A_13, A_22, A_23, A_33) of one
 // tet (edge vectors e[i] = v_(i+1) - v_0) at x = target - v_0 by the rule of N^3
@@ -1770,10 +1774,9 @@ __global__ __launch_bounds__(256, FCH <= 4 ? 3 : 2) void k_direct(int nblk, int6
     __shared__ int s_cnt[NC], s_next;
     const int b = xcd_item(nblk);
     if (b < 0) return;
-    const int64_t tb = (int64_t)b * DT;
-    const int nt = (int)min<int64_t>(DT, T - tb);
+    constexpr int NST = kDirectTets / DT;  // stages
     const int lane = threadIdx.x;
-    {
+    auto stage = [&](int64_t tb, int nt) {
         const int t = lane / FCH, f = lane % FCH;
         if (t < nt) {
             const int64_t tt = tb + t;
@@ -1814,7 +1817,9 @@ __global__ __launch_bounds__(256, FCH <= 4 ? 3 : 2) void k_direct(int nblk, int6
                 D.vol6 = fabs(det);
             }
         }
-    }
+    };
+    const int64_t tb0 = (int64_t)b * kDirectTets;
+    if constexpr (NST == 1) stage(tb0, (int)min<int64_t>(DT, T - tb0));
     __syncthreads();
     const int wl = lane & 63;
     for (int64_t i0 = (int64_t)blockIdx.y * 256; i0 < N; i0 += 256 * (int64_t)gridDim.y) {
@@ -1825,116 +1830,123 @@ __global__ __launch_bounds__(256, FCH <= 4 ? 3 : 2) void k_direct(int nblk, int6
         for (int k = 0; k < 3; ++k) s_x[k][lane] = x[k];
 #pragma unroll
         for (int f = 0; f < FCH; ++f) s_u[f][lane] = 0.0;
-        if (lane < NC) s_cnt[lane] = 0;
-        if (lane == NC) s_next = 0;
-        __syncthreads();
-        // sort the pairs (tet, target) by class: count, then place
-        uint64_t cls = 0;  // this target's class per tet, 4 bits each
-        int at[NC];
-#pragma unroll
-        for (int k = 0; k < NC; ++k) at[k] = 0;
 #pragma unroll 1
-        for (int t = 0; t < nt; ++t) {
-            const DirectTet &D = s_t[t];
-            const double dc0 = x[0] - D.c[0], dc1 = x[1] - D.c[1], dc2 = x[2] - D.c[2];
-            const double rat2 = (dc0 * dc0 + dc1 * dc1 + dc2 * dc2) * D.id2;
-            int c = 0;
+        for (int st = 0; st < NST; ++st) {
+            const int64_t tb = tb0 + st * DT;
+            const int nt = (int)min<int64_t>(DT, T - tb);
+            if (nt <= 0) break;
+            if constexpr (NST > 1) stage(tb, nt);
+            if (lane < NC) s_cnt[lane] = 0;
+            if (lane == NC) s_next = 0;
+            __syncthreads();
+            // sort the pairs (tet, target) by class: count, then place
+            uint64_t cls = 0;  // this target's class per tet, 4 bits each
+            int at[NC];
 #pragma unroll
-            for (int k = 1; k < kFarRules; ++k) c += !(rat2 < kFarRatio[k] * kFarRatio[k]);
-            if (rat2 < kFarRatio[0] * kFarRatio[0]) c = kFarRules;
-            if (!ok) c = 15;
-            cls |= (uint64_t)c << (4 * t);
-#pragma unroll
-            for (int k = 0; k < NC; ++k) at[k] += __popcll(__ballot(c == k));
-        }
-#pragma unroll
-        for (int k = 0; k < NC; ++k) {
-            int base = 0;
-            if (wl == 0) base = atomicAdd(&s_cnt[k], at[k]);
-            at[k] = __builtin_amdgcn_readfirstlane(base);
-        }
-        __syncthreads();
-        int cnt[NC], start[NC + 1];
-        start[0] = 0;
-#pragma unroll
-        for (int k = 0; k < NC; ++k) {
-            cnt[k] = __builtin_amdgcn_readfirstlane(s_cnt[k]);
-            start[k + 1] = start[k] + cnt[k];
-            at[k] += start[k];
-        }
+            for (int k = 0; k < NC; ++k) at[k] = 0;
 #pragma unroll 1
-        for (int t = 0; t < nt; ++t) {
-            const int c = (int)(cls >> (4 * t)) & 15;
-#pragma unroll
-            for (int k = 0; k < NC; ++k) {
-                const uint64_t mask = __ballot(c == k);
-                if (c == k) s_pair[at[k] + __popcll(mask & ((1ull << wl) - 1))] = (uint16_t)(t * 256 + lane);
-                at[k] += __popcll(mask);
-            }
-        }
-        __syncthreads();
-        for (;;) {
-            int chunk = 0;
-            if (wl == 0) chunk = atomicAdd(&s_next, 1);
-            chunk = __builtin_amdgcn_readfirstlane(chunk);
-            int c = 0, p0 = 0, p1 = 0;
-#pragma unroll
-            for (int k = 0; k < NC; ++k) {
-                const int nch = (cnt[k] + 63) / 64;
-                if (chunk >= 0 && chunk < nch) {
-                    c = k;
-                    p0 = start[k] + 64 * chunk;
-                    p1 = start[k + 1];
-                }
-                chunk -= nch;
-            }
-            if (chunk >= 0) break;
-            const bool on = p0 + wl < p1;
-            const int pr = s_pair[on ? p0 + wl : p1 - 1], t = pr >> 8, j = pr & 255;
-            const double y[3] = {s_x[0][j], s_x[1][j], s_x[2][j]};
-            double acc[FCH];
-            if (c == kFarRules) {
-#pragma unroll
-                for (int f = 0; f < FCH; ++f) acc[f] = 0.0;
-                pair_accumulate<FCH>(y, s_g[t], s_f[t], acc);
-            } else {
+            for (int t = 0; t < nt; ++t) {
                 const DirectTet &D = s_t[t];
-                const double xv[3] = {y[0] - s_g[t].v[0][0], y[1] - s_g[t].v[0][1], y[2] - s_g[t].v[0][2]};
-                double e[3][3], m[10];
+                const double dc0 = x[0] - D.c[0], dc1 = x[1] - D.c[1], dc2 = x[2] - D.c[2];
+                const double rat2 = (dc0 * dc0 + dc1 * dc1 + dc2 * dc2) * D.id2;
+                int c = 0;
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
+                for (int k = 1; k < kFarRules; ++k) c += !(rat2 < kFarRatio[k] * kFarRatio[k]);
+                if (rat2 < kFarRatio[0] * kFarRatio[0]) c = kFarRules;
+                if (!ok) c = 15;
+                cls |= (uint64_t)c << (4 * t);
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) e[q][k] = D.e[q][k];
-                switch (c) {
-                case 0: far_moments<kFarPts[0]>(xv, e, rules + far_offset(0), m); break;
-                case 1: far_moments<kFarPts[1]>(xv, e, rules + far_offset(1), m); break;
-                case 2: far_moments<kFarPts[2]>(xv, e, rules + far_offset(2), m); break;
-                default: far_moments<kFarPts[3]>(xv, e, rules + far_offset(3), m); break;
-                }
-                double K[4][3];
+                for (int k = 0; k < NC; ++k) at[k] += __popcll(__ballot(c == k));
+            }
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    K[0][k] = D.vol6 * fma(m[0], xv[k], -fma(m[1], e[0][k], fma(m[2], e[1][k], m[3] * e[2][k])));
-                    K[1][k] = D.vol6 * fma(m[1], xv[k], -fma(m[4], e[0][k], fma(m[5], e[1][k], m[6] * e[2][k])));
-                    K[2][k] = D.vol6 * fma(m[2], xv[k], -fma(m[5], e[0][k], fma(m[7], e[1][k], m[8] * e[2][k])));
-                    K[3][k] = D.vol6 * fma(m[3], xv[k], -fma(m[6], e[0][k], fma(m[8], e[1][k], m[9] * e[2][k])));
-                }
+            for (int k = 0; k < NC; ++k) {
+                int base = 0;
+                if (wl == 0) base = atomicAdd(&s_cnt[k], at[k]);
+                at[k] = __builtin_amdgcn_readfirstlane(base);
+            }
+            __syncthreads();
+            int cnt[NC], start[NC + 1];
+            start[0] = 0;
 #pragma unroll
-                for (int f = 0; f < FCH; ++f) {
-                    const double *M4 = s_m[t][f];
-                    double v = 0.0;
+            for (int k = 0; k < NC; ++k) {
+                cnt[k] = __builtin_amdgcn_readfirstlane(s_cnt[k]);
+                start[k + 1] = start[k] + cnt[k];
+                at[k] += start[k];
+            }
+#pragma unroll 1
+            for (int t = 0; t < nt; ++t) {
+                const int c = (int)(cls >> (4 * t)) & 15;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) v = fma(M4[3 * q + k], K[q][k], v);
-                    acc[f] = v;
+                for (int k = 0; k < NC; ++k) {
+                    const uint64_t mask = __ballot(c == k);
+                    if (c == k) s_pair[at[k] + __popcll(mask & ((1ull << wl) - 1))] = (uint16_t)(t * 256 + lane);
+                    at[k] += __popcll(mask);
                 }
             }
-            if (on)
+            __syncthreads();
+            for (;;) {
+                int chunk = 0;
+                if (wl == 0) chunk = atomicAdd(&s_next, 1);
+                chunk = __builtin_amdgcn_readfirstlane(chunk);
+                int c = 0, p0 = 0, p1 = 0;
 #pragma unroll
-                for (int f = 0; f < FCH; ++f) atomicAdd(&s_u[f][j], acc[f]);
+                for (int k = 0; k < NC; ++k) {
+                    const int nch = (cnt[k] + 63) / 64;
+                    if (chunk >= 0 && chunk < nch) {
+                        c = k;
+                        p0 = start[k] + 64 * chunk;
+                        p1 = start[k + 1];
+                    }
+                    chunk -= nch;
+                }
+                if (chunk >= 0) break;
+                const bool on = p0 + wl < p1;
+                const int pr = s_pair[on ? p0 + wl : p1 - 1], t = pr >> 8, j = pr & 255;
+                const double y[3] = {s_x[0][j], s_x[1][j], s_x[2][j]};
+                double acc[FCH];
+                if (c == kFarRules) {
+#pragma unroll
+                    for (int f = 0; f < FCH; ++f) acc[f] = 0.0;
+                    pair_accumulate<FCH>(y, s_g[t], s_f[t], acc);
+                } else {
+                    const DirectTet &D = s_t[t];
+                    const double xv[3] = {y[0] - s_g[t].v[0][0], y[1] - s_g[t].v[0][1], y[2] - s_g[t].v[0][2]};
+                    double e[3][3], m[10];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) e[q][k] = D.e[q][k];
+                    switch (c) {
+                    case 0: far_moments<kFarPts[0]>(xv, e, rules + far_offset(0), m); break;
+                    case 1: far_moments<kFarPts[1]>(xv, e, rules + far_offset(1), m); break;
+                    case 2: far_moments<kFarPts[2]>(xv, e, rules + far_offset(2), m); break;
+                    default: far_moments<kFarPts[3]>(xv, e, rules + far_offset(3), m); break;
+                    }
+                    double K[4][3];
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        K[0][k] = D.vol6 * fma(m[0], xv[k], -fma(m[1], e[0][k], fma(m[2], e[1][k], m[3] * e[2][k])));
+                        K[1][k] = D.vol6 * fma(m[1], xv[k], -fma(m[4], e[0][k], fma(m[5], e[1][k], m[6] * e[2][k])));
+                        K[2][k] = D.vol6 * fma(m[2], xv[k], -fma(m[5], e[0][k], fma(m[7], e[1][k], m[8] * e[2][k])));
+                        K[3][k] = D.vol6 * fma(m[3], xv[k], -fma(m[6], e[0][k], fma(m[8], e[1][k], m[9] * e[2][k])));
+                    }
+#pragma unroll
+                    for (int f = 0; f < FCH; ++f) {
+                        const double *M4 = s_m[t][f];
+                        double v = 0.0;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+#pragma unroll
+                            for (int k = 0; k < 3; ++k) v = fma(M4[3 * q + k], K[q][k], v);
+                        acc[f] = v;
+                    }
+                }
+                if (on)
+#pragma unroll
+                    for (int f = 0; f < FCH; ++f) atomicAdd(&s_u[f][j], acc[f]);
+            }
+            __syncthreads();
         }
-        __syncthreads();
         if (ok) {
             const int64_t o = tgt_perm[i];
 #pragma unroll
@@ -4673,7 +4685,7 @@ void run_direct(DevicePlan &dp, const double *M, int32_t F, double *u, hipStream
         const int left = F - f;
         auto go = [&](auto fc) {
             constexpr int FC = decltype(fc)::value;
-            const int nblk = (int)((hp.n_tets + direct_stage(FC) - 1) / direct_stage(FC));
+            const int nblk = (int)((hp.n_tets + kDirectTets - 1) / kDirectTets);
             // enough workgroups for five rounds of three a CU; more would only stage the tets again
             const int64_t shares = std::min<int64_t>((hp.n_targets + 255) / 256, std::max(1, (4096 + nblk - 1) / nblk));
             k_direct<FC><<<dim3(xcd_grid(nblk), (unsigned)shares), dim3(256), 0, st>>>(
