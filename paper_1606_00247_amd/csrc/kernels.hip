@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstdio>
 #include <mutex>
@@ -4410,7 +4411,10 @@ void autotune(DevicePlan &dp, hipStream_t st)
         dp.m2l_max_ent = best_ent;
         dp.m2l_pack = true;
         if (m2l_packed(dp, 1)) {
-            std::vector<std::vector<int>> tried;  // caps with the same cuts are one schedule, the plan's own first
+            // caps with the same cuts are one schedule, known by the plan's own cap or the
+            // largest; timed in turn, twice, so that a clock still rising favours none
+            std::vector<std::vector<int>> tried;
+            std::vector<int> caps;
             for (int grp : {best_grp, 1024, 512}) {
                 dp.m2l_max_grp = grp;
                 prepare_evaluate(dp, 1);
@@ -4421,9 +4425,16 @@ void autotune(DevicePlan &dp, hipStream_t st)
                     cuts.push_back(pack_cut(dp, dp.m2l_packs[0], 1));
                 if (std::find(tried.begin(), tried.end(), cuts) != tried.end()) continue;
                 tried.push_back(cuts);
-                const float t = time_config(dp, M, u, st);
-                if (t < best) best = t, best_grp = grp, best_pack = true;
+                caps.push_back(grp);
             }
+            std::vector<float> ms(caps.size(), FLT_MAX);
+            for (int turn = 0; turn < 2; ++turn)
+                for (size_t c = 0; c < caps.size(); ++c) {
+                    dp.m2l_max_grp = caps[c];
+                    ms[c] = std::min(ms[c], time_config(dp, M, u, st));
+                }
+            for (size_t c = 0; c < caps.size(); ++c)
+                if (ms[c] < best) best = ms[c], best_grp = caps[c], best_pack = true;
         }
         dp.m2l_pack = best_pack;
         dp.m2l_max_grp = best_grp;
